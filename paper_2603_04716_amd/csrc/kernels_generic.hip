@@ -634,12 +634,81 @@ __global__ void kv_copy_kernel(T *ck, T *cv, T *k, T *v, int slot, int Hkv, int 
     }
 }
 
+// The same for the blocked layouts, a block of positions at a time.  Bound by memory; element-wise, a slot
+// leaves the cache in 2-byte accesses, because a position's values lie 64 bytes apart: 2050 positions of
+// 8 heads took 10.6 us, this way 4.3 us (16.8 MB read and written: 3.9 TB/s).  Here a workgroup moves one block of 32 (bf16) or 64
+// (8-bit) positions of one kv head, keys or values, with 8- and 16-byte accesses on both sides: a key run of 8
+// channels is contiguous in the cache as it is, values turn through LDS.  kVtRow: the row stride that puts
+// the four position groups of a wave's transposing accesses on different banks and keeps rows
+// 16-byte aligned.
+constexpr int kVtRow = 128 + 8;
+
+template <bool TO_CACHE>
+__global__ __launch_bounds__(256) void kv_copy_block_kernel(uint16_t *ck, uint16_t *cv, uint16_t *k, uint16_t *v, int slot,
+                                                            int Hkv, int len, int max_len_pad)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t tile[32 * kVtRow];
+    const int p0 = blockIdx.x * 32, g = blockIdx.y, tid = threadIdx.x;
+    const int n_pos = len - p0 < 32 ? len - p0 : 32;
+    const size_t plane = ((size_t)slot * Hkv + g) * max_len_pad * 128;
+    const size_t user = ((size_t)g * len + p0) * 128;
+    if (blockIdx.z == 0) {
+        for (int e = tid; e < n_pos * 16; e += 256) {
+            uint4 *c = (uint4 *)(ck + plane + kblk_off(p0 + (e >> 4), (e & 15) * 8));
+            uint4 *u = (uint4 *)(k + user + (size_t)e * 8);
+            if (TO_CACHE) *c = *u;
+            else *u = *c;
+        }
+        return;
+    }
+    uint16_t *vb = cv + plane + (size_t)(p0 >> 5) * 4096;          // [channel][sigma(position)]
+    if (TO_CACHE) {
+        if (n_pos < 32) {                                          // positions past the end keep their contents
+            for (int e = tid; e < n_pos * 128; e += 256) vb[vblk_off(e >> 7, e & 127)] = v[user + e];
+            return;
+        }
+        for (int e = tid; e < 32 * 16; e += 256)
+            *(uint4 *)(tile + (e >> 4) * kVtRow + (e & 15) * 8) = *(const uint4 *)(v + user + (size_t)e * 8);
+        __syncthreads();
+    }
+    // chunk e of the block: channel e / 4, positions 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3 with q = e % 4
+    for (int e = tid; e < 128 * 4; e += 256) {
+        const int d = e >> 2, q = e & 3;
+        uint16_t *t = tile + 4 * q * kVtRow + d;
+        uint4 x;
+        if (TO_CACHE) {
+            x.x = t[0] | ((uint32_t)t[kVtRow] << 16);
+            x.y = t[2 * kVtRow] | ((uint32_t)t[3 * kVtRow] << 16);
+            x.z = t[16 * kVtRow] | ((uint32_t)t[17 * kVtRow] << 16);
+            x.w = t[18 * kVtRow] | ((uint32_t)t[19 * kVtRow] << 16);
+            *(uint4 *)(vb + (size_t)e * 8) = x;
+        } else {
+            x = *(const uint4 *)(vb + (size_t)e * 8);
+            t[0] = (uint16_t)x.x; t[kVtRow] = (uint16_t)(x.x >> 16);
+            t[2 * kVtRow] = (uint16_t)x.y; t[3 * kVtRow] = (uint16_t)(x.y >> 16);
+            t[16 * kVtRow] = (uint16_t)x.z; t[17 * kVtRow] = (uint16_t)(x.z >> 16);
+            t[18 * kVtRow] = (uint16_t)x.w; t[19 * kVtRow] = (uint16_t)(x.w >> 16);
+        }
+    }
+    if (!TO_CACHE) {
+        __syncthreads();
+        for (int e = tid; e < n_pos * 16; e += 256)
+            *(uint4 *)(v + user + (size_t)e * 8) = *(const uint4 *)(tile + (e >> 4) * kVtRow + (e & 15) * 8);
+    }
+}
+
 hipError_t launch_kv_copy(int dtype, void *cache_k, void *cache_v, const void *k, const void *v,
                           int slot, int Hkv, int len, int hd, int max_len, int blocked, int to_cache,
                           hipStream_t s)
 {
     size_t n = (size_t)Hkv * len * hd;
     if (n == 0) return hipSuccess;
+    if (blocked && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
+        const dim3 grid((unsigned)((len + 31) / 32), (unsigned)Hkv, 2);
+        auto *kern = to_cache ? kv_copy_block_kernel<true> : kv_copy_block_kernel<false>;
+        kern<<<grid, 256, 0, s>>>((uint16_t *)cache_k, (uint16_t *)cache_v, (uint16_t *)k, (uint16_t *)v, slot, Hkv, len, max_len);
+        return hipGetLastError();
+    }
     unsigned grid = (unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
     if (dtype == PD_F32)
         kv_copy_kernel<float><<<grid, 256, 0, s>>>((float *)cache_k, (float *)cache_v, (float *)k,
@@ -676,12 +745,62 @@ __global__ void kv_copy_fp8_kernel(uint8_t *ck, uint8_t *cv, bf16_t *k, bf16_t *
     }
 }
 
+// Out of the 8-bit cache, a block of 64 positions of one kv head at a time (see kv_copy_block_kernel), the
+// same conversion per element.
+__device__ __forceinline__ uint32_t e4m3_pair_to_bf16(uint32_t two_codes, double scale)
+{
+    return pack2bf((float)(scale * (double)e4m3_decode(two_codes & 0xffu)), (float)(scale * (double)e4m3_decode((two_codes >> 8) & 0xffu)));
+}
+__global__ __launch_bounds__(256) void kv_read_block_fp8_kernel(const uint8_t *__restrict__ ck, const uint8_t *__restrict__ cv,
+                                                                uint16_t *__restrict__ k, uint16_t *__restrict__ v, int slot,
+                                                                int Hkv, int len, int max_len_pad, double k_scale, double v_scale)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t tile[64 * kVtRow];
+    const int p0 = blockIdx.x * 64, g = blockIdx.y, tid = threadIdx.x;
+    const int n_pos = len - p0 < 64 ? len - p0 : 64;
+    const size_t plane = ((size_t)slot * Hkv + g) * max_len_pad * 128;
+    const size_t user = ((size_t)g * len + p0) * 128;
+    if (blockIdx.z == 0) {
+        for (int e = tid; e < n_pos * 16; e += 256) {
+            const uint2 c = *(const uint2 *)(ck + plane + kblk8_off(p0 + (e >> 4), (e & 15) * 8));
+            *(uint4 *)(k + user + (size_t)e * 8) = make_uint4(e4m3_pair_to_bf16(c.x, k_scale), e4m3_pair_to_bf16(c.x >> 16, k_scale),
+                                                              e4m3_pair_to_bf16(c.y, k_scale), e4m3_pair_to_bf16(c.y >> 16, k_scale));
+        }
+        return;
+    }
+    // run e of the block (8 bytes): channel 16 (e / 128) + e / 2 % 16, half e % 2 of the positions, and inside it
+    // positions 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3 with q = e / 32 % 4
+    const uint8_t *vb = cv + plane + (size_t)(p0 >> 6) * 8192;
+    for (int e = tid; e < 1024; e += 256) {
+        const int d = (e >> 7) * 16 + ((e >> 1) & 15), q = (e >> 5) & 3;
+        uint16_t *t = tile + ((e & 1) * 32 + 4 * q) * kVtRow + d;
+        const uint2 c = *(const uint2 *)(vb + (size_t)e * 8);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t w = j ? c.y : c.x;
+            const uint32_t lo = e4m3_pair_to_bf16(w, v_scale), hi = e4m3_pair_to_bf16(w >> 16, v_scale);
+            uint16_t *tj = t + 16 * j * kVtRow;
+            tj[0] = (uint16_t)lo; tj[kVtRow] = (uint16_t)(lo >> 16);
+            tj[2 * kVtRow] = (uint16_t)hi; tj[3 * kVtRow] = (uint16_t)(hi >> 16);
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < n_pos * 16; e += 256)
+        *(uint4 *)(v + user + (size_t)e * 8) = *(const uint4 *)(tile + (e >> 4) * kVtRow + (e & 15) * 8);
+}
+
 hipError_t launch_kv_copy_fp8(void *cache_k, void *cache_v, const void *k, const void *v, int slot, int Hkv,
                               int len, int max_len_pad, double k_scale, double v_scale, int to_cache,
                               hipStream_t s)
 {
     size_t n = (size_t)Hkv * len * 128;
     if (n == 0) return hipSuccess;
+    if (!to_cache && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
+        const dim3 blocks((unsigned)((len + 63) / 64), (unsigned)Hkv, 2);
+        kv_read_block_fp8_kernel<<<blocks, 256, 0, s>>>((const uint8_t *)cache_k, (const uint8_t *)cache_v, (uint16_t *)k, (uint16_t *)v,
+                                                        slot, Hkv, len, max_len_pad, k_scale, v_scale);
+        return hipGetLastError();
+    }
     unsigned grid = (unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
     kv_copy_fp8_kernel<<<grid, 256, 0, s>>>((uint8_t *)cache_k, (uint8_t *)cache_v, (bf16_t *)k, (bf16_t *)v,
                                             slot, Hkv, len, max_len_pad, k_scale, v_scale, to_cache);

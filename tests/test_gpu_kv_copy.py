@@ -1,0 +1,50 @@
+"""Cache fill and read-back over the blocked layouts: whole and partial blocks, tensors that are and are not
+16-byte aligned, and what a fill must leave alone."""
+import pytest
+import torch
+
+import paper_2603_04716_amd as pd
+import pd_inputs as I
+from gpu_util import GpuLayer
+
+pytestmark = pytest.mark.gpu
+
+CFG = I.small_config(dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=512)
+
+
+def _tensors(n, seed, shift):
+    """Two [2, n, 128] bf16 tensors whose first element sits `shift` elements behind a 16-byte boundary."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    flat = torch.randn((2, 2 * n * 128 + 8), device="cuda", generator=gen).to(torch.bfloat16)
+    return [f[shift:shift + 2 * n * 128].view(2, n, 128) for f in flat]
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 127, 200])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_set_get_blocks(fp8, n, shift):
+    gl = GpuLayer(CFG, I.layer_weights(CFG, std=0.05))
+    cap = 203
+    gc = gl.cache(3, cap, fp8_scales=(0.5, 0.125) if fp8 else None)
+    full_k, full_v = _tensors(cap, 1, 0)
+    for s in range(3):
+        pd.pd_kv_cache_set(gc, s, full_k, full_v)
+    k, v = _tensors(n, 2, shift)
+    pd.pd_kv_cache_set(gc, 1, k, v)
+    pd.pd_kv_cache_set_len(gc, 1, cap)           # positions behind the new ones must still be the old ones
+
+    def stored(t, scale):
+        if not fp8:
+            return t
+        return (t.float() / scale).clamp(-448, 448).to(torch.float8_e4m3fn).float().mul(scale).to(torch.bfloat16)
+
+    for s in (0, 1, 2):
+        want_k, want_v = stored(full_k, 0.5).clone(), stored(full_v, 0.125).clone()
+        if s == 1:
+            want_k[:, :n], want_v[:, :n] = stored(k, 0.5), stored(v, 0.125)
+        for length in (cap, n):
+            gk, gv = _tensors(length, 3, shift)
+            pd.pd_kv_cache_get(gc, s, gk, gv)
+            torch.cuda.synchronize()
+            assert torch.equal(gk, want_k[:, :length]) and torch.equal(gv, want_v[:, :length])
+    gl.close()
