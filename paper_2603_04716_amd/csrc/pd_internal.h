@@ -216,7 +216,9 @@ struct GemmArgs {
 // ---- launchers (each returns hipGetLastError() after the launch) ------------------------------
 hipError_t launch_rmsnorm(int dtype, const void *x, const void *g, void *y, int T, int d, float eps,
                           hipStream_t s);
-hipError_t launch_gemm_generic(int dtype, const GemmArgs &a, hipStream_t s);
+hipError_t launch_gemm_generic(int dtype, const GemmArgs &a, hipStream_t s);   // fp32: through the next where it can
+bool gemm_f32_mfma_supported(const GemmArgs &a);
+hipError_t launch_gemm_f32_mfma(const GemmArgs &a, hipStream_t s);
 bool gemm_mfma_supported(const GemmArgs &a);
 hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s);   // bf16 only
 bool gemm_mfma_f8_supported(const GemmArgs &a);                   // E4M3 x E4M3, dense

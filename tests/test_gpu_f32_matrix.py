@@ -1,0 +1,51 @@
+"""fp32 layers on the fp32 matrix instructions and the split attention: tile edges, K that is not a multiple of
+the 16-wide k-step, both tile sizes, every head size with its own form, one and four waves per attention row.
+Bound: the fp32 bound of the other parity tests, 1e-5 of the largest element."""
+import numpy as np
+import pytest
+
+import pd_inputs as I
+from oracle import layer as O
+from gpu_util import GpuLayer, TOL, relmax
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows", [[1], [15], [17, 1], [33], [65, 64], [300, 401]])
+@pytest.mark.parametrize("cfg", [
+    I.small_config(d_model=100, d_ff=516),                                    # K = 100: a last k-step of 4
+    I.small_config(d_model=516, n_q_heads=8, n_kv_heads=2, head_dim=64, d_ff=260),
+    I.small_config(d_model=64, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=64),
+    I.small_config(d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=256, d_ff=68),
+    I.small_config(d_model=96, d_ff=132, n_experts=5, top_k=2),
+], ids=["k100", "k516_hd64", "hd128", "hd256", "moe"])
+def test_prefill_then_decode(cfg, rows):
+    w = I.layer_weights(cfg, std=0.05)
+    ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
+    cu = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    n, cap = len(rows), max(rows) + 2
+    slots = list(range(n))
+    oc, gc = O.KVCache(ol, n, cap), gl.cache(n, cap)
+    rl = I.router_logits(int(cu[-1]), cfg["n_experts"], seed=5) if cfg["n_experts"] else None
+    x = I.hidden(int(cu[-1]), cfg["d_model"], seed=21)
+    assert relmax(gl.prefill(x, cu, gc, slots, rl), O.prefill(ol, x, cu, rl, cache=oc, slots=slots)) <= TOL["f32"]
+    for step in range(2):
+        xn = I.hidden(n, cfg["d_model"], seed=30 + step)
+        rn = None if rl is None else I.router_logits(n, cfg["n_experts"], seed=40 + step)
+        assert relmax(gl.decode(xn, slots, gc, rn), O.decode_step(ol, xn, slots, oc, rn)) <= TOL["f32"]
+    gl.close()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_unseen_keys_do_not_reach_a_query(head_dim):
+    """A token that is not finite leaves every earlier row of its sequence, and every other sequence, as it was."""
+    cfg = I.small_config(d_model=64, n_q_heads=2, n_kv_heads=1, head_dim=head_dim, d_ff=64)
+    gl = GpuLayer(cfg, I.layer_weights(cfg, std=0.05))
+    cu = np.array([0, 40, 60], np.int32)
+    x = I.hidden(60, cfg["d_model"], seed=3)
+    want = gl.prefill(x, cu)
+    x[21] = np.inf
+    got = gl.prefill(x, cu)
+    clean = np.r_[0:21, 40:60]
+    assert np.array_equal(got[clean], want[clean]) and not np.isfinite(got[21:40]).any()
+    gl.close()
