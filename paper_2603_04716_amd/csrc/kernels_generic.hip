@@ -883,13 +883,14 @@ __global__ void kv_copy_kernel(T *ck, T *cv, T *k, T *v, int slot, int Hkv, int 
 // leaves the cache in 2-byte accesses, because a position's values lie 64 bytes apart: 2050 positions of
 // 8 heads took 10.6 us, this way 4.3 us (16.8 MB read and written: 3.9 TB/s).  Here a workgroup moves one block of 32 (bf16) or 64
 // (8-bit) positions of one kv head, keys or values, with 8- and 16-byte accesses on both sides: a key run of 8
-// channels is contiguous in the cache as it is, values turn through LDS.  kVtRow: the row stride that puts
+// channels is contiguous in the cache as it is, values turn through LDS; a thread makes one access per pass, so
+// that a slot of a few positions costs one round trip.  kVtRow: the row stride that puts
 // the four position groups of a wave's transposing accesses on different banks and keeps rows
 // 16-byte aligned.
 constexpr int kVtRow = 128 + 8;
 
 template <bool TO_CACHE>
-__global__ __launch_bounds__(256) void kv_copy_block_kernel(uint16_t *ck, uint16_t *cv, uint16_t *k, uint16_t *v, int slot,
+__global__ __launch_bounds__(512) void kv_copy_block_kernel(uint16_t *ck, uint16_t *cv, uint16_t *k, uint16_t *v, int slot,
                                                             int Hkv, int len, int max_len_pad)
 {
     __shared__ __attribute__((aligned(16))) uint16_t tile[32 * kVtRow];
@@ -898,7 +899,7 @@ __global__ __launch_bounds__(256) void kv_copy_block_kernel(uint16_t *ck, uint16
     const size_t plane = ((size_t)slot * Hkv + g) * max_len_pad * 128;
     const size_t user = ((size_t)g * len + p0) * 128;
     if (blockIdx.z == 0) {
-        for (int e = tid; e < n_pos * 16; e += 256) {
+        for (int e = tid; e < n_pos * 16; e += 512) {
             uint4 *c = (uint4 *)(ck + plane + kblk_off(p0 + (e >> 4), (e & 15) * 8));
             uint4 *u = (uint4 *)(k + user + (size_t)e * 8);
             if (TO_CACHE) *c = *u;
@@ -909,16 +910,17 @@ __global__ __launch_bounds__(256) void kv_copy_block_kernel(uint16_t *ck, uint16
     uint16_t *vb = cv + plane + (size_t)(p0 >> 5) * 4096;          // [channel][sigma(position)]
     if (TO_CACHE) {
         if (n_pos < 32) {                                          // positions past the end keep their contents
-            for (int e = tid; e < n_pos * 128; e += 256) vb[vblk_off(e >> 7, e & 127)] = v[user + e];
+            for (int e = tid; e < n_pos * 128; e += 512) vb[vblk_off(e >> 7, e & 127)] = v[user + e];
             return;
         }
-        for (int e = tid; e < 32 * 16; e += 256)
+        for (int e = tid; e < 32 * 16; e += 512)
             *(uint4 *)(tile + (e >> 4) * kVtRow + (e & 15) * 8) = *(const uint4 *)(v + user + (size_t)e * 8);
         __syncthreads();
     }
     // chunk e of the block: channel e / 4, positions 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3 with q = e % 4
-    for (int e = tid; e < 128 * 4; e += 256) {
+    for (int e = tid; e < 128 * 4; e += 512) {
         const int d = e >> 2, q = e & 3;
+        if (4 * q >= n_pos) continue;
         uint16_t *t = tile + 4 * q * kVtRow + d;
         uint4 x;
         if (TO_CACHE) {
@@ -937,7 +939,7 @@ __global__ __launch_bounds__(256) void kv_copy_block_kernel(uint16_t *ck, uint16
     }
     if (!TO_CACHE) {
         __syncthreads();
-        for (int e = tid; e < n_pos * 16; e += 256)
+        for (int e = tid; e < n_pos * 16; e += 512)
             *(uint4 *)(v + user + (size_t)e * 8) = *(const uint4 *)(tile + (e >> 4) * kVtRow + (e & 15) * 8);
     }
 }
@@ -951,7 +953,7 @@ hipError_t launch_kv_copy(int dtype, void *cache_k, void *cache_v, const void *k
     if (blocked && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
         const dim3 grid((unsigned)((len + 31) / 32), (unsigned)Hkv, 2);
         auto *kern = to_cache ? kv_copy_block_kernel<true> : kv_copy_block_kernel<false>;
-        kern<<<grid, 256, 0, s>>>((uint16_t *)cache_k, (uint16_t *)cache_v, (uint16_t *)k, (uint16_t *)v, slot, Hkv, len, max_len);
+        kern<<<grid, 512, 0, s>>>((uint16_t *)cache_k, (uint16_t *)cache_v, (uint16_t *)k, (uint16_t *)v, slot, Hkv, len, max_len);
         return hipGetLastError();
     }
     unsigned grid = (unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
@@ -996,7 +998,7 @@ __device__ __forceinline__ uint32_t e4m3_pair_to_bf16(uint32_t two_codes, double
 {
     return pack2bf((float)(scale * (double)e4m3_decode(two_codes & 0xffu)), (float)(scale * (double)e4m3_decode((two_codes >> 8) & 0xffu)));
 }
-__global__ __launch_bounds__(256) void kv_read_block_fp8_kernel(const uint8_t *__restrict__ ck, const uint8_t *__restrict__ cv,
+__global__ __launch_bounds__(1024) void kv_read_block_fp8_kernel(const uint8_t *__restrict__ ck, const uint8_t *__restrict__ cv,
                                                                 uint16_t *__restrict__ k, uint16_t *__restrict__ v, int slot,
                                                                 int Hkv, int len, int max_len_pad, double k_scale, double v_scale)
 {
@@ -1006,7 +1008,7 @@ __global__ __launch_bounds__(256) void kv_read_block_fp8_kernel(const uint8_t *_
     const size_t plane = ((size_t)slot * Hkv + g) * max_len_pad * 128;
     const size_t user = ((size_t)g * len + p0) * 128;
     if (blockIdx.z == 0) {
-        for (int e = tid; e < n_pos * 16; e += 256) {
+        for (int e = tid; e < n_pos * 16; e += 1024) {
             const uint2 c = *(const uint2 *)(ck + plane + kblk8_off(p0 + (e >> 4), (e & 15) * 8));
             *(uint4 *)(k + user + (size_t)e * 8) = make_uint4(e4m3_pair_to_bf16(c.x, k_scale), e4m3_pair_to_bf16(c.x >> 16, k_scale),
                                                               e4m3_pair_to_bf16(c.y, k_scale), e4m3_pair_to_bf16(c.y >> 16, k_scale));
@@ -1016,8 +1018,9 @@ __global__ __launch_bounds__(256) void kv_read_block_fp8_kernel(const uint8_t *_
     // run e of the block (8 bytes): channel 16 (e / 128) + e / 2 % 16, half e % 2 of the positions, and inside it
     // positions 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3 with q = e / 32 % 4
     const uint8_t *vb = cv + plane + (size_t)(p0 >> 6) * 8192;
-    for (int e = tid; e < 1024; e += 256) {
+    for (int e = tid; e < 1024; e += 1024) {
         const int d = (e >> 7) * 16 + ((e >> 1) & 15), q = (e >> 5) & 3;
+        if ((e & 1) * 32 + 4 * q >= n_pos) continue;
         uint16_t *t = tile + ((e & 1) * 32 + 4 * q) * kVtRow + d;
         const uint2 c = *(const uint2 *)(vb + (size_t)e * 8);
 #pragma unroll
@@ -1030,7 +1033,7 @@ __global__ __launch_bounds__(256) void kv_read_block_fp8_kernel(const uint8_t *_
         }
     }
     __syncthreads();
-    for (int e = tid; e < n_pos * 16; e += 256)
+    for (int e = tid; e < n_pos * 16; e += 1024)
         *(uint4 *)(v + user + (size_t)e * 8) = *(const uint4 *)(tile + (e >> 4) * kVtRow + (e & 15) * 8);
 }
 
@@ -1042,7 +1045,7 @@ hipError_t launch_kv_copy_fp8(void *cache_k, void *cache_v, const void *k, const
     if (n == 0) return hipSuccess;
     if (!to_cache && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
         const dim3 blocks((unsigned)((len + 63) / 64), (unsigned)Hkv, 2);
-        kv_read_block_fp8_kernel<<<blocks, 256, 0, s>>>((const uint8_t *)cache_k, (const uint8_t *)cache_v, (uint16_t *)k, (uint16_t *)v,
+        kv_read_block_fp8_kernel<<<blocks, 1024, 0, s>>>((const uint8_t *)cache_k, (const uint8_t *)cache_v, (uint16_t *)k, (uint16_t *)v,
                                                         slot, Hkv, len, max_len_pad, k_scale, v_scale);
         return hipGetLastError();
     }
