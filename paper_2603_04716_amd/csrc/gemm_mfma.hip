@@ -599,22 +599,59 @@ static int choose_splits(const GemmArgs &a, int BM, int BN)
     return splits < 1 ? 1 : splits;
 }
 
-// Split count for chunk-sized problems (a few hundred to a few thousand rows): these are bound by
-// the matrix pipe, but 256 x 256 tiles alone leave most CUs idle, so K is split until about one
-// workgroup per CU exists (at least 8 k-tiles per split; the fp32 partials must fit the scratch).
-static int choose_splits_mid(const GemmArgs &a)
+// Tile and K split of a dense product of more than 256 rows, for both operand widths (a k-tile is 64 x 2
+// bytes wide in either, and takes the same time).  256 x 256 tiles are the fastest per flop, but a launch runs in
+// rounds of one workgroup per CU: a few hundred to a few thousand rows fill the last round badly, and so do 257 rows
+// that take two row tiles.  Each form's time is therefore estimated as
+//   rounds x k-tiles per split x time of a k-tile + 5 us + (split: the launch that adds the partials)
+// with the times of a k-tile measured on the projections of the 8B shape at 300 ... 8192 rows (us):
+//   256 x 256 1.80 (1.70 where one round does), 192 x 256 1.45, 128 x 128 with two workgroups per CU 1.06 for the
+//   pair (a last round of at most one per CU 0.5 ... 0.8 of that, the fuller the slower), 128 x 128 with eight waves,
+//   alone on its CU with a four-stage ring, 0.66
+// and a split costing 5 us plus its partials written and read at 8 TB/s.  Measured against 256 x 256 tiles with
+// their best split, us: bf16 QKV 771 rows 68 -> 59 (192), O 512 rows 39 -> 33 (128, 8 waves), gate/up 300 rows
+// 110 -> 88 (192), down 5107 rows 737 -> 641 (192); 8-bit QKV 512 rows 40 -> 23, O 1024 rows 46 -> 27 (128, 8 waves),
+// gate/up 300 rows 60 -> 46 (192).
+enum TileForm { TILE_256, TILE_192, TILE_128_PAIR, TILE_128_DEEP };
+struct TilePlan {
+    TileForm form;
+    int splits;
+};
+
+static TilePlan plan_tiles(const GemmArgs &a)
 {
-    if (!a.splitk_ws || a.group_offsets || a.a_gather || a.N % 4 != 0 || a.ldc % 4 != 0 ||
-        (a.epilogue == EPI_RESIDUAL && a.ldr % 4 != 0))
-        return 1;
     const int n_cols = a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N;
-    const int tiles = ((a.M + 255) / 256) * ((n_cols + 255) / 256);
-    if (tiles >= 192) return 1;
-    int splits = (256 + tiles / 2) / tiles;
     const int nk = a.K / BK;
-    if (splits > nk / 8) splits = nk / 8;
-    while (splits > 1 && (size_t)splits * a.M * n_cols > a.splitk_ws_elems) --splits;
-    return splits < 1 ? 1 : splits;
+    const bool can_split = a.splitk_ws && a.N % 4 == 0 && a.ldc % 4 == 0 && (a.epilogue != EPI_RESIDUAL || a.ldr % 4 == 0);
+    TilePlan best = {TILE_256, 1};
+    double best_us = 1e30;
+    const struct {
+        TileForm form;
+        int bm, bn;
+        double kt_us;
+    } forms[] = {{TILE_256, 256, 256, 1.80}, {TILE_192, 192, 256, 1.45}, {TILE_128_PAIR, 128, 128, 1.06}, {TILE_128_DEEP, 128, 128, 0.66}};
+    for (const auto &f : forms) {
+        const long long tiles = (long long)((a.M + f.bm - 1) / f.bm) * ((n_cols + f.bn - 1) / f.bn);
+        for (int sp = 1; sp <= 8; ++sp) {
+            if (sp > 1 && (!can_split || nk / sp < 6 || (size_t)sp * a.M * n_cols > a.splitk_ws_elems)) break;
+            const long long wg = tiles * sp;
+            double rounds = (double)((wg + 255) / 256);
+            double kt_us = f.kt_us;
+            if (f.form == TILE_256 && wg <= 256) kt_us = 1.70;
+            if (f.form == TILE_128_PAIR) {
+                const long long rem = wg % 512;
+                rounds = (double)(wg / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 0.5 + 0.3 * (double)rem / 256.0 : 1.0);
+            }
+            double us = rounds * ((nk + sp - 1) / sp) * kt_us + 5.0;
+            if (sp > 1) us += 5.0 + (double)sp * a.M * n_cols * 8.0 / 8e6;
+            else if (a.fuse_y) us += 4.0;              // the norm that a split's sum carries costs a launch of its own
+            if (us < best_us) {
+                best_us = us;
+                best = {f.form, sp};
+            }
+        }
+    }
+    return best;
 }
 
 // 8-bit operands (see the kernel): a.A are E4M3 codes [M, 2 K] with a.a_scale per row, a.B the codes in
@@ -624,18 +661,27 @@ bool gemm_mfma_f8_supported(const GemmArgs &a)
     return gemm_mfma_supported(a) && a.a_scale && a.b_scale;
 }
 
+template <bool F8>
+static hipError_t launch_planned(const GemmArgs &a, hipStream_t s)
+{
+    const TilePlan p = plan_tiles(a);
+    switch (p.form) {
+    case TILE_192: return launch_cfg<192, 256, 2, 4, 2, F8>(a, s, p.splits);
+    case TILE_128_PAIR: return launch_cfg<128, 128, 2, 2, 2, F8>(a, s, p.splits);
+    case TILE_128_DEEP: return launch_cfg<128, 128, 4, 2, 4, F8>(a, s, p.splits);
+    default: break;
+    }
+    // 8 waves (two per SIMD hide each other's stalls) or 16: at 8192 rows, us, 8 -> 16 waves: 8-bit gate/up 854 -> 834,
+    // down 398 -> 374, O 138 -> 129, QKV 180 -> 175; bf16 O 254 -> 246, but QKV 348 -> 372, gate/up 1689 -> 1694,
+    // down 851 -> 862
+    if (F8 || (a.epilogue == EPI_RESIDUAL && a.K <= 4096)) return launch_cfg<256, 256, 4, 4, 2, F8>(a, s, p.splits);
+    return launch_cfg<256, 256, 2, 4, 2, F8>(a, s, p.splits);
+}
+
 hipError_t launch_gemm_mfma_f8(const GemmArgs &a, hipStream_t s)
 {
-    // a decode batch of a few hundred rows is bound by the weight stream, not by the matrix pipe: for the
-    // products with few columns narrow column tiles and K split over workgroups, as for bf16 (measured
-    // at 448 rows: QKV 44 -> 26 us, O 46 -> 34, down 68 -> 57; the wide gate / up product is faster on
-    // the large tiles, 65 against 74 us)
-    if (a.M <= 512 && !a.group_offsets && (a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N) < 16384)
-        return launch_cfg<256, 64, 8, 1, 3, true>(a, s, choose_splits(a, 256, 64));
-    // as for bf16: 16 waves for the short-K products (a.K counts code pairs)
-    if (a.K <= 2048 && a.epilogue != EPI_SWIGLU && !a.group_offsets)
-        return launch_cfg<256, 256, 4, 4, 2, true>(a, s, choose_splits_mid(a));
-    return launch_cfg<256, 256, 2, 4, 2, true>(a, s, choose_splits_mid(a));
+    if (a.group_offsets || a.a_gather) return launch_cfg<256, 256, 2, 4, 2, true>(a, s);
+    return launch_planned<true>(a, s);
 }
 
 hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s)
@@ -644,11 +690,8 @@ hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s)
     // (larger groups take several row tiles)
     const int rows = a.group_offsets ? (a.M + a.n_groups - 1) / a.n_groups : a.M;
     if (rows > 256) {
-        // 8 waves (two per SIMD hide each other's stalls); short-K problems spend relatively more time in
-        // the prologue / epilogue, where 16 waves measured 5-8 % faster
-        const int splits = choose_splits_mid(a);
-        if (a.K <= 4096 && a.epilogue != EPI_SWIGLU && !a.group_offsets) return launch_cfg<256, 256, 4, 4, 2>(a, s, splits);
-        return launch_cfg<256, 256, 2, 4, 2>(a, s, splits);
+        if (a.group_offsets || a.a_gather) return launch_cfg<256, 256, 2, 4, 2>(a, s);
+        return launch_planned<false>(a, s);
     }
     const int n_cols = a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N;
     const bool wide = n_cols >= 16384;                            // enough column tiles without splitting K

@@ -1,0 +1,59 @@
+"""Products of more than 256 rows: the sizes here take each tile form (256, 192, 128 in pairs, 128 deep) and
+each with and without a K split, with ragged last row and column tiles, one row over a tile, and all epilogues."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_04716_amd as pd
+import pd_inputs as I
+from oracle import layer as O
+from gpu_util import GpuLayer, TOL, relmax, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K", [(257, 1040, 1536), (300, 28672, 256), (771, 6144, 256), (513, 528, 2048), (512, 28672, 256),
+                                   (1000, 4096, 1536), (770, 4112, 3072), (385, 272, 14336)])
+def test_codes_product(M, N, K):
+    """Bound: one rounding to bf16 and the order of the fp32 sums, 2^-8 of the row's largest output."""
+    rng = np.random.default_rng(M + N)
+    a, b = (rng.integers(0, 256, s, dtype=np.uint8) & 0xB7 for s in ((M, K), (N, K)))
+    sa = (2.0 ** rng.integers(-6, 2, M)).astype(np.float32)
+    sb = (2.0 ** rng.integers(-6, 2, N)).astype(np.float32)
+    out = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    pd.pd_gemm_e4m3(torch.from_numpy(a).cuda(), torch.from_numpy(sa).cuda(), torch.from_numpy(b).cuda(),
+                    torch.from_numpy(sb).cuda(), out)
+    got = out.float().cpu().numpy()
+    rows = np.unique(np.r_[0, M - 1, M // 2, 255, 256, rng.choice(M, 12)])
+    ref = O.gemm_e4m3(a[rows], sa[rows], b, sb)
+    assert max(relmax(got[r], ref[j]) for j, r in enumerate(rows)) <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("T,d,V", [(257, 1536, 1040), (771, 256, 6144), (513, 2048, 528), (300, 256, 28672), (700, 256, 12304)])
+def test_bf16_product(T, d, V):
+    hw = I.head_weights(d, V, seed=d + V, dtype="bf16", std=0.05)
+    dev = {k: to_dev(v, "bf16") for k, v in hw.items()}
+    h = pd.pd_head_create(d, V, 1e-6, "bf16", dev["g_final"], dev["w_lm"], None, T)
+    x = I.hidden(T, d, seed=T, dtype="bf16")
+    logits = torch.empty((T, V), dtype=torch.bfloat16, device="cuda")
+    pd.pd_lm_head(h, to_dev(x, "bf16"), logits)
+    torch.cuda.synchronize()
+    rows = np.unique(np.r_[0, T - 1, T // 2, 255, 256])
+    ref = O.lm_head(x[rows], hw["g_final"], hw["w_lm"])
+    got = to_np(logits)[rows]
+    assert max(relmax(got[j], ref[j]) for j in range(len(rows))) <= TOL["bf16"]
+    pd.pd_head_destroy(h)
+
+
+@pytest.mark.parametrize("a8", [False, True])
+@pytest.mark.parametrize("rows", [257, 300, 385, 513])
+def test_layer_epilogues(a8, rows):
+    """A wide FFN (28672 gate / up columns) beside narrow products: SwiGLU and residual epilogues of the forms; the
+    bound with 8-bit activations is the one derived for the layer (6e-2)."""
+    cfg = I.small_config(dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=14336)
+    w = I.layer_weights(cfg, std=0.05)
+    ol, gl = O.Layer(cfg, O.quantise_layer_weights(w) if a8 else w), GpuLayer(cfg, w, a8=a8)
+    x = I.hidden(rows, cfg["d_model"], seed=rows, dtype="bf16")
+    cu = np.array([0, rows // 3, rows], np.int32)
+    assert relmax(gl.prefill(x, cu), O.prefill(ol, x, cu, act8=a8)) <= (6e-2 if a8 else TOL["bf16"])
+    gl.close()
