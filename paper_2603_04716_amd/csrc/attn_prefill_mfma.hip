@@ -15,7 +15,7 @@
 // turns that into the 8 consecutive keys the B operand wants.
 //
 // K tiles are read from the projection buffer and V^T tiles from a transposed copy of V made by
-// v_transpose_kernel (sequence starts padded to 64 so every tile row is 16-byte aligned and
+// rope_tile_kernel (sequence starts padded to 64 so every tile row is 16-byte aligned and
 // zero-filled past the sequence end).  Both arrive with direct-to-LDS loads, XOR-swizzled on
 // the global side like the GEMM, double buffered, one barrier per tile.
 #include "pd_internal.h"
@@ -37,49 +37,6 @@ constexpr float kLazy = 8.0f;
 // s_waitcnt with only the vector-memory count set: at most n of the wave's loads still in flight
 #define PD_ATT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
 constexpr int kAttnSplitGrid = 512;   // four-wave workgroups a split launch aims for: two per CU
-
-// ---------------------------------------------------------------------------------------------
-// vt[g][d][pad_cu[s] + p] = V[token cu[s] + p][g][d]; zero for padded positions p >= L_s.
-// Block = 64 padded positions of one kv head.
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void v_transpose_kernel(const uint16_t *__restrict__ qkv, int ld,
-                                                          int v_col0, const int32_t *__restrict__ cu,
-                                                          const int32_t *__restrict__ pad_cu,
-                                                          int n_seqs, uint16_t *__restrict__ vt,
-                                                          int vt_ld)
-{
-    __shared__ uint16_t tile[64][HD + 2];
-    const int p0 = blockIdx.x * 64, g = blockIdx.y;
-    int lo = 0, hi = n_seqs;   // largest s with pad_cu[s] <= p0
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (pad_cu[mid] <= p0) lo = mid; else hi = mid;
-    }
-    const int s = lo;
-    const int L = cu[s + 1] - cu[s];
-    const int pos0 = p0 - pad_cu[s];
-    for (int idx = threadIdx.x; idx < 64 * (HD / 8); idx += 256) {
-        int r = idx / (HD / 8), c = idx % (HD / 8);
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (pos0 + r < L)
-            v = *(const uint4 *)(qkv + (size_t)(cu[s] + pos0 + r) * ld + v_col0 + g * HD + c * 8);
-        uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            tile[r][c * 8 + 2 * j] = (uint16_t)(w[j] & 0xffffu);
-            tile[r][c * 8 + 2 * j + 1] = (uint16_t)(w[j] >> 16);
-        }
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < HD * 8; idx += 256) {
-        int d = idx >> 3, c = idx & 7;   // 8 positions per 16-byte chunk
-        uint32_t w[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            w[j] = (uint32_t)tile[c * 8 + 2 * j][d] | ((uint32_t)tile[c * 8 + 2 * j + 1][d] << 16);
-        *(uint4 *)(vt + ((size_t)g * HD + d) * vt_ld + p0 + c * 8) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-}
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -485,7 +442,7 @@ __global__ __launch_bounds__(256) void kv_gather_blocked_fp8_kernel(
 
 bool attn_prefill_mfma_supported(const AttnArgs &a)
 {
-    return a.hd == HD && !a.decode && a.ld % 8 == 0 && a.T > 0 &&
+    return a.hd == HD && !a.decode && a.ld % 8 == 0 && a.T > 0 && a.Hkv <= kRopeTileMaxHkv &&
            (int64_t)a.T * a.ld * 2 < (1ll << 31);
 }
 
@@ -524,14 +481,9 @@ static hipError_t launch_attn_kernel(const AttnArgs &a, const uint16_t *vt, int 
 }
 
 // vt: transposed-V scratch [Hkv][128][vt_ld]; pad_cu: device [n_seqs+1] padded sequence starts.
-hipError_t launch_attn_prefill_mfma(const AttnArgs &a, uint16_t *vt, int vt_ld, const int32_t *pad_cu,
+hipError_t launch_attn_prefill_mfma(const AttnArgs &a, const uint16_t *vt, int vt_ld, const int32_t *pad_cu,
                                     hipStream_t s)
 {
-    v_transpose_kernel<<<dim3(vt_ld / 64, a.Hkv), 256, 0, s>>>((const uint16_t *)a.qkv, a.ld,
-                                                               (a.Hq + a.Hkv) * HD, a.d_cu, pad_cu,
-                                                               a.n_seqs, vt, vt_ld);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     return launch_attn_kernel<false>(a, vt, vt_ld, pad_cu, 1, nullptr, nullptr, s);
 }
 

@@ -995,6 +995,43 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
     for (int q = 0; q < n; ++q)
         pad[(size_t)q + 1] = pad[(size_t)q] +
                              (prefix[(size_t)q] + tk->cu_seqlens[q + 1] - tk->cu_seqlens[q] + 63) / 64 * 64;
+    // Attention path, and the scratch of the matrix-core ones (transposed values, gathered keys, partial results of
+    // a split) before anything is enqueued
+    AttnArgs a;
+    memset(&a, 0, sizeof(a));
+    a.qkv = L->qkv; a.ld = L->Nqkv; a.o = L->o; a.T = T; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads;
+    a.hd = c.head_dim; a.scale = (float)(1.0 / sqrt((double)c.head_dim)); a.tok_pos = L->tok_pos;
+    a.decode = 0; a.d_cu = L->d_cu; a.n_seqs = n; a.max_seq_len = max_L;
+    const bool short_chunk = chunk && cache->blocked && max_L <= kShortChunk;
+    const bool tile_attn = chunk ? cache->blocked && !short_chunk : L->use_mfma && attn_prefill_mfma_supported(a);
+    const int vt_ld = pad[(size_t)n];
+    const size_t vt_bytes = (size_t)c.n_kv_heads * c.head_dim * vt_ld * 2;
+    int n_split = 1;
+    if (tile_attn) {
+        if (chunk && !attn_prefill_mfma_supported(a)) {
+            set_error("pd_prefill_chunk: blocked cache without the matrix-core attention path");
+            return PD_ERR_SHAPE;
+        }
+        int max_keys = 0;
+        if (chunk) {
+            for (int q = 0; q < n; ++q)
+                max_keys = std::max(max_keys, prefix[(size_t)q] + tk->cu_seqlens[q + 1] - tk->cu_seqlens[q]);
+            n_split = attn_chunk_splits(a, max_keys);
+        }
+        const size_t need = chunk ? 2 * vt_bytes + attn_chunk_split_bytes(a, n_split) : vt_bytes;
+        if (need > L->vt_cap) {
+            HIP_TRY(hipDeviceSynchronize(), PD_ERR_DEVICE);
+            if (L->vt) (void)hipFree(L->vt);
+            L->vt = nullptr;
+            L->vt_cap = 0;
+            hipError_t e = hipMalloc(&L->vt, need);
+            if (e != hipSuccess) {
+                set_error("pd_prefill: cannot allocate %zu bytes of attention scratch", need);
+                return PD_ERR_OOM;
+            }
+            L->vt_cap = need;
+        }
+    }
     {
         int32_t *const dst[4] = {L->d_cu, L->d_pad_cu, L->d_slots, L->d_prefix};
         const int32_t *const src[4] = {tk->cu_seqlens, pad.data(), tk->slots, prefix.data()};
@@ -1014,18 +1051,20 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
     r.max_len = keep ? cache->plane_len : 0; r.blocked = keep ? cache->blocked : 0; r.inv_freq = L->inv_freq;
     r.fp8 = keep ? cache->fp8 : 0; r.k_scale = keep ? cache->k_scale : 1.0; r.v_scale = keep ? cache->v_scale : 1.0;
     r.table = L->rope_table; r.table_len = kRopeTableLen;
-    STEP("rope_kv_write", launch_rope_kv(c.dtype, r, s));
-    AttnArgs a;
-    memset(&a, 0, sizeof(a));
-    a.qkv = L->qkv; a.ld = L->Nqkv; a.o = L->o; a.T = T; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads;
-    a.hd = c.head_dim; a.scale = (float)(1.0 / sqrt((double)c.head_dim)); a.tok_pos = L->tok_pos;
-    a.decode = 0; a.d_cu = L->d_cu; a.n_seqs = n; a.max_seq_len = max_L;
+    if (rope_tile_supported(c.dtype, r) && !short_chunk) {
+        RopeTiles rt;
+        rt.cu = L->d_cu; rt.prefix = chunk ? L->d_prefix : nullptr; rt.slots = L->d_slots; rt.pad_cu = L->d_pad_cu;
+        rt.n_seqs = n; rt.max_len = max_L; rt.vt = tile_attn && !chunk ? (uint16_t *)L->vt : nullptr; rt.vt_ld = vt_ld;
+        STEP("rope_kv_write", launch_rope_tile(r, rt, s));
+    } else {
+        STEP("rope_kv_write", launch_rope_kv(c.dtype, r, s));
+    }
     if (chunk && !cache->blocked) {
         // plain cache layout: every row reads keys 0 .. its own position of its slot
         a.decode = 1; a.tok_slot = L->tok_slot; a.k_cache = cache->k; a.v_cache = cache->v;
         a.max_len = cache->max_len;
         STEP("prefill_attention", launch_attn_generic(c.dtype, a, s));
-    } else if (chunk && max_L <= kShortChunk) {
+    } else if (short_chunk) {
         // A few new tokens per sequence over a blocked cache (multi-token decode): the decode
         // attention kernel streams the cache once per unit of a few tokens instead of gathering the
         // prefix for the prefill kernel.
@@ -1098,32 +1137,7 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
         da.part_o = part;
         da.part_ml = part + (size_t)total_chunks * c.n_kv_heads * 16 * 128;
         STEP("prefill_attention", launch_decode_attn_mfma(da, s));
-    } else if (chunk || (L->use_mfma && attn_prefill_mfma_supported(a))) {
-        if (chunk && !attn_prefill_mfma_supported(a)) {
-            set_error("pd_prefill_chunk: blocked cache without the matrix-core attention path");
-            return PD_ERR_SHAPE;
-        }
-        const int vt_ld = pad[(size_t)n];
-        const size_t vt_bytes = (size_t)c.n_kv_heads * c.head_dim * vt_ld * 2;
-        int n_split = 1, max_keys = 0;
-        if (chunk) {
-            for (int q = 0; q < n; ++q)
-                max_keys = std::max(max_keys, prefix[(size_t)q] + tk->cu_seqlens[q + 1] - tk->cu_seqlens[q]);
-            n_split = attn_chunk_splits(a, max_keys);
-        }
-        const size_t need = chunk ? 2 * vt_bytes + attn_chunk_split_bytes(a, n_split) : vt_bytes;
-        if (need > L->vt_cap) {
-            HIP_TRY(hipDeviceSynchronize(), PD_ERR_DEVICE);
-            if (L->vt) (void)hipFree(L->vt);
-            L->vt = nullptr;
-            L->vt_cap = 0;
-            hipError_t e = hipMalloc(&L->vt, need);
-            if (e != hipSuccess) {
-                set_error("pd_prefill: cannot allocate %zu bytes of attention scratch", need);
-                return PD_ERR_OOM;
-            }
-            L->vt_cap = need;
-        }
+    } else if (tile_attn) {
         if (chunk) {
             a.prefix = L->d_prefix; a.k_cache = cache->k; a.v_cache = cache->v; a.max_len = cache->plane_len;
             a.kv_fp8 = cache->fp8; a.k_scale = (float)cache->k_scale; a.v_scale = (float)cache->v_scale;

@@ -327,6 +327,18 @@ __device__ __forceinline__ void append_token_body(const RopeArgs &a, int t, floa
     }
 }
 
+// A prefill call's sequences for the tiled form: sequence s owns rows cu[s] .. cu[s + 1] - 1 of qkv, the first
+// at position prefix[s] (null: 0), and writes slot slots[s] where RopeArgs has a cache.  vt (optional, no prefix):
+// transposed values [Hkv][128][vt_ld] as launch_attn_prefill_mfma reads them, sequence starts at pad_cu.
+struct RopeTiles {
+    const int32_t *cu, *prefix, *slots, *pad_cu;
+    int32_t n_seqs, max_len;   // max_len: rows of the longest sequence
+    uint16_t *vt;
+    int32_t vt_ld;
+};
+constexpr int kRopeTileMaxHkv = 32767;   // two grid rows per kv head
+bool rope_tile_supported(int dtype, const RopeArgs &a);
+hipError_t launch_rope_tile(const RopeArgs &a, const RopeTiles &t, hipStream_t s);
 hipError_t launch_rope_table(float2 *table, int table_len, int half, const double *inv_freq, hipStream_t s);
 hipError_t launch_rope_kv(int dtype, const RopeArgs &a, hipStream_t s);
 // RMSNorm of n_rows bf16 rows (d a multiple of 8) and, in the same launch, the cache append of a decode
@@ -365,9 +377,10 @@ struct AttnArgs {
 };
 hipError_t launch_attn_generic(int dtype, const AttnArgs &a, hipStream_t s);
 bool attn_prefill_mfma_supported(const AttnArgs &a);
-// bf16, hd = 128.  vt: scratch for V transposed, [Hkv][128][vt_ld] with vt_ld = padded token count
-// (each sequence start rounded up to a multiple of 64); pad_cu: device [n_seqs+1] padded starts.
-hipError_t launch_attn_prefill_mfma(const AttnArgs &a, uint16_t *vt, int vt_ld, const int32_t *pad_cu,
+// bf16, hd = 128.  vt: V transposed (launch_rope_tile), [Hkv][128][vt_ld] with vt_ld = padded token count
+// (each sequence start rounded up to a multiple of 64), zero past each sequence's end; pad_cu: device
+// [n_seqs+1] padded starts.
+hipError_t launch_attn_prefill_mfma(const AttnArgs &a, const uint16_t *vt, int vt_ld, const int32_t *pad_cu,
                                     hipStream_t s);
 // Chunked prefill over a blocked cache: copies the keys (as plain rows kx[pad_cu[s] + pos][Hkv*128])
 // and the values (transposed, vt[g][d][pad_cu[s] + pos], zero past the end) of positions

@@ -1,0 +1,90 @@
+"""Tiled rotary embedding + cache write of a prefill: sequences that end on, before and behind a 64-position tile,
+chunks that start anywhere in one, every cache form (blocked, 8-bit with power-of-two and other scales, plain, none),
+positions past the rotary table.  Outputs, stored keys and values against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_04716_amd as pd
+import pd_inputs as I
+from oracle import layer as O
+from gpu_util import GpuLayer, TOL, relmax, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+CFG = I.small_config(dtype="bf16", d_model=128, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=128)
+PLAIN = I.small_config(dtype="bf16", d_model=128, n_q_heads=20, n_kv_heads=1, head_dim=128, d_ff=128)
+
+
+def _check_cache(gl, gc, oc, slots, scales):
+    for s in slots:
+        n = pd.pd_kv_cache_len(gc, s)
+        k = torch.empty((oc.k.shape[1], n, 128), dtype=torch.bfloat16, device="cuda")
+        v = torch.empty_like(k)
+        pd.pd_kv_cache_get(gc, s, k, v)
+        torch.cuda.synchronize()
+        for got, ref, scale in ((to_np(k), oc.k[s, :, :n], 0), (to_np(v), oc.v[s, :, :n], 1)):
+            slack = TOL["bf16"] * np.max(np.abs(ref))
+            if scales:                               # the neighbouring code: one spacing
+                mag = np.maximum(np.maximum(np.abs(ref), np.abs(got)) / scales[scale], 2.0 ** -6)
+                slack = slack + scales[scale] * 2.0 ** (np.floor(np.log2(mag)) - 3)
+            assert np.all(np.abs(got - ref) <= slack)
+
+
+@pytest.mark.parametrize("form", ["bf16", "fp8", "fp8_odd", "plain", "none"])
+@pytest.mark.parametrize("lens", [[1], [7, 64, 9], [63, 65], [200, 1, 130]])
+def test_prefill(form, lens):
+    cfg = PLAIN if form == "plain" else CFG
+    w = I.layer_weights(cfg, std=0.05)
+    ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
+    scales = {"fp8": (0.5, 0.125), "fp8_odd": (0.3, 0.07)}.get(form)
+    n = len(lens)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    slots = list(range(n))[::-1]
+    x = I.hidden(int(cu[-1]), cfg["d_model"], seed=5, dtype="bf16")
+    if form == "none":
+        assert relmax(gl.prefill(x, cu), O.prefill(ol, x, cu)) <= TOL["bf16"]
+    else:
+        oc, gc = O.KVCache(ol, n, 260, fp8_scales=scales), gl.cache(n, 260, fp8_scales=scales)
+        assert relmax(gl.prefill(x, cu, gc, slots), O.prefill(ol, x, cu, cache=oc, slots=slots)) <= TOL["bf16"]
+        _check_cache(gl, gc, oc, slots, scales)
+    gl.close()
+
+
+@pytest.mark.parametrize("form", ["bf16", "fp8", "plain"])
+@pytest.mark.parametrize("prefix,lens", [([0, 5], [20, 9]), ([63, 64], [66, 70]), ([100, 33], [9, 150])])
+def test_chunk(form, prefix, lens):
+    """What the slots hold behind a chunk's start stays as it was, except for the chunk's own positions."""
+    cfg = PLAIN if form == "plain" else CFG
+    w = I.layer_weights(cfg, std=0.05)
+    ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
+    scales = (0.5, 0.125) if form == "fp8" else None
+    cap = 300
+    oc, gc = O.KVCache(ol, 2, cap, fp8_scales=scales), gl.cache(2, cap, fp8_scales=scales)
+    for s in range(2):
+        k, v = I.kv_fill(cfg["n_kv_heads"], cap, 128, seed=s, dtype="bf16")
+        oc.set(s, k, v)
+        pd.pd_kv_cache_set(gc, s, to_dev(k, "bf16"), to_dev(v, "bf16"))
+        oc.lens[s] = prefix[s]
+        pd.pd_kv_cache_set_len(gc, s, prefix[s])
+    cu = np.array([0, lens[0], sum(lens)], np.int32)
+    x = I.hidden(int(cu[-1]), cfg["d_model"], seed=6, dtype="bf16")
+    assert relmax(gl.prefill_chunk(x, cu, [0, 1], gc), O.prefill_chunk(ol, x, cu, [0, 1], oc)) <= TOL["bf16"]
+    for s in range(2):
+        pd.pd_kv_cache_set_len(gc, s, cap)
+    _check_cache(gl, gc, oc, [0, 1], scales)
+    gl.close()
+
+
+def test_chunk_past_the_rotary_table():
+    ol, gl = (lambda w: (O.Layer(CFG, w), GpuLayer(CFG, w)))(I.layer_weights(CFG, std=0.05))
+    n, rows = 32760, 20                              # positions 32760 .. 32779; the table ends at 32767
+    oc, gc = O.KVCache(ol, 1, n + rows), gl.cache(1, n + rows)
+    k, v = I.kv_fill(2, n, 128, seed=9, dtype="bf16")
+    oc.set(0, k, v)
+    pd.pd_kv_cache_set(gc, 0, to_dev(k, "bf16"), to_dev(v, "bf16"))
+    x = I.hidden(rows, CFG["d_model"], seed=7, dtype="bf16")
+    cu = np.array([0, rows], np.int32)
+    assert relmax(gl.prefill_chunk(x, cu, [0], gc), O.prefill_chunk(ol, x, cu, [0], oc)) <= TOL["bf16"]
+    _check_cache(gl, gc, oc, [0], None)
+    gl.close()
