@@ -65,7 +65,16 @@ __global__ __launch_bounds__(64 * WAVES_M *WAVES_N) void gemm_mfma_kernel(GemmAr
     constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
 
     // ---- tile id: contiguous ranges of tiles per XCD, 8-row bands inside ------------------------
+    // A grouped launch has a row tile per group more than its rows may need.  Only the tiles in use are dealt: dealt
+    // with the empty ones, these fall together on the last XCDs, and the others do their share.  Before -> now, us
+    // (8 experts of the 8B shape): 128 rows gate/up 372 -> 343 (5.5 TB/s), down 248 -> 163 (5.8 TB/s); 11990 rows
+    // gate/up 3209 -> 2947.
+    if (a.group_offsets) {
+        tiles_m = 0;
+        for (int g = 0; g < a.n_groups; ++g) tiles_m += (a.group_offsets[g + 1] - a.group_offsets[g] + BM - 1) / BM;
+    }
     const int n_tiles = tiles_m * tiles_n;
+    if ((int)blockIdx.x >= n_tiles) return;
     int pid = blockIdx.x;
     {
         const int per = n_tiles / 8, rem = n_tiles % 8;

@@ -1,0 +1,34 @@
+"""Mixture-of-experts products on the tiled kernel: a grouped launch holds a row tile per group more than its rows
+may need, and the tiles in use are dealt over the chip whatever the loads of the experts are."""
+import numpy as np
+import pytest
+
+import pd_inputs as I
+from oracle import layer as O
+from gpu_util import GpuLayer, TOL, relmax
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,d_ff", [(12, 1024), (64, 2048), (700, 1024), (2500, 512)])
+@pytest.mark.parametrize("skew", ["even", "two", "ragged"])
+def test_grouped_products_deal_the_tiles_in_use(T, d_ff, skew):
+    """Expert loads from even to two experts with all rows: the tiles in use are from all to few of those launched."""
+    cfg = I.small_config(dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=d_ff, n_experts=8, top_k=2)
+    w = I.layer_weights(cfg, std=0.05)
+    ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
+    r = I.router_logits(T, 8, seed=T)
+    if skew == "two":
+        r[:, 1] += 9.0
+        r[:, 6] += 8.0
+    if skew == "ragged":
+        r += np.linspace(0.0, 3.0, 8, dtype=r.dtype)
+    n = T // 4
+    cu = np.array([0, n, 2 * n, 3 * n, T], np.int32)
+    x = I.hidden(T, cfg["d_model"], seed=8, dtype="bf16")
+    ref, eref = O.prefill(ol, x, cu, router_logits=r, return_experts=True)
+    got = gl.prefill(x, cu, router_logits=r)
+    assert np.array_equal(gl.experts(T), eref)
+    assert relmax(got, ref) <= TOL["bf16"]
+    assert max(relmax(got[i], ref[i]) for i in range(T)) <= 2 * TOL["bf16"]
+    gl.close()
