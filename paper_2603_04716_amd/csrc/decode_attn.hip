@@ -28,10 +28,10 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float dexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // One block: pos / len update and the prefix sum of chunks per sequence (B <= 4096).  BYVAL: the
-// slots arrive in the kernel arguments (B <= 256) and are also stored to slots_out for the kernels
+// slots arrive in the kernel arguments and are also stored to slots_out for the kernels
 // that follow, which saves the separate upload launch of a small decode step.
-template <bool BYVAL>
-__device__ __forceinline__ void decode_meta_chunks_body(const int32_t *__restrict__ slots, const IntChunk &sv,
+template <bool BYVAL, typename CHUNK>
+__device__ __forceinline__ void decode_meta_chunks_body(const int32_t *__restrict__ slots, const CHUNK &sv,
                                                         int32_t *slots_out, int B, int32_t *len, int32_t *pos,
                                                         int32_t *chunk_cu, int32_t *chunk_seq, int chunk_keys,
                                                         int *wave_tot)
@@ -79,8 +79,8 @@ __device__ __forceinline__ void decode_meta_chunks_body(const int32_t *__restric
     }
 }
 
-template <bool BYVAL>
-__global__ __launch_bounds__(1024) void decode_meta_chunks_kernel(const int32_t *__restrict__ slots, IntChunk sv,
+template <bool BYVAL, typename CHUNK>
+__global__ __launch_bounds__(1024) void decode_meta_chunks_kernel(const int32_t *__restrict__ slots, CHUNK sv,
                                                                   int32_t *slots_out, int B, int32_t *len,
                                                                   int32_t *pos, int32_t *chunk_cu, int32_t *chunk_seq,
                                                                   int chunk_keys)
@@ -124,7 +124,7 @@ hipError_t launch_decode_meta_chunks(const int32_t *d_slots, int B, int32_t *d_l
 {
     IntChunk none;
     none.v[0] = 0;
-    decode_meta_chunks_kernel<false><<<1, 1024, 0, s>>>(d_slots, none, nullptr, B, d_len, d_pos, chunk_cu, chunk_seq, chunk_keys);
+    decode_meta_chunks_kernel<false, IntChunk><<<1, 1024, 0, s>>>(d_slots, none, nullptr, B, d_len, d_pos, chunk_cu, chunk_seq, chunk_keys);
     return hipGetLastError();
 }
 
@@ -132,10 +132,16 @@ hipError_t launch_decode_meta_chunks_upload(const int32_t *host_slots, int32_t *
                                             int32_t *d_pos, int32_t *chunk_cu, int32_t *chunk_seq, int chunk_keys,
                                             hipStream_t s)
 {
-    if (B > 256) return hipErrorInvalidValue;
-    IntChunk sv;
-    for (int i = 0; i < B; ++i) sv.v[i] = host_slots[i];
-    decode_meta_chunks_kernel<true><<<1, 256, 0, s>>>(nullptr, sv, d_slots, B, d_len, d_pos, chunk_cu, chunk_seq, chunk_keys);
+    if (B < 1 || B > kMetaUploadRows) return hipErrorInvalidValue;
+    if (B <= 256) {
+        IntChunk sv;
+        for (int i = 0; i < B; ++i) sv.v[i] = host_slots[i];
+        decode_meta_chunks_kernel<true, IntChunk><<<1, 256, 0, s>>>(nullptr, sv, d_slots, B, d_len, d_pos, chunk_cu, chunk_seq, chunk_keys);
+    } else {
+        IntChunkLong sv;
+        memcpy(sv.v, host_slots, (size_t)B * sizeof(int32_t));
+        decode_meta_chunks_kernel<true, IntChunkLong><<<1, 256, 0, s>>>(nullptr, sv, d_slots, B, d_len, d_pos, chunk_cu, chunk_seq, chunk_keys);
+    }
     return hipGetLastError();
 }
 
@@ -404,8 +410,9 @@ __global__ __launch_bounds__(256, 2) void decode_attn_kernel(DecodeAttnArgs a, i
                     const float x0 = bfbits2f((klo[wi] >> sh) & 0xffffu), x1 = bfbits2f((khi[wi] >> sh) & 0xffffu);
                     float y0 = x0 * c[e] - x1 * sn[e], y1 = x1 * c[e] + x0 * sn[e];
                     if (FP8) {
-                        y0 = e4m3_decode(e4m3_encode((double)y0 / a.k_scale_d));
-                        y1 = e4m3_decode(e4m3_encode((double)y1 / a.k_scale_d));
+                        const auto r = __builtin_amdgcn_cvt_pk_f32_fp8((int)e4m3_encode2(y0, y1, a.k_scale_d, a.k_inv), false);
+                        y0 = r[0];
+                        y1 = r[1];
                     } else {
                         y0 = bf2f(f2bf(y0));
                         y1 = bf2f(f2bf(y1));
@@ -425,11 +432,15 @@ __global__ __launch_bounds__(256, 2) void decode_attn_kernel(DecodeAttnArgs a, i
         for (int db = 0; db < 8; ++db) {
             const uint2 vv = *(const uint2 *)(vr + 16 * db + 4 * kg);     // channels 16 db + 4 kg + j
             float v[4] = {bfbits2f(vv.x & 0xffffu), bfbits2f(vv.x >> 16), bfbits2f(vv.y & 0xffffu), bfbits2f(vv.y >> 16)};
+            if (FP8)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (FP8) v[j] = e4m3_decode(e4m3_encode((double)v[j] / a.v_scale_d));
-                oacc[db][j] = oacc[db][j] * alpha + pnew * v[j];
-            }
+                for (int j = 0; j < 4; j += 2) {
+                    const auto r = __builtin_amdgcn_cvt_pk_f32_fp8((int)e4m3_encode2(v[j], v[j + 1], a.v_scale_d, a.v_inv), false);
+                    v[j] = r[0];
+                    v[j + 1] = r[1];
+                }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) oacc[db][j] = oacc[db][j] * alpha + pnew * v[j];
         }
     }
     float l_tot = l_run + __shfl_xor(l_run, 16, 64);

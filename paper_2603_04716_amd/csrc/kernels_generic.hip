@@ -204,7 +204,8 @@ hipError_t launch_gemm_generic(int dtype, const GemmArgs &a, hipStream_t s)
 // ---------------------------------------------------------------------------------------------
 // Metadata kernels.
 // ---------------------------------------------------------------------------------------------
-__global__ void write_ints_kernel(int32_t *dst, IntChunk c, int n)
+template <typename CHUNK>
+__global__ __launch_bounds__(1024) void write_ints_kernel(int32_t *dst, CHUNK c, int n)
 {
     int i = threadIdx.x;
     if (i < n) dst[i] = c.v[i];
@@ -212,11 +213,17 @@ __global__ void write_ints_kernel(int32_t *dst, IntChunk c, int n)
 
 hipError_t launch_write_ints(int32_t *dst, const int32_t *host_src, int n, hipStream_t s)
 {
-    for (int off = 0; off < n; off += 256) {
-        IntChunk c;
-        int m = n - off < 256 ? n - off : 256;
-        for (int i = 0; i < m; ++i) c.v[i] = host_src[off + i];
-        write_ints_kernel<<<1, 256, 0, s>>>(dst + off, c, m);
+    for (int off = 0; off < n; off += 960) {
+        const int m = n - off < 960 ? n - off : 960;
+        if (m <= 256) {
+            IntChunk c;
+            memcpy(c.v, host_src + off, (size_t)m * sizeof(int32_t));
+            write_ints_kernel<<<1, 256, 0, s>>>(dst + off, c, m);
+        } else {
+            IntChunkLong c;
+            memcpy(c.v, host_src + off, (size_t)m * sizeof(int32_t));
+            write_ints_kernel<<<1, 960, 0, s>>>(dst + off, c, m);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -259,23 +266,32 @@ hipError_t launch_write_ints4(int32_t *const dst[4], const int32_t *const host_s
     return hipGetLastError();
 }
 
-__global__ void scatter_ints_kernel(int32_t *dst, IntChunk c, int n)
+// c: up to half its length of indices, and as many values in its second half
+template <typename CHUNK>
+__global__ __launch_bounds__(512) void scatter_ints_kernel(int32_t *dst, CHUNK c, int n)
 {
+    constexpr int kHalf = sizeof(c.v) / sizeof(c.v[0]) / 2;
     int i = threadIdx.x;
-    if (i < n) dst[c.v[i]] = c.v[128 + i];
+    if (i < n) dst[c.v[i]] = c.v[kHalf + i];
 }
 
 hipError_t launch_scatter_ints(int32_t *dst, const int32_t *host_idx, const int32_t *host_val, int n,
                                hipStream_t s)
 {
-    for (int off = 0; off < n; off += 128) {
-        IntChunk c;
-        int m = n - off < 128 ? n - off : 128;
-        for (int i = 0; i < m; ++i) {
-            c.v[i] = host_idx[off + i];
-            c.v[128 + i] = host_val[off + i];
+    for (int off = 0; off < n; off += 480) {
+        const int m = n - off < 480 ? n - off : 480;
+        const size_t bytes = (size_t)m * sizeof(int32_t);
+        if (m <= 128) {
+            IntChunk c;
+            memcpy(c.v, host_idx + off, bytes);
+            memcpy(c.v + 128, host_val + off, bytes);
+            scatter_ints_kernel<<<1, 128, 0, s>>>(dst, c, m);
+        } else {
+            IntChunkLong c;
+            memcpy(c.v, host_idx + off, bytes);
+            memcpy(c.v + 480, host_val + off, bytes);
+            scatter_ints_kernel<<<1, 512, 0, s>>>(dst, c, m);
         }
-        scatter_ints_kernel<<<1, 128, 0, s>>>(dst, c, m);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -439,8 +455,9 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(RopeArgs a)
             T *plane = (T *)a.k_cache + ((size_t)slot * a.Hkv + g) * a.max_len * a.hd;
             if (a.fp8) {
                 uint8_t *p8 = (uint8_t *)a.k_cache + ((size_t)slot * a.Hkv + g) * a.max_len * a.hd;
-                p8[kblk8_off(pos, i)] = (uint8_t)e4m3_encode((double)y0 / a.k_scale);
-                p8[kblk8_off(pos, i + half)] = (uint8_t)e4m3_encode((double)y1 / a.k_scale);
+                const uint32_t code = e4m3_encode2(y0, y1, a.k_scale, a.k_inv);
+                p8[kblk8_off(pos, i)] = (uint8_t)code;
+                p8[kblk8_off(pos, i + half)] = (uint8_t)(code >> 8);
             } else if (a.blocked) {
                 Elem<T>::st(plane + kblk_off(pos, i), y0);
                 Elem<T>::st(plane + kblk_off(pos, i + half), y1);
@@ -457,7 +474,7 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(RopeArgs a)
             T *plane = (T *)a.v_cache + ((size_t)slot * a.Hkv + g) * a.max_len * a.hd;
             if (a.fp8)
                 ((uint8_t *)a.v_cache)[((size_t)slot * a.Hkv + g) * a.max_len * a.hd + vblk8_off(pos, i)] =
-                    (uint8_t)e4m3_encode((double)Elem<T>::ld(vsrc + idx) / a.v_scale);
+                    (uint8_t)e4m3_encode2(Elem<T>::ld(vsrc + idx), 0.f, a.v_scale, a.v_inv);
             else if (a.blocked) plane[vblk_off(pos, i)] = vsrc[idx];
             else plane[(size_t)pos * a.hd + i] = vsrc[idx];
         }

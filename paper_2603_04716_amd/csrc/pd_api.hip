@@ -1050,6 +1050,7 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
     r.k_cache = keep ? cache->k : nullptr; r.v_cache = keep ? cache->v : nullptr;
     r.max_len = keep ? cache->plane_len : 0; r.blocked = keep ? cache->blocked : 0; r.inv_freq = L->inv_freq;
     r.fp8 = keep ? cache->fp8 : 0; r.k_scale = keep ? cache->k_scale : 1.0; r.v_scale = keep ? cache->v_scale : 1.0;
+    r.k_inv = e4m3_inverse(r.k_scale); r.v_inv = e4m3_inverse(r.v_scale);
     r.table = L->rope_table; r.table_len = kRopeTableLen;
     if (rope_tile_supported(c.dtype, r) && !short_chunk) {
         RopeTiles rt;
@@ -1313,7 +1314,7 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
         STEP("rmsnorm_attn", launch_decode_meta_norm(bt->slots, L->d_slots, B, cache->d_len, L->tok_pos, L->chunk_cu,
                                                      L->chunk_seq, chunk_keys, bt->hidden, L->g_attn, L->y, c.d_model,
                                                      c.rms_eps, s));
-    } else if (mfma_dec && B <= 256) {
+    } else if (mfma_dec && B <= kMetaUploadRows) {
         HIP_TRY(launch_decode_meta_chunks_upload(bt->slots, L->d_slots, B, cache->d_len, L->tok_pos, L->chunk_cu,
                                                  L->chunk_seq, chunk_keys, s),
                 PD_ERR_DEVICE);
@@ -1338,6 +1339,7 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
     r.tok_pos = L->tok_pos; r.tok_slot = L->d_slots; r.k_cache = cache->k; r.v_cache = cache->v;
     r.max_len = cache->plane_len; r.blocked = cache->blocked; r.inv_freq = L->inv_freq;
     r.fp8 = cache->fp8; r.k_scale = cache->k_scale; r.v_scale = cache->v_scale;
+    r.k_inv = e4m3_inverse(r.k_scale); r.v_inv = e4m3_inverse(r.v_scale);
     r.table = L->rope_table; r.table_len = kRopeTableLen;
     // Fused form (matrix-core attention over a blocked cache, no 8-bit activations in this call): the
     // attention kernel rotates q and the new key itself and takes the new token from registers; the
@@ -1350,7 +1352,7 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
         memset(&da, 0, sizeof(da));
         if (fused_rope) {
             da.rope_table = L->rope_table; da.rope_table_len = kRopeTableLen; da.inv_freq = L->inv_freq;
-            da.k_scale_d = cache->k_scale; da.v_scale_d = cache->v_scale;
+            da.k_scale_d = cache->k_scale; da.v_scale_d = cache->v_scale; da.k_inv = r.k_inv; da.v_inv = r.v_inv;
         }
         da.qkv = L->qkv; da.ld = L->Nqkv; da.o = L->o; da.B = B; da.Hq = c.n_q_heads; da.Hkv = c.n_kv_heads;
         da.scale = (float)(1.0 / sqrt((double)c.head_dim)); da.slots = L->d_slots; da.pos = L->tok_pos;

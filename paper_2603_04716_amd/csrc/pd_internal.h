@@ -4,6 +4,8 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <cmath>
+#include <cstring>
 
 #include "pd.h"
 
@@ -109,6 +111,29 @@ __device__ __forceinline__ float e4m3_decode(uint32_t code)
 {
     return __builtin_amdgcn_cvt_pk_f32_fp8((int)code, false)[0];
 }
+// 1 / scale where scale is a power of two well inside fp32's range: the fp32 product with it is then the quotient,
+// and the hardware conversion of the clamped product gives e4m3_encode's code.  0 for any other scale.
+inline float e4m3_inverse(double scale)
+{
+    int e;
+    return frexp(scale, &e) == 0.5 && e > -120 && e < 120 ? (float)(1.0 / scale) : 0.f;
+}
+// Codes of two values (bits 0-7 and 8-15) by the hardware conversion: nearest even, saturating at +-448, NaN
+// stays NaN; bits 16-31 are zero.
+__device__ __forceinline__ uint32_t e4m3_cvt2(float f0, float f1)
+{
+    if (f0 == f0) f0 = fminf(fmaxf(f0, -448.f), 448.f);
+    if (f1 == f1) f1 = fminf(fmaxf(f1, -448.f), 448.f);
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(f0, f1, 0, false);
+}
+// Codes of f0 / scale and f1 / scale, inv = e4m3_inverse(scale).  The double-precision form costs about a hundred
+// instructions per value: 64 values per lane of the decode attention's last workers were a third of that kernel's
+// time at five sequences (23 -> 14 us), and the append of a decode step waited on it (7.2 -> 6.0 us).
+__device__ __forceinline__ uint32_t e4m3_encode2(float f0, float f1, double scale, float inv)
+{
+    if (inv != 0.f) return e4m3_cvt2(f0 * inv, f1 * inv);
+    return e4m3_encode((double)f0 / scale) | (e4m3_encode((double)f1 / scale) << 8);
+}
 
 // Packed weight layout of the matrix-core kernels.  A [N, K] matrix is cut into blocks of 16 rows x
 // 32 k (1 KB); inside a block the order is [k/8][row][k%8], i.e. exactly the register image of one
@@ -165,6 +190,11 @@ __device__ __forceinline__ void rmsnorm_bf16_row(const uint4 *__restrict__ xr, c
 constexpr int kMetaChunk = 255;  // ints carried by value per meta-kernel launch (+1 for cu_seqlens)
 struct IntChunk {
     int32_t v[256];
+};
+// The same for calls with more sequences, near the 4 KB that a kernel's arguments may take: 384 slots are one launch
+// instead of two or three of 4 - 5 us each, while short calls keep the smaller copy.
+struct IntChunkLong {
+    int32_t v[960];
 };
 struct IntDst4 {
     int32_t *dst[4];
@@ -274,6 +304,7 @@ struct RopeArgs {
     int32_t blocked;
     int32_t fp8;             // blocked cache of E4M3 codes: element stored = code of x / scale
     double k_scale, v_scale;
+    float k_inv, v_inv;      // e4m3_inverse of the scales (8-bit cache)
     const double *inv_freq;  // [hd/2] rope_base^(-2i/hd)
     const float2 *table;     // optional [table_len][hd/2] (cos, sin) of pos * inv_freq, made in double
     int32_t table_len;
@@ -308,8 +339,9 @@ __device__ __forceinline__ void append_token_body(const RopeArgs &a, int t, floa
         const size_t plane = ((size_t)slot * a.Hkv + gk) * plane_elems;
         if (a.fp8) {
             uint8_t *p8 = (uint8_t *)a.k_cache + plane;
-            p8[kblk8_off(pos, i)] = (uint8_t)e4m3_encode((double)y0 / a.k_scale);
-            p8[kblk8_off(pos, i + half)] = (uint8_t)e4m3_encode((double)y1 / a.k_scale);
+            const uint32_t code = e4m3_encode2(y0, y1, a.k_scale, a.k_inv);
+            p8[kblk8_off(pos, i)] = (uint8_t)code;
+            p8[kblk8_off(pos, i + half)] = (uint8_t)(code >> 8);
         } else {
             uint16_t *pk = (uint16_t *)a.k_cache + plane;
             pk[kblk_off(pos, i)] = f2bf(y0).x;
@@ -321,7 +353,7 @@ __device__ __forceinline__ void append_token_body(const RopeArgs &a, int t, floa
         const int gv = idx / a.hd, i = idx - gv * a.hd;
         const size_t plane = ((size_t)slot * a.Hkv + gv) * plane_elems;
         if (a.fp8)
-            ((uint8_t *)a.v_cache)[plane + vblk8_off(pos, i)] = (uint8_t)e4m3_encode((double)bfbits2f(vsrc[idx]) / a.v_scale);
+            ((uint8_t *)a.v_cache)[plane + vblk8_off(pos, i)] = (uint8_t)e4m3_encode2(bfbits2f(vsrc[idx]), 0.f, a.v_scale, a.v_inv);
         else
             ((uint16_t *)a.v_cache)[plane + vblk_off(pos, i)] = vsrc[idx];
     }
@@ -442,13 +474,15 @@ struct DecodeAttnArgs {
     int32_t rope_table_len;
     const double *inv_freq;    // [64], for positions beyond the table
     double k_scale_d, v_scale_d;
+    float k_inv, v_inv;
 };
 hipError_t launch_decode_attn_mfma(const DecodeAttnArgs &a, hipStream_t s);
 // pos[b] = len[slot[b]]; len[slot[b]] += 1; chunk_cu = prefix sum of ceil((pos+1)/chunk_keys);
 // chunk_seq[c] = b for the chunks c of sequence b
 hipError_t launch_decode_meta_chunks(const int32_t *d_slots, int B, int32_t *d_len, int32_t *d_pos,
                                      int32_t *chunk_cu, int32_t *chunk_seq, int chunk_keys, hipStream_t s);
-// the same for B <= 256 with the slots taken from the host array (and stored to d_slots): one launch
+// the same for B <= kMetaUploadRows with the slots taken from the host array (and stored to d_slots): one launch
+constexpr int kMetaUploadRows = 960;     // an IntChunkLong
 hipError_t launch_decode_meta_chunks_upload(const int32_t *host_slots, int32_t *d_slots, int B, int32_t *d_len,
                                             int32_t *d_pos, int32_t *chunk_cu, int32_t *chunk_seq, int chunk_keys,
                                             hipStream_t s);

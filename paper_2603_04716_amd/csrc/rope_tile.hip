@@ -16,32 +16,11 @@ namespace pd {
 
 constexpr int kTileRow = 128 + 2;     // LDS row stride of the value tile (elements): columns fall on different banks
 
-// Eight codes of f: nearest even, saturating at +-448; NaN stays NaN.
-__device__ __forceinline__ uint2 e4m3_encode8(float (&f)[8])
+// Codes of f / scale, inv = e4m3_inverse(scale).
+__device__ __forceinline__ uint2 encode_run(const float (&f)[8], double scale, float inv)
 {
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (f[j] == f[j]) f[j] = fminf(fmaxf(f[j], -448.f), 448.f);
-    int lo = __builtin_amdgcn_cvt_pk_fp8_f32(f[0], f[1], 0, false);
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(f[2], f[3], lo, true);
-    int hi = __builtin_amdgcn_cvt_pk_fp8_f32(f[4], f[5], 0, false);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(f[6], f[7], hi, true);
-    return make_uint2((uint32_t)lo, (uint32_t)hi);
-}
-
-// Codes of f / scale.  inv: 1 / scale where scale is a power of two in fp32's range (the fp32 product is then the
-// quotient, and the hardware rounds it like e4m3_encode), else 0.
-__device__ __forceinline__ uint2 encode_run(float (&f)[8], double scale, float inv)
-{
-    if (inv != 0.f) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) f[j] *= inv;
-        return e4m3_encode8(f);
-    }
-    uint32_t c[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) c[j] = e4m3_encode((double)f[j] / scale);
-    return make_uint2(c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24), c[4] | (c[5] << 8) | (c[6] << 16) | (c[7] << 24));
+    return make_uint2(e4m3_encode2(f[0], f[1], scale, inv) | (e4m3_encode2(f[2], f[3], scale, inv) << 16),
+                      e4m3_encode2(f[4], f[5], scale, inv) | (e4m3_encode2(f[6], f[7], scale, inv) << 16));
 }
 
 __device__ __forceinline__ uint4 pack8(const float (&f)[8])
@@ -60,7 +39,7 @@ __device__ __forceinline__ void unpack8(uint4 v, float (&f)[8])
 }
 
 template <bool FP8>
-__global__ __launch_bounds__(512) void rope_tile_kernel(RopeArgs a, RopeTiles t, float k_inv, float v_inv)
+__global__ __launch_bounds__(512) void rope_tile_kernel(RopeArgs a, RopeTiles t)
 {
     __shared__ uint32_t tile32[64 * kTileRow / 2];
     uint16_t *tile = (uint16_t *)tile32;
@@ -123,8 +102,8 @@ __global__ __launch_bounds__(512) void rope_tile_kernel(RopeArgs a, RopeTiles t,
                 if (queries || slot < 0) continue;
                 if (FP8) {
                     uint8_t *kp = (uint8_t *)a.k_cache + plane;
-                    *(uint2 *)(kp + kblk8_off(pos, c8)) = encode_run(y0, a.k_scale, k_inv);
-                    *(uint2 *)(kp + kblk8_off(pos, c8 + 64)) = encode_run(y1, a.k_scale, k_inv);
+                    *(uint2 *)(kp + kblk8_off(pos, c8)) = encode_run(y0, a.k_scale, a.k_inv);
+                    *(uint2 *)(kp + kblk8_off(pos, c8 + 64)) = encode_run(y1, a.k_scale, a.k_inv);
                 } else {
                     uint16_t *kp = (uint16_t *)a.k_cache + plane;
                     *(uint4 *)(kp + (a.blocked ? kblk_off(pos, c8) : (size_t)pos * 128 + c8)) = o0;
@@ -175,7 +154,7 @@ __global__ __launch_bounds__(512) void rope_tile_kernel(RopeArgs a, RopeTiles t,
             float f[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) f[j] = bfbits2f(v[j]);
-            const uint2 code = encode_run(f, a.v_scale, v_inv);
+            const uint2 code = encode_run(f, a.v_scale, a.v_inv);
             uint8_t *vp = (uint8_t *)a.v_cache + plane + (size_t)(tb >> 6) * 8192 + (size_t)e * 8;
             if (whole) {
                 *(uint2 *)vp = code;
@@ -210,15 +189,11 @@ bool rope_tile_supported(int dtype, const RopeArgs &a)
 hipError_t launch_rope_tile(const RopeArgs &a, const RopeTiles &t, hipStream_t s)
 {
     if (a.T <= 0) return hipSuccess;
-    auto inverse = [](double scale) {
-        int e;
-        return frexp(scale, &e) == 0.5 && e > -120 && e < 120 ? (float)(1.0 / scale) : 0.f;
-    };
     const dim3 grid((unsigned)((t.max_len + (t.prefix ? 126 : 63)) / 64), (unsigned)(2 * a.Hkv), (unsigned)t.n_seqs);
     // a row per eight threads, up to the whole tile
     const unsigned nt = (unsigned)(t.max_len >= 64 || t.prefix ? 512 : (t.max_len + 7) / 8 * 64);
-    if (a.fp8) rope_tile_kernel<true><<<grid, nt, 0, s>>>(a, t, inverse(a.k_scale), inverse(a.v_scale));
-    else rope_tile_kernel<false><<<grid, nt, 0, s>>>(a, t, 0.f, 0.f);
+    if (a.fp8) rope_tile_kernel<true><<<grid, nt, 0, s>>>(a, t);
+    else rope_tile_kernel<false><<<grid, nt, 0, s>>>(a, t);
     return hipGetLastError();
 }
 
