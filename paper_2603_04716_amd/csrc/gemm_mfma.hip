@@ -621,17 +621,33 @@ static int choose_splits(const GemmArgs &a, int BM, int BN)
 // their best split, us: bf16 QKV 771 rows 68 -> 59 (192), O 512 rows 39 -> 33 (128, 8 waves), gate/up 300 rows
 // 110 -> 88 (192), down 5107 rows 737 -> 641 (192); 8-bit QKV 512 rows 40 -> 23, O 1024 rows 46 -> 27 (128, 8 waves),
 // gate/up 300 rows 60 -> 46 (192).
+// A grouped product's loads are known only on the average, so another form than 256 x 256 has to be 5 % ahead there
+// (without that, 9200 rows on 8 experts took 4330 instead of 4265 us).  Prefill layer of 8 experts,
+// top 2, 256 x 256 -> planned, us: 1100 rows 1530 -> 1326, 1300 1588 -> 1353, 2100 2475 -> 2219, 2600 2590 -> 2486,
+// 1700 and 3000 .. 4600 the same.
 enum TileForm { TILE_256, TILE_192, TILE_128_PAIR, TILE_128_DEEP };
 struct TilePlan {
     TileForm form;
     int splits;
 };
 
+// Row tiles of height bm.  Only the device knows the rows of each group of a grouped product: the mean number over
+// groups that spread around their mean as rows dealt at random would.
+static double row_tiles(const GemmArgs &a, int bm)
+{
+    if (!a.group_offsets) return (double)((a.M + bm - 1) / bm);
+    const double mean = (double)a.M / a.n_groups, sd = sqrt(mean * (1.0 - 1.0 / a.n_groups));
+    const double z[] = {-1.64, -1.04, -0.67, -0.39, -0.13, 0.13, 0.39, 0.67, 1.04, 1.64};
+    double sum = 0.0;
+    for (double q : z) sum += ceil(fmax(mean + q * sd, 0.0) / bm);
+    return sum / 10.0 * a.n_groups;
+}
+
 static TilePlan plan_tiles(const GemmArgs &a)
 {
     const int n_cols = a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N;
     const int nk = a.K / BK;
-    const bool can_split = a.splitk_ws && a.N % 4 == 0 && a.ldc % 4 == 0 && (a.epilogue != EPI_RESIDUAL || a.ldr % 4 == 0);
+    const bool can_split = a.splitk_ws && !a.group_offsets && !a.a_gather && a.N % 4 == 0 && a.ldc % 4 == 0 && (a.epilogue != EPI_RESIDUAL || a.ldr % 4 == 0);
     TilePlan best = {TILE_256, 1};
     double best_us = 1e30;
     const struct {
@@ -640,7 +656,7 @@ static TilePlan plan_tiles(const GemmArgs &a)
         double kt_us;
     } forms[] = {{TILE_256, 256, 256, 1.80}, {TILE_192, 192, 256, 1.45}, {TILE_128_PAIR, 128, 128, 1.06}, {TILE_128_DEEP, 128, 128, 0.66}};
     for (const auto &f : forms) {
-        const long long tiles = (long long)((a.M + f.bm - 1) / f.bm) * ((n_cols + f.bn - 1) / f.bn);
+        const long long tiles = (long long)ceil(row_tiles(a, f.bm) * ((n_cols + f.bn - 1) / f.bn));
         for (int sp = 1; sp <= 8; ++sp) {
             if (sp > 1 && (!can_split || nk / sp < 6 || (size_t)sp * a.M * n_cols > a.splitk_ws_elems)) break;
             const long long wg = tiles * sp;
@@ -654,6 +670,7 @@ static TilePlan plan_tiles(const GemmArgs &a)
             double us = rounds * ((nk + sp - 1) / sp) * kt_us + 5.0;
             if (sp > 1) us += 5.0 + (double)sp * a.M * n_cols * 8.0 / 8e6;
             else if (a.fuse_y) us += 4.0;              // the norm that a split's sum carries costs a launch of its own
+            if (a.group_offsets && f.form != TILE_256) us *= 1.05;
             if (us < best_us) {
                 best_us = us;
                 best = {f.form, sp};
@@ -689,7 +706,6 @@ static hipError_t launch_planned(const GemmArgs &a, hipStream_t s)
 
 hipError_t launch_gemm_mfma_f8(const GemmArgs &a, hipStream_t s)
 {
-    if (a.group_offsets || a.a_gather) return launch_cfg<256, 256, 2, 4, 2, true>(a, s);
     return launch_planned<true>(a, s);
 }
 
@@ -698,10 +714,7 @@ hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s)
     // rows that share a weight matrix: for a grouped problem the mean group size picks the tile
     // (larger groups take several row tiles)
     const int rows = a.group_offsets ? (a.M + a.n_groups - 1) / a.n_groups : a.M;
-    if (rows > 256) {
-        if (a.group_offsets || a.a_gather) return launch_cfg<256, 256, 2, 4, 2>(a, s);
-        return launch_planned<false>(a, s);
-    }
+    if (rows > 256) return launch_planned<false>(a, s);
     const int n_cols = a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N;
     const bool wide = n_cols >= 16384;                            // enough column tiles without splitting K
     if (rows > 128) {
