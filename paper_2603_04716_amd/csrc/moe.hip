@@ -42,9 +42,9 @@ hipError_t launch_router_logits(int dtype, const void *y, const void *w_router, 
 // and the selection compares logits; logits closer than 1e-6 (where rounding could make two
 // probabilities equal, which the lower index then wins) are decided on the probabilities
 // themselves.  Only those and the chosen experts' weights need exponentials.
-__device__ __forceinline__ void moe_topk_token(const MoeRouteArgs &a, int t, int *chosen = nullptr)
+// r: the token's logits.
+__device__ __forceinline__ void moe_topk_token(const MoeRouteArgs &a, int t, const float *r, int *chosen = nullptr)
 {
-    const float *r = a.logits + (size_t)t * a.E;
     double mx = -INFINITY;
     for (int e = 0; e < a.E; ++e) mx = fmax(mx, (double)r[e]);
     double denom = 0.0;
@@ -81,32 +81,55 @@ __device__ __forceinline__ void moe_topk_token(const MoeRouteArgs &a, int t, int
 __global__ void moe_topk_kernel(MoeRouteArgs a)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < a.T) moe_topk_token(a, t);
+    if (t < a.T) moe_topk_token(a, t, a.logits + (size_t)t * a.E);
 }
 
-// Decode-sized routing, at most 64 (token, expert) pairs: one wavefront selects the experts and
-// sorts the pairs in a single launch.  Lane i owns pair i; for every expert a ballot gives the
-// lanes that chose it, so a pair's place is the expert's base plus the number of lower lanes with
-// the same expert: the same stable order as the general kernel.
-__global__ __launch_bounds__(64) void moe_route_small_kernel(MoeRouteArgs a)
+// Decode-sized routing, up to 1024 (token, expert) pairs: one workgroup selects the experts and sorts the pairs in a
+// single launch.  A token's selection is a chain of some thirty reads of its logits, so they are staged in LDS.  Thread i
+// owns pair i; a ballot per expert gives the lanes of a wave that chose it, so a pair's place is the expert's first
+// place, plus the pairs of that expert in earlier waves and in lower lanes: the same stable order as the general
+// kernels.  64 tokens, 8 experts: 10.3 us against 9.5 + 5.0 + 5.1 for the three launches of the general form.
+constexpr int kRouteSmallPairs = 1024, kRouteSmallLogits = 10240;   // 40 KB
+constexpr int kRouteRowPad = 1;       // tokens' logits on different banks
+__global__ __launch_bounds__(1024) void moe_route_small_kernel(MoeRouteArgs a)
 {
-    __shared__ int chosen[64];
-    const int lane = threadIdx.x;
-    const int P = a.T * a.top_k;
-    if (lane < a.T) moe_topk_token(a, lane, chosen);
+    __shared__ float rl[kRouteSmallLogits];
+    __shared__ int chosen[kRouteSmallPairs];
+    __shared__ int wcnt[64][16], first[64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+    const int P = a.T * a.top_k, pitch = a.E + kRouteRowPad;
+    for (int i = tid; i < a.T * a.E; i += blockDim.x) rl[i / a.E * pitch + i % a.E] = a.logits[i];
     __syncthreads();
-    const int e = lane < P ? chosen[lane] : -1;
-    int base = 0;
-    if (lane == 0) a.offsets[0] = 0;
+    if (tid < a.T) moe_topk_token(a, tid, rl + tid * pitch, chosen);
+    __syncthreads();
+    const int e = tid < P ? chosen[tid] : -1;
+    int rank = 0;
     for (int ex = 0; ex < a.E; ++ex) {
         const unsigned long long mask = __ballot(e == ex);
-        if (e == ex) {
-            const int pos = base + __popcll(mask & ((1ull << lane) - 1ull));
-            a.sorted_token[pos] = lane / a.top_k;
-            a.pair_pos[lane] = pos;
+        if (e == ex) rank = __popcll(mask & ((1ull << lane) - 1ull));
+        if (lane == 0) wcnt[ex][wave] = __popcll(mask);
+    }
+    __syncthreads();
+    if (wave == 0) {                                  // lane ex: an expert's pairs, then the sum over lower experts
+        int n = 0;
+        if (lane < a.E)
+            for (int w = 0; w < nw; ++w) n += wcnt[lane][w];
+        int inc = n;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += v;
         }
-        base += __popcll(mask);
-        if (lane == 0) a.offsets[ex + 1] = base;
+        first[lane] = inc - n;
+        if (lane < a.E) a.offsets[lane + 1] = inc;
+        if (lane == 0) a.offsets[0] = 0;
+    }
+    __syncthreads();
+    if (e >= 0) {
+        int pos = first[e] + rank;
+        for (int w = 0; w < wave; ++w) pos += wcnt[e][w];
+        a.sorted_token[pos] = tid / a.top_k;
+        a.pair_pos[tid] = pos;
     }
 }
 
@@ -220,8 +243,8 @@ __global__ __launch_bounds__(256) void moe_block_scatter_kernel(MoeRouteArgs a, 
 hipError_t launch_moe_route(const MoeRouteArgs &a, hipStream_t s)
 {
     if (a.T <= 0) return hipSuccess;
-    if (a.T * a.top_k <= 64) {
-        moe_route_small_kernel<<<1, 64, 0, s>>>(a);
+    if (a.E <= 64 && (long long)a.T * a.top_k <= kRouteSmallPairs && (long long)a.T * (a.E + kRouteRowPad) <= kRouteSmallLogits) {
+        moe_route_small_kernel<<<1, (unsigned)((a.T * a.top_k + 63) / 64 * 64), 0, s>>>(a);
         return hipGetLastError();
     }
     moe_topk_kernel<<<(a.T + 255) / 256, 256, 0, s>>>(a);

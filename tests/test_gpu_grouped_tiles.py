@@ -32,3 +32,21 @@ def test_grouped_products_deal_the_tiles_in_use(T, d_ff, skew):
     assert relmax(got, ref) <= TOL["bf16"]
     assert max(relmax(got[i], ref[i]) for i in range(T)) <= 2 * TOL["bf16"]
     gl.close()
+
+
+@pytest.mark.parametrize("T,E,top_k", [(31, 8, 2), (32, 8, 2), (33, 8, 2), (512, 8, 2), (513, 8, 2), (200, 64, 5), (128, 64, 8), (157, 64, 6), (158, 64, 6), (1, 3, 1)])
+def test_routing_in_one_launch(T, E, top_k):
+    """Up to 1024 pairs and 10240 staged logits are sorted by one workgroup, more by the general kernels; the place of
+    every pair shows in the rows' outputs, ties go to the lower expert."""
+    cfg = I.small_config(dtype="bf16", d_model=128, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=64, n_experts=E, top_k=top_k)
+    w = I.layer_weights(cfg, std=0.05)
+    ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
+    r = I.router_logits(T, E, seed=T + E)
+    r[T // 2] = 0.25
+    cu = np.array([0, T], np.int32)
+    x = I.hidden(T, cfg["d_model"], seed=9, dtype="bf16")
+    ref, eref = O.prefill(ol, x, cu, router_logits=r, return_experts=True)
+    got = gl.prefill(x, cu, router_logits=r)
+    assert np.array_equal(gl.experts(T), eref)
+    assert max(relmax(got[i], ref[i]) for i in range(T)) <= 2 * TOL["bf16"]
+    gl.close()
