@@ -19,6 +19,8 @@
 // W8 form: the weights are E4M3 codes with one power-of-two scale per weight row (half the bytes).
 // One 16-byte-per-lane load then carries the operands of two k-steps; the codes are widened to bf16
 // in registers (exact) and the row scale multiplies the accumulated sum in the epilogue.
+#include <type_traits>
+
 #include "pd_internal.h"
 
 namespace pd {
@@ -27,9 +29,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-// GV_WAVES waves split K; each keeps GV_UNROLL blocks per row block in flight.  Measured on the 8B
-// shapes: the SwiGLU pair streams fastest with 2 waves x 16 blocks, a long K (the down projection)
-// with 8 waves x 4, the short square ones with 4 x 8.
+// GV_WAVES waves split K; each keeps GV_UNROLL 1 KB blocks per row block in flight.  Measured on the 8B
+// shapes: the SwiGLU pair streams fastest with 2 waves x 16 blocks, a long K (the down projection) with 8 waves x 4,
+// the short square ones with 4 x 8.  8-bit blocks hold two k-steps: half as many for the pair and for QKV (9.3 us either
+// way, 14 rows 11.7 -> 13.0 with eight), but as many for the residual products, whose waves otherwise make twice the
+// round trips: 5 rows down 16.7 -> 13.3, O 7.3 -> 6.5 us; 14 rows 18.4 -> 19.1, 8.1 -> 7.8.
 __device__ __forceinline__ bf16x8 w8_to_bf16(unsigned w0, unsigned w1)
 {
     auto f0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w0, false);
@@ -95,18 +99,20 @@ __global__ __launch_bounds__(64 * GV_WAVES) void gemv_mfma_kernel(GemmArgs a)
 
     int s = s_begin;
     if (W8) {
-        constexpr int U = GV_UNROLL / 2 > 0 ? GV_UNROLL / 2 : 1;     // pairs of k-steps per batch
-        for (; s + U <= s_end; s += U) {
+        constexpr int U = GV_UNROLL;                  // pairs of k-steps per batch
+        // the last batch may reach past s_end: it asks for the last pair again and multiplies it with zeros
+        auto batch = [&](auto part) {
             u32x4 wr[RB][U];
             bf16x8 xf[U][2];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                const int su = part.value ? min(s + u, s_end - 1) : s + u;
 #pragma unroll
-                for (int i = 0; i < RB; ++i) wr[i][u] = *(const u32x4 *)(wp8[i] + (size_t)(s + u) * 1024);
+                for (int i = 0; i < RB; ++i) wr[i][u] = *(const u32x4 *)(wp8[i] + (size_t)su * 1024);
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     u32x4 z = {0u, 0u, 0u, 0u};
-                    if (xrow) z = *(const u32x4 *)(xp + (size_t)(2 * (s + u) + h) * 32);
+                    if (xrow && (!part.value || s + u < s_end)) z = *(const u32x4 *)(xp + (size_t)(2 * su + h) * 32);
                     xf[u][h] = __builtin_bit_cast(bf16x8, z);
                 }
             }
@@ -120,20 +126,9 @@ __global__ __launch_bounds__(64 * GV_WAVES) void gemv_mfma_kernel(GemmArgs a)
                     acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w8_to_bf16(wr[i][u][2], wr[i][u][3]), xf[u][1],
                                                                      acc[i], 0, 0, 0);
                 }
-        }
-        for (; s < s_end; ++s) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                u32x4 z = {0u, 0u, 0u, 0u};
-                if (xrow) z = *(const u32x4 *)(xp + (size_t)(2 * s + h) * 32);
-                bf16x8 xf = __builtin_bit_cast(bf16x8, z);
-#pragma unroll
-                for (int i = 0; i < RB; ++i) {
-                    const uint2 wr = *(const uint2 *)(wp8[i] + (size_t)s * 1024 + h * 8);
-                    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w8_to_bf16(wr.x, wr.y), xf, acc[i], 0, 0, 0);
-                }
-            }
-        }
+        };
+        for (; s + U <= s_end; s += U) batch(std::false_type{});
+        if (s < s_end) batch(std::true_type{});
     } else {
     for (; s + GV_UNROLL <= s_end; s += GV_UNROLL) {
         bf16x8 wf[RB][GV_UNROLL], xf[GV_UNROLL];
@@ -229,16 +224,17 @@ static void launch_gemv_t(const GemmArgs &a, hipStream_t s)
 {
     const dim3 grid(a.N / 16, a.group_offsets ? a.n_groups : 1);
     const bool long_k = a.K >= 8192;
+    constexpr int UN = W8 ? 4 : 8, UG = W8 ? 8 : 16;
     switch (a.epilogue) {
     case EPI_NONE:
         if (long_k) gemv_mfma_kernel<EPI_NONE, 8, 4, W8><<<grid, 512, 0, s>>>(a);
-        else gemv_mfma_kernel<EPI_NONE, 4, 8, W8><<<grid, 256, 0, s>>>(a);
+        else gemv_mfma_kernel<EPI_NONE, 4, UN, W8><<<grid, 256, 0, s>>>(a);
         break;
     case EPI_RESIDUAL:
         if (long_k) gemv_mfma_kernel<EPI_RESIDUAL, 8, 4, W8><<<grid, 512, 0, s>>>(a);
         else gemv_mfma_kernel<EPI_RESIDUAL, 4, 8, W8><<<grid, 256, 0, s>>>(a);
         break;
-    default: gemv_mfma_kernel<EPI_SWIGLU, 2, 16, W8><<<grid, 128, 0, s>>>(a); break;
+    default: gemv_mfma_kernel<EPI_SWIGLU, 2, UG, W8><<<grid, 128, 0, s>>>(a); break;
     }
 }
 
