@@ -9,7 +9,8 @@
 // holding channels 8i .. 8i + 7 and their partners 64 higher, so cosines and sines are loaded once for all heads.
 // Measured (8B shape, rope + transposition, which was a launch of its own, -> this kernel): 8192 rows 77 + 8 -> 44 us
 // (218 MB: 5.0 TB/s), 5107 rows into an 8-bit cache 57 + 6 -> 32 us, 771 rows 15 + 5 -> 9 us, a 512-row chunk
-// 11 -> 6.5 us.
+// 11 -> 6.5 us.  The whole workgroup also for a few rows: with eight threads a row the values of 13 rows took eight
+// dependent passes (a call of one 13-row prompt into an 8-bit cache 92.7 us, now 88.6; a launch per row before: 89.4).
 #include "pd_internal.h"
 
 namespace pd {
@@ -145,6 +146,7 @@ __global__ __launch_bounds__(512) void rope_tile_kernel(RopeArgs a, RopeTiles t)
         const int half = FP8 ? e & 1 : e >> 9;
         const int d = FP8 ? (e >> 7) * 16 + ((e >> 1) & 15) : (e >> 2) & 127, q = FP8 ? (e >> 5) & 3 : e & 3;
         const int p = half * 32 + 4 * q;
+        if (tb + p >= hi) continue;
         const uint16_t *c = tile + p * kTileRow + d;
         uint16_t v[8];
 #pragma unroll
@@ -190,10 +192,8 @@ hipError_t launch_rope_tile(const RopeArgs &a, const RopeTiles &t, hipStream_t s
 {
     if (a.T <= 0) return hipSuccess;
     const dim3 grid((unsigned)((t.max_len + (t.prefix ? 126 : 63)) / 64), (unsigned)(2 * a.Hkv), (unsigned)t.n_seqs);
-    // a row per eight threads, up to the whole tile
-    const unsigned nt = (unsigned)(t.max_len >= 64 || t.prefix ? 512 : (t.max_len + 7) / 8 * 64);
-    if (a.fp8) rope_tile_kernel<true><<<grid, nt, 0, s>>>(a, t);
-    else rope_tile_kernel<false><<<grid, nt, 0, s>>>(a, t);
+    if (a.fp8) rope_tile_kernel<true><<<grid, 512, 0, s>>>(a, t);
+    else rope_tile_kernel<false><<<grid, 512, 0, s>>>(a, t);
     return hipGetLastError();
 }
 
