@@ -446,8 +446,13 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(RopeArgs a)
         int h = idx / half, i = idx - h * half;
         T *v = row + (size_t)h * a.hd;
         float x0 = Elem<T>::ld(v + i), x1 = Elem<T>::ld(v + i + half);
-        float y0 = x0 * cs[i] - x1 * sn[i];
-        float y1 = x1 * cs[i] + x0 * sn[i];
+        float y0, y1;
+        if (sizeof(T) == 2) {
+            rope_pair(x0, x1, cs[i], sn[i], y0, y1);
+        } else {                                       // fp32 rows are rotated here only
+            y0 = fmaf(x0, cs[i], -(x1 * sn[i]));
+            y1 = fmaf(x1, cs[i], x0 * sn[i]);
+        }
         Elem<T>::st(v + i, y0);
         Elem<T>::st(v + i + half, y1);
         if (slot >= 0 && h >= a.Hq) {

@@ -135,6 +135,15 @@ __device__ __forceinline__ uint32_t e4m3_encode2(float f0, float f1, double scal
     return e4m3_encode((double)f0 / scale) | (e4m3_encode((double)f1 / scale) << 8);
 }
 
+// Rotary embedding of one channel pair of a bf16 layer, for every kernel that stores a rotated row.  The fused
+// multiply-adds are written out: left to the compiler, these kernels rounded different products, and a key's bits
+// depended on the call that brought it.
+__device__ __forceinline__ void rope_pair(float x0, float x1, float c, float s, float &y0, float &y1)
+{
+    y0 = fmaf(x0, c, -(x1 * s));
+    y1 = fmaf(x0, s, x1 * c);
+}
+
 // Packed weight layout of the matrix-core kernels.  A [N, K] matrix is cut into blocks of 16 rows x
 // 32 k (1 KB); inside a block the order is [k/8][row][k%8], i.e. exactly the register image of one
 // v_mfma_f32_16x16x32_bf16 A operand (lane = 16*(k/8) + row holds 8 consecutive k), so a wave reads
@@ -335,7 +344,8 @@ __device__ __forceinline__ void append_token_body(const RopeArgs &a, int t, floa
         const int gk = idx / half, i = idx - gk * half;
         const uint16_t *kv = row + (size_t)(a.Hq + gk) * a.hd;
         const float x0 = bfbits2f(kv[i]), x1 = bfbits2f(kv[i + half]);
-        const float y0 = x0 * cs[i] - x1 * sn[i], y1 = x1 * cs[i] + x0 * sn[i];
+        float y0, y1;
+        rope_pair(x0, x1, cs[i], sn[i], y0, y1);
         const size_t plane = ((size_t)slot * a.Hkv + gk) * plane_elems;
         if (a.fp8) {
             uint8_t *p8 = (uint8_t *)a.k_cache + plane;

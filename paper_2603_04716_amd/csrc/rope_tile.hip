@@ -93,10 +93,7 @@ __global__ __launch_bounds__(512) void rope_tile_kernel(RopeArgs a, RopeTiles t)
                 unpack8(r0[u], x0);
                 unpack8(r1[u], x1);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    y0[j] = x0[j] * cs[j] - x1[j] * sn[j];
-                    y1[j] = x1[j] * cs[j] + x0[j] * sn[j];
-                }
+                for (int j = 0; j < 8; ++j) rope_pair(x0[j], x1[j], cs[j], sn[j], y0[j], y1[j]);
                 const uint4 o0 = pack8(y0), o1 = pack8(y1);
                 *(uint4 *)(p + 128 * u) = o0;
                 *(uint4 *)(p + 128 * u + 64) = o1;

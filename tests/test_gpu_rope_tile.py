@@ -88,3 +88,39 @@ def test_chunk_past_the_rotary_table():
     assert relmax(gl.prefill_chunk(x, cu, [0], gc), O.prefill_chunk(ol, x, cu, [0], oc)) <= TOL["bf16"]
     _check_cache(gl, gc, oc, [0], None)
     gl.close()
+
+
+def _stored_keys(gc, slots, n_kv_heads, n):
+    k = torch.empty((len(slots), n_kv_heads, n, 128), dtype=torch.bfloat16, device="cuda")
+    for i, s in enumerate(slots):
+        pd.pd_kv_cache_get(gc, s, k[i], torch.empty_like(k[i]))
+    torch.cuda.synchronize()
+    return k.view(torch.int16)
+
+
+def test_a_key_has_the_same_bits_whichever_call_brings_it():
+    """The same rows (so the same projections: neither product depends on how rows are grouped into sequences) at the
+    same positions, rotated by tiles (prefill, longer chunks), row by row (chunks of a few tokens) and in the append
+    of a decode step: every stored key is the same bit pattern, 131072 and 32768 pairs of channels."""
+    cfg = I.small_config(dtype="bf16", d_model=128, n_q_heads=32, n_kv_heads=32, head_dim=128, d_ff=128)
+    gl = GpuLayer(cfg, I.layer_weights(cfg, std=0.05))
+    n, L = 8, 8
+    x = I.hidden(n * L, cfg["d_model"], seed=3, dtype="bf16")
+    cu, slots = np.arange(0, n * L + 1, L).astype(np.int32), list(range(n))
+    tiled, rows = gl.cache(n, 64), gl.cache(n, 64)
+    gl.prefill(x, cu, tiled, slots)
+    gl.prefill_chunk(x, cu, slots, rows)
+    assert torch.equal(_stored_keys(tiled, slots, 32, L), _stored_keys(rows, slots, 32, L))
+
+    p = 50                                           # a chunk of 16 rows at positions 50 .. 65 and 16 slots of one row each
+    x = x[:16]
+    chunk, steps = gl.cache(1, 128), gl.cache(16, 128)
+    for s in range(16):
+        pd.pd_kv_cache_set_len(steps, s, p + s)
+    pd.pd_kv_cache_set_len(chunk, 0, p)
+    gl.prefill_chunk(x, np.array([0, 16], np.int32), [0], chunk)
+    gl.decode(x, list(range(16)), steps)
+    want, got = _stored_keys(chunk, [0], 32, p + 16)[0], _stored_keys(steps, list(range(16)), 32, p + 16)
+    for s in range(16):
+        assert torch.equal(got[s, :, p + s], want[:, p + s])
+    gl.close()
