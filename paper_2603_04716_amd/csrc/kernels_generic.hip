@@ -620,6 +620,11 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a)
     }
 }
 
+// What a wave's scores are taken from before the exponential.  A wave of the kernels below walks only a part of the
+// keys, and every score that it has seen may be -infinity where other waves' are not: their weight is 0, not
+// exp(-inf + inf).
+__device__ __forceinline__ float finite_from(float m) { return m == -INFINITY ? 0.f : m; }
+
 // fp32 rows over a cache (decode), head sizes 32, 64, 128 and 256: a few hundred keys are a serial chain of
 // memory round trips, so the four waves of a workgroup share an item (row, query head), each walking every
 // fourth 64-key chunk, and every load is 16 bytes.  Scores: a lane per key, hd / 4 independent loads.
@@ -661,9 +666,9 @@ __global__ __launch_bounds__(256) void attn_decode_f32_kernel(AttnArgs a)
             d.z = fmaf(q4.z, k4.z, d.z); d.w = fmaf(q4.w, k4.w, d.w);
         }
         const float sc = s < n_keys ? (d.x + d.y) + (d.z + d.w) : -INFINITY;
-        const float m_new = fmaxf(m, wave_max(sc));
-        const float p = s < n_keys ? expf(sc - m_new) : 0.f;
-        const float corr = expf(m - m_new);        // m = -inf on the first chunk -> 0
+        const float m_new = fmaxf(m, wave_max(sc)), from = finite_from(m_new);
+        const float p = s < n_keys ? expf(sc - from) : 0.f;
+        const float corr = expf(m - from);         // m = -inf on the first chunk -> 0
         l = l * corr + wave_sum(p);
         m = m_new;
         o.x *= corr; o.y *= corr; o.z *= corr; o.w *= corr;
@@ -770,10 +775,10 @@ __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(AttnArgs a)
         float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float m_new = fmaxf(m, mx), corr = expf(m - m_new);   // a query always sees the tile's first key
+        const float m_new = fmaxf(m, mx), from = finite_from(m_new), corr = expf(m - from);
         f32x4 p;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) p[e] = expf(s[e] - m_new);
+        for (int e = 0; e < 4; ++e) p[e] = expf(s[e] - from);
         float ps = (p[0] + p[1]) + (p[2] + p[3]);
         ps += __shfl_xor(ps, 16, 64);
         ps += __shfl_xor(ps, 32, 64);

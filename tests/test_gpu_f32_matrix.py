@@ -4,9 +4,10 @@ Bound: the fp32 bound of the other parity tests, 1e-5 of the largest element."""
 import numpy as np
 import pytest
 
+import paper_2603_04716_amd as pd
 import pd_inputs as I
 from oracle import layer as O
-from gpu_util import GpuLayer, TOL, relmax
+from gpu_util import GpuLayer, TOL, relmax, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -48,4 +49,39 @@ def test_unseen_keys_do_not_reach_a_query(head_dim):
     got = gl.prefill(x, cu)
     clean = np.r_[0:21, 40:60]
     assert np.array_equal(got[clean], want[clean]) and not np.isfinite(got[21:40]).any()
+    gl.close()
+
+
+@pytest.mark.parametrize("head_dim", [32, 64, 128, 256])
+@pytest.mark.parametrize("lost", [(0, 64), (64, 128), (192, 256), (64, 300)])
+def test_decode_with_keys_of_score_minus_infinity(head_dim, lost):
+    """Whole 64-key chunks whose scores are all -infinity (the first that a wave sees among them) have no weight."""
+    cfg = I.small_config(d_model=64, n_q_heads=2, n_kv_heads=1, head_dim=head_dim, d_ff=64)
+    w = I.layer_weights(cfg, std=0.05)
+    w["w_q"] = np.abs(w["w_q"])                      # with inputs > 0 every query channel is positive, also once the
+    x = np.abs(I.hidden(1, 64, seed=4)) + 0.1        # slowest pair (hd / 2 - 1 and hd - 1) is turned by under 0.06
+    ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
+    k, v = I.kv_fill(1, 300, head_dim, seed=6)
+    k[:, lost[0]:lost[1], head_dim // 2 - 1] = -np.inf
+    oc, gc = O.KVCache(ol, 1, 301), gl.cache(1, 301)
+    oc.set(0, k, v)
+    pd.pd_kv_cache_set(gc, 0, to_dev(k, "f32"), to_dev(v, "f32"))
+    assert relmax(gl.decode(x, [0], gc), O.decode_step(ol, x, [0], oc)) <= TOL["f32"]
+    gl.close()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128, 256])
+@pytest.mark.parametrize("lost", [(16, 32), (48, 64), (16, 80)])
+def test_prefill_with_keys_of_score_minus_infinity(head_dim, lost):
+    """The same for 16-key tiles: the lost tokens' keys overflow to -infinity in the slowest rotary pair."""
+    cfg = I.small_config(d_model=64, n_q_heads=2, n_kv_heads=1, head_dim=head_dim, d_ff=64)
+    w = I.layer_weights(cfg, std=0.05)
+    w["w_q"] = np.abs(w["w_q"])
+    w["w_k"][head_dim // 2 - 1, 0] = -3e38
+    x = np.abs(I.hidden(100, 64, seed=4)) + 0.1
+    x[:, 0] = 0.0
+    x[lost[0]:lost[1], 0] = 4.0                      # more than 1.2 after the norm: the product leaves fp32
+    ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
+    cu = np.array([0, 100], np.int32)
+    assert relmax(gl.prefill(x, cu), O.prefill(ol, x, cu)) <= TOL["f32"]
     gl.close()
