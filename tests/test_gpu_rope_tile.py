@@ -124,3 +124,73 @@ def test_a_key_has_the_same_bits_whichever_call_brings_it():
     for s in range(16):
         assert torch.equal(got[s, :, p + s], want[:, p + s])
     gl.close()
+
+
+def _many(n, long, seed):
+    """One long sequence somewhere among n - 1 of 0 .. 5 rows."""
+    lens = np.random.default_rng(seed).integers(0, 6, n)
+    lens[n // 3] = long
+    return [int(v) for v in lens]
+
+
+@pytest.mark.parametrize("form,n,long", [("bf16", 63, 300), ("fp8", 64, 300), ("bf16", 65, 700), ("fp8_odd", 130, 700),
+                                         ("none", 1000, 1500), ("none", 4096, 130), ("bf16", 300, 5), ("fp8", 300, 40)])
+def test_prefill_of_many_sequences(form, n, long):
+    """A long prompt among many short ones (tiles found by search, in one and two rounds of 64 sequences), and short
+    ones only."""
+    ol, gl = (lambda w: (O.Layer(CFG, w), GpuLayer(CFG, w)))(I.layer_weights(CFG, std=0.05))
+    scales = {"fp8": (0.5, 0.125), "fp8_odd": (0.3, 0.07)}.get(form)
+    lens = _many(n, long, n)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    x = I.hidden(int(cu[-1]), CFG["d_model"], seed=5, dtype="bf16")
+    if form == "none":
+        assert relmax(gl.prefill(x, cu), O.prefill(ol, x, cu)) <= TOL["bf16"]
+    else:
+        slots = list(range(n))[::-1]
+        oc, gc = O.KVCache(ol, n, long, fp8_scales=scales), gl.cache(n, long, fp8_scales=scales)
+        assert relmax(gl.prefill(x, cu, gc, slots), O.prefill(ol, x, cu, cache=oc, slots=slots)) <= TOL["bf16"]
+        _check_cache(gl, gc, oc, [s for s in slots if pd.pd_kv_cache_len(gc, s)], scales)
+    gl.close()
+
+
+@pytest.mark.parametrize("form", ["bf16", "fp8"])
+def test_chunk_of_many_sequences(form):
+    ol, gl = (lambda w: (O.Layer(CFG, w), GpuLayer(CFG, w)))(I.layer_weights(CFG, std=0.05))
+    scales = (0.5, 0.125) if form == "fp8" else None
+    n, cap = 90, 420
+    rng = np.random.default_rng(2)
+    prefix, lens = rng.integers(0, 140, n), np.array(_many(n, 260, 7))
+    oc, gc = O.KVCache(ol, n, cap, fp8_scales=scales), gl.cache(n, cap, fp8_scales=scales)
+    for s in range(n):
+        k, v = I.kv_fill(2, 140, 128, seed=s, dtype="bf16")
+        oc.set(s, k, v)
+        pd.pd_kv_cache_set(gc, s, to_dev(k, "bf16"), to_dev(v, "bf16"))
+        oc.lens[s] = prefix[s]
+        pd.pd_kv_cache_set_len(gc, s, int(prefix[s]))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    slots = [int(s) for s in rng.permutation(n)]
+    x = I.hidden(int(cu[-1]), CFG["d_model"], seed=6, dtype="bf16")
+    assert relmax(gl.prefill_chunk(x, cu, slots, gc), O.prefill_chunk(ol, x, cu, slots, oc)) <= TOL["bf16"]
+    _check_cache(gl, gc, oc, [s for s in slots if pd.pd_kv_cache_len(gc, s)], scales)
+    gl.close()
+
+
+def test_time_follows_the_rows_not_the_longest_sequence():
+    """8192 + 3999 x 4 rows against as many in 24 sequences: the rotation takes a few times as long (64-position tiles of
+    4 rows), not the number of sequences times the tiles of the longest (70 times)."""
+    cfg = dict(CFG, n_q_heads=32, n_kv_heads=8)
+    gl = GpuLayer(cfg, I.layer_weights(cfg, std=0.05))
+
+    def rope_ms(lens):
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        x = torch.zeros((int(cu[-1]), cfg["d_model"]), dtype=torch.bfloat16, device="cuda")
+        y, best = torch.empty_like(x), 1e9
+        for _ in range(5):
+            pd.pd_profile_enable(gl.h, True)
+            pd.pd_prefill(gl.h, x, cu, y)
+            best = min(best, dict(pd.pd_profile_read(gl.h))["rope_kv_write"])
+        return best
+
+    even = rope_ms([1008] * 24)
+    assert rope_ms([8192] + [4] * 3999) <= 8 * even
+    gl.close()
