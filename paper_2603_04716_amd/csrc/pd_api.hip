@@ -1072,7 +1072,12 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
     r.fp8 = keep ? cache->fp8 : 0; r.k_scale = keep ? cache->k_scale : 1.0; r.v_scale = keep ? cache->v_scale : 1.0;
     r.k_inv = e4m3_inverse(r.k_scale); r.v_inv = e4m3_inverse(r.v_scale);
     r.table = L->rope_table; r.table_len = kRopeTableLen;
-    if (rope_tile_supported(c.dtype, r) && !short_chunk) {
+    // Chunks have no values to transpose, and a few rows are done sooner by a workgroup per row than by tiles, whose
+    // value path is one round trip longer.  Rotation behind 200 keys (8B shape), rows -> tiles, us: bf16 cache 9 rows
+    // 6.6 -> 7.1, 64 rows 7.1 -> 7.5, 100 rows 7.5 -> 7.6, 16 x 9 rows 10.2 -> 8.4; 8-bit cache 9 rows 6.5 -> 8.1,
+    // 256 rows 8.8 -> 9.1, 16 x 32 rows 13.2 -> 11.6, 300 x 9 rows 36 -> 41, 300 x 16 rows 58 -> 49.
+    const bool by_rows = short_chunk || (chunk && (cache->fp8 ? T <= 256 || T <= 10 * n : T <= 64));
+    if (rope_tile_supported(c.dtype, r) && !by_rows) {
         RopeTiles rt;
         rt.cu = L->d_cu; rt.prefix = chunk ? L->d_prefix : nullptr; rt.slots = L->d_slots; rt.pad_cu = L->d_pad_cu;
         rt.n_seqs = n; rt.max_len = max_L; rt.vt = tile_attn && !chunk ? (uint16_t *)L->vt : nullptr; rt.vt_ld = vt_ld;

@@ -52,9 +52,11 @@ def test_prefill(form, lens):
 
 
 @pytest.mark.parametrize("form", ["bf16", "fp8", "plain"])
-@pytest.mark.parametrize("prefix,lens", [([0, 5], [20, 9]), ([63, 64], [66, 70]), ([100, 33], [9, 150])])
+@pytest.mark.parametrize("prefix,lens", [([0, 5], [20, 9]), ([63, 64], [66, 70]), ([100, 33], [9, 150]), ([3, 70], [40, 24]),
+                                         ([3, 70], [40, 25]), ([1, 60], [200, 56]), ([1, 60], [200, 57])])
 def test_chunk(form, prefix, lens):
-    """What the slots hold behind a chunk's start stays as it was, except for the chunk's own positions."""
+    """What the slots hold behind a chunk's start stays as it was, except for the chunk's own positions.  Up to 64 rows
+    (8-bit cache: 256) are rotated row by row, more by tiles."""
     cfg = PLAIN if form == "plain" else CFG
     w = I.layer_weights(cfg, std=0.05)
     ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
@@ -153,13 +155,14 @@ def test_prefill_of_many_sequences(form, n, long):
     gl.close()
 
 
-@pytest.mark.parametrize("form", ["bf16", "fp8"])
-def test_chunk_of_many_sequences(form):
+@pytest.mark.parametrize("form,long", [("bf16", 260), ("fp8", 260), ("fp8", 900)])
+def test_chunk_of_many_sequences(form, long):
+    """8-bit cache: row by row up to 10 rows per sequence on the average, by tiles that are searched beyond."""
     ol, gl = (lambda w: (O.Layer(CFG, w), GpuLayer(CFG, w)))(I.layer_weights(CFG, std=0.05))
     scales = (0.5, 0.125) if form == "fp8" else None
-    n, cap = 90, 420
+    n, cap = 90, 1050
     rng = np.random.default_rng(2)
-    prefix, lens = rng.integers(0, 140, n), np.array(_many(n, 260, 7))
+    prefix, lens = rng.integers(0, 140, n), np.array(_many(n, long, 7))
     oc, gc = O.KVCache(ol, n, cap, fp8_scales=scales), gl.cache(n, cap, fp8_scales=scales)
     for s in range(n):
         k, v = I.kv_fill(2, 140, 128, seed=s, dtype="bf16")
