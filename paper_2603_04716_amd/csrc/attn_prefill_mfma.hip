@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256) void kv_gather_blocked_fp8_kernel(
 
 bool attn_prefill_mfma_supported(const AttnArgs &a)
 {
-    return a.hd == HD && !a.decode && a.ld % 8 == 0 && a.T > 0 && a.Hkv <= kRopeTileMaxHkv &&
+    return a.hd == HD && !a.decode && a.ld % 8 == 0 && a.T > 0 &&
            (int64_t)a.T * a.ld * 2 < (1ll << 31);
 }
 

@@ -378,7 +378,6 @@ struct RopeTiles {
     uint16_t *vt;
     int32_t vt_ld;
 };
-constexpr int kRopeTileMaxHkv = 32767;   // two grid rows per kv head
 bool rope_tile_supported(int dtype, const RopeArgs &a);
 hipError_t launch_rope_tile(const RopeArgs &a, const RopeTiles &t, hipStream_t s);
 hipError_t launch_rope_table(float2 *table, int table_len, int half, const double *inv_freq, hipStream_t s);

@@ -61,8 +61,10 @@ __global__ __launch_bounds__(512) void rope_tile_kernel(RopeArgs a, RopeTiles t,
 {
     __shared__ uint32_t tile32[64 * kTileRow / 2];
     uint16_t *tile = (uint16_t *)tile32;
-    const int tid = threadIdx.x, g = halves ? blockIdx.y >> 1 : blockIdx.y;
-    const bool queries = !halves || !(blockIdx.y & 1), kv = !halves || (blockIdx.y & 1);
+    const int part = blockIdx.y + blockIdx.z * gridDim.y;          // a grid dimension holds 65535
+    const int tid = threadIdx.x, g = halves ? part >> 1 : part;
+    if (g >= a.Hkv) return;
+    const bool queries = !halves || !(part & 1), kv = !halves || (part & 1);
     const int extra = t.prefix ? 2 : 1;
     const int s = per_seq ? (int)blockIdx.x / per_seq : tile_sequence(t, extra, blockIdx.x);
     const int row0 = t.cu[s], L = t.cu[s + 1] - row0, P = t.prefix ? t.prefix[s] : 0;
@@ -206,7 +208,7 @@ __global__ __launch_bounds__(512) void rope_tile_kernel(RopeArgs a, RopeTiles t,
 
 bool rope_tile_supported(int dtype, const RopeArgs &a)
 {
-    return dtype == PD_BF16 && a.hd == 128 && a.ld % 8 == 0 && a.Hkv <= kRopeTileMaxHkv;
+    return dtype == PD_BF16 && a.hd == 128 && a.ld % 8 == 0;
 }
 
 // Tiles are dealt in one grid dimension.  Sequences of similar lengths: the tiles of the longest for each, so that a
@@ -226,7 +228,8 @@ hipError_t launch_rope_tile(const RopeArgs &a, const RopeTiles &t, hipStream_t s
     const unsigned nx = (unsigned)(per_seq ? (long long)per_seq * t.n_seqs : found);
     const bool few_rows = a.T <= 16 * ((a.T >> 6) + (long long)t.n_seqs) && (long long)nx * a.Hkv >= 512;
     const int halves = few_rows ? 0 : 1, nt = few_rows ? 128 : 512;
-    const dim3 grid(nx, (unsigned)((1 + halves) * a.Hkv));
+    const unsigned parts = (unsigned)((1 + halves) * a.Hkv), ny = parts < 65535u ? parts : 65535u;
+    const dim3 grid(nx, ny, (parts + ny - 1) / ny);
     if (a.fp8) rope_tile_kernel<true><<<grid, nt, 0, s>>>(a, t, per_seq, halves);
     else rope_tile_kernel<false><<<grid, nt, 0, s>>>(a, t, per_seq, halves);
     return hipGetLastError();

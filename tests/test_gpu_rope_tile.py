@@ -197,3 +197,26 @@ def test_time_follows_the_rows_not_the_longest_sequence():
     even = rope_ms([1008] * 24)
     assert rope_ms([8192] + [4] * 3999) <= 8 * even
     gl.close()
+
+
+def test_more_kv_heads_than_half_a_grid_dimension():
+    """33000 kv heads, 70 rows behind an empty slot: a chunk (tiled rotation, gather, matrix-core attention) against
+    pd_prefill of the same rows (attention of the plain kernels)."""
+    d, h = 8, 33000
+    cfg = I.small_config(dtype="bf16", d_model=d, n_q_heads=h, n_kv_heads=h, head_dim=128, d_ff=8)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    draw = lambda *s, std: torch.empty(s, device="cuda", dtype=torch.bfloat16).normal_(0.0, std, generator=gen)
+    w = {"g_attn": torch.ones(d, device="cuda", dtype=torch.bfloat16), "w_q": draw(h * 128, d, std=0.3), "w_k": draw(h * 128, d, std=0.3),
+         "w_v": draw(h * 128, d, std=0.3), "w_o": draw(d, h * 128, std=0.001), "g_ffn": torch.ones(d, device="cuda", dtype=torch.bfloat16),
+         "w_gate": draw(8, d, std=0.3), "w_up": draw(8, d, std=0.3), "w_down": draw(d, 8, std=0.3)}
+    torch.cuda.synchronize()
+    layer = pd.pd_layer_create(cfg, w)
+    cache = pd.pd_kv_cache_create(layer, 1, 70)
+    x = draw(70, d, std=1.0)
+    want, got = torch.empty_like(x), torch.empty_like(x)
+    pd.pd_prefill(layer, x, [0, 70], want)
+    pd.pd_prefill_chunk(layer, x, [0, 70], [0], cache, got)
+    torch.cuda.synchronize()
+    assert relmax(to_np(got), to_np(want)) <= TOL["bf16"]
+    pd.pd_kv_cache_destroy(cache)
+    pd.pd_layer_destroy(layer)
