@@ -137,10 +137,12 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GemmArgs a)
     }
 }
 
-// 16-byte operand loads: rows of both operands start on 16 bytes
+// 16-byte operand loads: rows of both operands start on 16 bytes.  Row tiles go over a grid dimension, which holds
+// 65535: with tiles of 32 rows that is half of what the plain form's 64-row tiles reach.
 bool gemm_f32_mfma_supported(const GemmArgs &a)
 {
-    return a.M > 0 && a.N > 0 && a.K >= 4 && a.K % 4 == 0 && a.lda % 4 == 0 && a.ldb % 4 == 0 && a.b_group_stride % 4 == 0 &&
+    const long long row_tiles = ((long long)a.M + 31) / 32 + (a.group_offsets ? a.n_groups : 0);
+    return row_tiles <= 65535 && a.M > 0 && a.N > 0 && a.K >= 4 && a.K % 4 == 0 && a.lda % 4 == 0 && a.ldb % 4 == 0 && a.b_group_stride % 4 == 0 &&
            (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)(a.epilogue == EPI_SWIGLU ? a.B1 : nullptr)) & 15) == 0;
 }
 

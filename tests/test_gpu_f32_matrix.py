@@ -3,6 +3,7 @@ the 16-wide k-step, both tile sizes, every head size with its own form, one and 
 Bound: the fp32 bound of the other parity tests, 1e-5 of the largest element."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2603_04716_amd as pd
 import pd_inputs as I
@@ -85,3 +86,18 @@ def test_prefill_with_keys_of_score_minus_infinity(head_dim, lost):
     cu = np.array([0, 100], np.int32)
     assert relmax(gl.prefill(x, cu), O.prefill(ol, x, cu)) <= TOL["f32"]
     gl.close()
+
+
+def test_product_of_more_rows_than_a_grid_holds_tiles():
+    """2.1 million rows: more 32-row tiles than a grid dimension holds."""
+    T, d, V = 65535 * 32 + 33, 4, 16
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x, w = torch.randn((T, d), device="cuda", generator=gen), torch.randn((V, d), device="cuda", generator=gen)
+    g = torch.ones(d, device="cuda")
+    head = pd.pd_head_create(d, V, 1e-6, "f32", g, w, None, T)
+    got = torch.full((T, V), float("nan"), device="cuda")
+    pd.pd_lm_head(head, x, got)
+    xd = x.double()
+    ref = (xd * torch.rsqrt(xd.square().mean(1, keepdim=True) + 1e-6)) @ w.double().T
+    assert float((got - ref).abs().max() / ref.abs().max()) <= TOL["f32"]
+    pd.pd_head_destroy(head)
