@@ -860,7 +860,8 @@ hipError_t launch_attn_generic(int dtype, const AttnArgs &a, hipStream_t s)
     if (items <= 0) return hipSuccess;
     // 16-byte rows: buffers aligned, row strides whole (head sizes here are multiples of 4 elements)
     if (dtype == PD_F32 && a.ld % 4 == 0 && (((uintptr_t)a.qkv | (uintptr_t)a.o) & 15) == 0) {
-        if (a.decode && (((uintptr_t)a.k_cache | (uintptr_t)a.v_cache) & 15) == 0 && items <= 0x7fffffffll) {
+        // a workgroup per item: a launch is limited to 2^32 - 1 threads, which four items a workgroup reach later
+        if (a.decode && (((uintptr_t)a.k_cache | (uintptr_t)a.v_cache) & 15) == 0 && items <= 0xffffffffll / 256) {
             const unsigned n = (unsigned)items;
             if (a.hd == 32) { attn_decode_f32_kernel<8><<<n, 256, 0, s>>>(a); return hipGetLastError(); }
             if (a.hd == 64) { attn_decode_f32_kernel<16><<<n, 256, 0, s>>>(a); return hipGetLastError(); }

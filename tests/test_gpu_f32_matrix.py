@@ -101,3 +101,19 @@ def test_product_of_more_rows_than_a_grid_holds_tiles():
     ref = (xd * torch.rsqrt(xd.square().mean(1, keepdim=True) + 1e-6)) @ w.double().T
     assert float((got - ref).abs().max() / ref.abs().max()) <= TOL["f32"]
     pd.pd_head_destroy(head)
+
+
+def test_chunk_attention_of_more_items_than_workgroups_fit_a_launch():
+    """4096 chunks of 65 rows with 64 heads: 17.0 million (row, head) items, more than 2^32 threads of a workgroup each.
+    Single sequences of it, fed alone, take the other form."""
+    n, L = 4096, 65
+    cfg = I.small_config(d_model=4, n_q_heads=64, n_kv_heads=1, head_dim=32, d_ff=4)
+    gl = GpuLayer(cfg, I.layer_weights(cfg, std=0.5))
+    x = I.hidden(n * L, 4, seed=9)
+    all_, alone = gl.cache(n, L), gl.cache(1, L)
+    got = gl.prefill_chunk(x, np.arange(0, n * L + 1, L), list(range(n)), all_)
+    for s in (0, 1, 2047, n - 1):
+        rows = slice(s * L, (s + 1) * L)
+        pd.pd_kv_cache_set_len(alone, 0, 0)
+        assert relmax(got[rows], gl.prefill_chunk(x[rows], [0, L], [0], alone)) <= TOL["f32"]
+    gl.close()
