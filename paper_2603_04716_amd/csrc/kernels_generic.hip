@@ -916,6 +916,7 @@ __global__ void kv_copy_kernel(T *ck, T *cv, T *k, T *v, int slot, int Hkv, int 
 // the four position groups of a wave's transposing accesses on different banks and keeps rows
 // 16-byte aligned.
 constexpr int kVtRow = 128 + 8;
+constexpr int kMaxGridHeads = 65535;     // heads go over a grid dimension; more of them take the element-wise form
 
 template <bool TO_CACHE>
 __global__ __launch_bounds__(512) void kv_copy_block_kernel(uint16_t *ck, uint16_t *cv, uint16_t *k, uint16_t *v, int slot,
@@ -978,7 +979,7 @@ hipError_t launch_kv_copy(int dtype, void *cache_k, void *cache_v, const void *k
 {
     size_t n = (size_t)Hkv * len * hd;
     if (n == 0) return hipSuccess;
-    if (blocked && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
+    if (blocked && (((uintptr_t)k | (uintptr_t)v) & 15) == 0 && Hkv <= kMaxGridHeads) {
         const dim3 grid((unsigned)((len + 31) / 32), (unsigned)Hkv, 2);
         auto *kern = to_cache ? kv_copy_block_kernel<true> : kv_copy_block_kernel<false>;
         kern<<<grid, 512, 0, s>>>((uint16_t *)cache_k, (uint16_t *)cache_v, (uint16_t *)k, (uint16_t *)v, slot, Hkv, len, max_len);
@@ -1071,7 +1072,7 @@ hipError_t launch_kv_copy_fp8(void *cache_k, void *cache_v, const void *k, const
 {
     size_t n = (size_t)Hkv * len * 128;
     if (n == 0) return hipSuccess;
-    if (!to_cache && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
+    if (!to_cache && (((uintptr_t)k | (uintptr_t)v) & 15) == 0 && Hkv <= kMaxGridHeads) {
         const dim3 blocks((unsigned)((len + 63) / 64), (unsigned)Hkv, 2);
         kv_read_block_fp8_kernel<<<blocks, 1024, 0, s>>>((const uint8_t *)cache_k, (const uint8_t *)cache_v, (uint16_t *)k, (uint16_t *)v,
                                                         slot, Hkv, len, max_len_pad, k_scale, v_scale);

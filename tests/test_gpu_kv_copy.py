@@ -48,3 +48,22 @@ def test_set_get_blocks(fp8, n, shift):
             torch.cuda.synchronize()
             assert torch.equal(gk, want_k[:, :length]) and torch.equal(gv, want_v[:, :length])
     gl.close()
+
+
+def test_more_heads_than_a_grid_dimension():
+    h = 65537
+    cfg = I.small_config(dtype="bf16", d_model=2, n_q_heads=h, n_kv_heads=h, head_dim=128, d_ff=2)
+    zeros = lambda *s: torch.zeros(s, device="cuda", dtype=torch.bfloat16)
+    layer = pd.pd_layer_create(cfg, {"g_attn": zeros(2), "w_q": zeros(h * 128, 2), "w_k": zeros(h * 128, 2), "w_v": zeros(h * 128, 2),
+                                     "w_o": zeros(2, h * 128), "g_ffn": zeros(2), "w_gate": zeros(2, 2), "w_up": zeros(2, 2),
+                                     "w_down": zeros(2, 2)})
+    cache = pd.pd_kv_cache_create(layer, 1, 3)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    k, v = (torch.randn((h, 3, 128), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    gk, gv = torch.empty_like(k), torch.empty_like(v)
+    pd.pd_kv_cache_set(cache, 0, k, v)
+    pd.pd_kv_cache_get(cache, 0, gk, gv)
+    torch.cuda.synchronize()
+    assert torch.equal(gk, k) and torch.equal(gv, v)
+    pd.pd_kv_cache_destroy(cache)
+    pd.pd_layer_destroy(layer)
