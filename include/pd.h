@@ -189,7 +189,7 @@ pd_status pd_kv_cache_set(pd_kv_cache *cache, int32_t slot, int32_t len, const v
 /* Sets a slot's length without touching its contents (0 <= len <= max_len); used to rewind a
  * cache between timed repetitions of the same decode step.  Enqueued on `stream`. */
 pd_status pd_kv_cache_set_len(pd_kv_cache *cache, int32_t slot, int32_t len, void *stream);
-/* The same for n (slot, len) pairs at once (host arrays). */
+/* The same for n (slot, len) pairs at once (host arrays); a slot listed more than once takes its last length. */
 pd_status pd_kv_cache_set_lens(pd_kv_cache *cache, int32_t n, const int32_t *slots,
                                const int32_t *lens, void *stream);
 /* Reads a slot's length (host-side mirror; no device access). */

@@ -1642,7 +1642,29 @@ extern "C" pd_status pd_kv_cache_set_lens(pd_kv_cache *c, int32_t n, const int32
             return PD_ERR_KV_CAPACITY;
         }
     }
-    HIP_TRY(launch_scatter_ints(c->d_len, slots, lens, n, (hipStream_t)stream), PD_ERR_DEVICE);
+    // A slot that is listed again takes its last entry, as the host's record does: the entries of one launch are stored
+    // in no order, so the earlier ones are left out.
+    std::vector<char> seen((size_t)c->max_seqs, 0);
+    bool repeated = false;
+    for (int i = 0; i < n; ++i) {
+        repeated |= seen[(size_t)slots[i]] != 0;
+        seen[(size_t)slots[i]] = 1;
+    }
+    std::vector<int32_t> last_slots, last_lens;
+    const int32_t *dev_slots = slots, *dev_lens = lens;
+    int dev_n = n;
+    if (repeated) {
+        for (int i = n - 1; i >= 0; --i)
+            if (seen[(size_t)slots[i]]) {
+                seen[(size_t)slots[i]] = 0;
+                last_slots.push_back(slots[i]);
+                last_lens.push_back(lens[i]);
+            }
+        dev_slots = last_slots.data();
+        dev_lens = last_lens.data();
+        dev_n = (int)last_slots.size();
+    }
+    HIP_TRY(launch_scatter_ints(c->d_len, dev_slots, dev_lens, dev_n, (hipStream_t)stream), PD_ERR_DEVICE);
     for (int i = 0; i < n; ++i) c->h_len[(size_t)slots[i]] = lens[i];
     return PD_OK;
 }

@@ -67,3 +67,25 @@ def test_more_heads_than_a_grid_dimension():
     assert torch.equal(gk, k) and torch.equal(gv, v)
     pd.pd_kv_cache_destroy(cache)
     pd.pd_layer_destroy(layer)
+
+
+@pytest.mark.parametrize("n,repeats", [(3, 5), (120, 4), (400, 3), (300, 1)])
+def test_last_length_of_a_repeated_slot_holds(n, repeats):
+    """Lengths set with every slot listed several times, in other orders: the device's lengths, seen in where a step
+    appends, are the host's, the last ones listed."""
+    gl = GpuLayer(CFG, I.layer_weights(CFG, std=0.05))
+    gc = gl.cache(n, 64)
+    rng = torch.Generator().manual_seed(n)
+    slots = [int(s) for _ in range(repeats) for s in torch.randperm(n, generator=rng)]
+    lens = [int(v) for v in torch.randint(0, 64, (len(slots),), generator=rng)]
+    pd.pd_kv_cache_set_lens(gc, slots, lens)
+    want = dict(zip(slots, lens))
+    assert all(pd.pd_kv_cache_len(gc, s) == want[s] for s in range(n))
+    x = torch.randn((n, CFG["d_model"]), device="cuda").to(torch.bfloat16)
+    pd.pd_decode_step(gl.h, x, list(range(n)), gc, torch.empty_like(x))
+    for s in range(n):
+        k = torch.empty((2, 64, 128), dtype=torch.bfloat16, device="cuda")
+        pd.pd_kv_cache_get(gc, s, k, torch.empty_like(k))
+        filled = (k != 0).any(2).any(0).nonzero().flatten().tolist()        # a new cache is zero
+        assert filled == [want[s]]
+    gl.close()
