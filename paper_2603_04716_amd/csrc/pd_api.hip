@@ -906,11 +906,11 @@ static pd_status run_tail(pd_layer *L, const void *x, int T, const void *router_
     return PD_OK;
 }
 
-// Shared body of pd_prefill (chunk = false: positions from 0, a cache slot is overwritten) and
-// pd_prefill_chunk (chunk = true: positions behind the slot's cached prefix, appended).
-// At least `need` bytes of attention scratch; where it has to grow, up to `ahead` bytes if those are at most 256 MiB
-// more and can be had.  A prompt fed in chunks needs a little more with every chunk, and each growth waits for the
-// device, frees and allocates: the first 4096-token prompt of a layer in chunks of 512 took 5140 us that way, 3000 us now (later ones 2710).
+// At least `need` bytes of attention scratch.  Where it has to grow it takes more, towards `ahead` bytes, if they can
+// be had: a prompt fed in chunks needs a little more with every chunk, and each growth waits for the device, frees and
+// allocates.  At most as much again as the call needs and at most 64 MiB: every layer holds its own scratch, and what
+// is taken ahead is missing from caches and layers made later.  The first prompt of a layer (8B shape), us, grown call
+// by call -> this way (later prompts): 4096 tokens in chunks of 512 5210 -> 3430 (2970), 8192 11530 -> 6650 (6050).
 static pd_status reserve_attn_scratch(pd_layer *L, size_t need, size_t ahead, const char *who)
 {
     if (need <= L->vt_cap) return PD_OK;
@@ -918,7 +918,7 @@ static pd_status reserve_attn_scratch(pd_layer *L, size_t need, size_t ahead, co
     if (L->vt) (void)hipFree(L->vt);
     L->vt = nullptr;
     L->vt_cap = 0;
-    size_t bytes = std::max(need, std::min(ahead, need + ((size_t)256 << 20)));
+    size_t bytes = std::max(need, std::min(ahead, need + std::min(need, (size_t)64 << 20)));
     hipError_t e = hipMalloc(&L->vt, bytes);
     if (e != hipSuccess && bytes > need) {
         (void)hipGetLastError();
@@ -934,6 +934,8 @@ static pd_status reserve_attn_scratch(pd_layer *L, size_t need, size_t ahead, co
     return PD_OK;
 }
 
+// Shared body of pd_prefill (chunk = false: positions from 0, a cache slot is overwritten) and
+// pd_prefill_chunk (chunk = true: positions behind the slot's cached prefix, appended).
 static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *cache, void *out,
                                 void *stream, bool chunk)
 {

@@ -235,3 +235,39 @@ def test_bf16_multi_token_decode_of_many_sequences(n_seqs, q):
     got = gl.decode(xn, slots, gc)
     assert relmax(got, ref) <= TOL["bf16"]
     gl.close()
+
+
+def _used_by(call):
+    """Device bytes that a call takes and keeps (the library allocates from the driver, in pages of 2 MiB)."""
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    call()
+    torch.cuda.synchronize()
+    return before - torch.cuda.mem_get_info()[0]
+
+
+def test_scratch_taken_ahead_is_bounded():
+    """A chunk's attention scratch grows ahead of the prompt, to at most twice what the call needs and by at most 64 MiB,
+    also where the slots could hold far more; chunks that fit the scratch take nothing."""
+    cfg = I.small_config(dtype="bf16", d_model=256, n_q_heads=16, n_kv_heads=8, head_dim=128, d_ff=512)
+    d = cfg["d_model"]
+    gl = GpuLayer(cfg, I.layer_weights(cfg, std=0.05))
+    gc = gl.cache(1, 131072)
+    pd.pd_layer_reserve(gl.h, 4096)
+    x = torch.zeros((4096, d), dtype=torch.bfloat16, device="cuda")
+    y = torch.empty_like(x)
+
+    def chunk(at, n):
+        pd.pd_kv_cache_set_len(gc, 0, at)
+        pd.pd_prefill_chunk(gl.h, x[:n], [0, n], [0], gc, y[:n])
+
+    per_key = 2 * 8 * 128 * 2                        # gathered keys and transposed values, and nothing else: no split
+    page = 2 << 20
+    first = _used_by(lambda: chunk(0, 4096))         # also loads kernels: only its upper bound is meant
+    assert first <= 2 * 4096 * per_key + 32 * page
+    assert _used_by(lambda: chunk(4096 - 2048, 4096)) == 0
+    need = 65536 * per_key                           # 256 MiB: 64 more are taken
+    grown = _used_by(lambda: chunk(65536 - 4096, 4096))
+    assert grown <= need + (64 << 20) - 4096 * per_key + 2 * page
+    assert _used_by(lambda: chunk(65536, 4096)) == 0
+    gl.close()
