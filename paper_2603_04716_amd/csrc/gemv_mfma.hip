@@ -33,7 +33,9 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // shapes: the SwiGLU pair streams fastest with 2 waves x 16 blocks, a long K (the down projection) with 8 waves x 4,
 // the short square ones with 4 x 8.  8-bit blocks hold two k-steps: half as many for the pair and for QKV (9.3 us either
 // way, 14 rows 11.7 -> 13.0 with eight), but as many for the residual products, whose waves otherwise make twice the
-// round trips: 5 rows down 16.7 -> 13.3, O 7.3 -> 6.5 us; 14 rows 18.4 -> 19.1, 8.1 -> 7.8.
+// round trips, the long K only up to 8 rows: beyond, the row operands of a deeper batch cost more than the trips save.
+// Half as many -> as many: down 1 row 13.3 -> 12.6 us, 5 13.3 -> 12.5, 8 14.2 -> 14.3, 12 16.5 -> 16.7, 16 18.8 -> 19.1;
+// O 1 row 7.8 -> 7.4, 8 8.2 -> 8.1, 16 9.3 -> 9.2.
 __device__ __forceinline__ bf16x8 w8_to_bf16(unsigned w0, unsigned w1)
 {
     auto f0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w0, false);
@@ -231,7 +233,8 @@ static void launch_gemv_t(const GemmArgs &a, hipStream_t s)
         else gemv_mfma_kernel<EPI_NONE, 4, UN, W8><<<grid, 256, 0, s>>>(a);
         break;
     case EPI_RESIDUAL:
-        if (long_k) gemv_mfma_kernel<EPI_RESIDUAL, 8, 4, W8><<<grid, 512, 0, s>>>(a);
+        if (long_k && W8 && a.M > 8) gemv_mfma_kernel<EPI_RESIDUAL, 8, 2, W8><<<grid, 512, 0, s>>>(a);
+        else if (long_k) gemv_mfma_kernel<EPI_RESIDUAL, 8, 4, W8><<<grid, 512, 0, s>>>(a);
         else gemv_mfma_kernel<EPI_RESIDUAL, 4, 8, W8><<<grid, 256, 0, s>>>(a);
         break;
     default: gemv_mfma_kernel<EPI_SWIGLU, 2, UG, W8><<<grid, 128, 0, s>>>(a); break;

@@ -9,7 +9,7 @@ from gpu_util import GpuLayer, TOL, relmax
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B", [1, 16])
+@pytest.mark.parametrize("B", [1, 8, 9, 16])
 @pytest.mark.parametrize("d_model,d_ff", [(64, 64), (192, 320), (256, 2048), (256, 2112), (576, 3200), (256, 8192), (256, 8256), (192, 9024)])
 def test_products(d_model, d_ff, B):
     """The down projection's K is d_ff (from 8192 on over eight waves), QKV's and gate / up's d_model."""
