@@ -680,6 +680,32 @@ static TilePlan plan_tiles(const GemmArgs &a)
     return best;
 }
 
+// The plan of a product of more than 256 rows, for tests that state which form their sizes take (host only; not part of
+// the C ABI): n_groups 0 for a dense product, scratch_elems floats for partials, fused_norm where a split's sum would
+// carry the norm behind it; codes count K in pairs.  form: in the order of TileForm.
+extern "C" void pd_internal_tile_plan(int M, int N, int K, int epilogue, int n_groups, long long scratch_elems, int fused_norm,
+                                      int *form, int *splits)
+{
+    static const int32_t some_offsets = 0;
+    static float some_scratch;
+    static char some_row;
+    GemmArgs a;
+    memset(&a, 0, sizeof(a));
+    a.M = M; a.N = N; a.K = K; a.ldc = N; a.ldr = N; a.epilogue = epilogue;
+    if (n_groups > 0) {
+        a.n_groups = n_groups;
+        a.group_offsets = &some_offsets;
+    }
+    if (scratch_elems > 0) {
+        a.splitk_ws = &some_scratch;
+        a.splitk_ws_elems = (size_t)scratch_elems;
+    }
+    if (fused_norm) a.fuse_y = &some_row;
+    const TilePlan p = plan_tiles(a);
+    *form = p.form;
+    *splits = p.splits;
+}
+
 // 8-bit operands (see the kernel): a.A are E4M3 codes [M, 2 K] with a.a_scale per row, a.B the codes in
 // the pack of the halved view with a.b_scale per packed row; a.K, a.lda, a.ldb count code pairs.
 bool gemm_mfma_f8_supported(const GemmArgs &a)

@@ -10,7 +10,7 @@ import paper_2603_04716_amd as pd
 import pd_inputs as I
 from oracle import layer as O
 from paper_2603_04716_amd import harness as H
-from gpu_util import TOL, relmax, to_np
+from gpu_util import TOL, layer_plans, relmax, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -61,6 +61,26 @@ def test_llama8b_prefill_8192_tokens_sampled_rows(llama, l_in):
     got2 = to_np(out)
     assert np.array_equal(got2[l_in:2 * l_in], got2[:l_in])
     assert np.array_equal(got2[:l_in], got[:l_in])
+
+
+@pytest.mark.parametrize("rows,forms", [(300, ["192/split", "pair/split", "192", "192/split"]), (512, ["deep", "deep/split", "256", "256/split"])])
+def test_llama8b_prefill_of_a_few_hundred_rows(llama, rows, forms):
+    """K splits of the wide tile forms, which only large products take: forms of QKV, O (its sum carries the norm),
+    gate / up and down.  One sampled row per 16-row block and both ends."""
+    cfg, w, layer = llama
+    assert layer_plans(cfg, rows) == forms
+    x = I.hidden(rows, cfg["d_model"], seed=12, dtype="bf16")
+    cu = np.array([0, 100, rows], np.int32)
+    xd = H._dev(x, "bf16")
+    out = torch.empty_like(xd)
+    pd.pd_prefill(layer.h, xd, cu, out)
+    torch.cuda.synchronize()
+    got = to_np(out)
+    sample = sorted(set(tile_rows(rows, 100, seed=rows, tile=16)))
+    ref = O.prefill(O.Layer(cfg, w), x, cu, rows=sample)
+    assert relmax(got[sample], ref) <= TOL["bf16"]
+    for i, r in enumerate(sample):
+        assert relmax(got[r], ref[i]) <= 2 * TOL["bf16"], r
 
 
 @pytest.mark.parametrize("B", [256, 8])

@@ -5,15 +5,20 @@ import pytest
 
 import pd_inputs as I
 from oracle import layer as O
-from gpu_util import GpuLayer, TOL, relmax
+from gpu_util import GpuLayer, TOL, relmax, tile_plan
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,d_ff", [(12, 1024), (64, 2048), (700, 1024), (2500, 512)])
+@pytest.mark.parametrize("T,d_ff,form", [(12, 1024, None), (64, 2048, None), (700, 1024, None), (2500, 512, "pair"), (2500, 1024, "192"),
+                                         (1450, 2048, "256"), (1510, 256, "deep")])
 @pytest.mark.parametrize("skew", ["even", "two", "ragged"])
-def test_grouped_products_deal_the_tiles_in_use(T, d_ff, skew):
-    """Expert loads from even to two experts with all rows: the tiles in use are from all to few of those launched."""
+def test_grouped_products_deal_the_tiles_in_use(T, d_ff, form, skew):
+    """Expert loads from even to two experts with all rows: the tiles in use are from all to few of those launched.
+    form: of the gate / up product, where an expert has more than 256 rows on the average (its loads are not known on
+    the host, so the forms are the same for every skew)."""
+    if form:
+        assert tile_plan(2 * T, d_ff, 256, 2, 8) == form
     cfg = I.small_config(dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=d_ff, n_experts=8, top_k=2)
     w = I.layer_weights(cfg, std=0.05)
     ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)

@@ -1,5 +1,8 @@
-"""Products of more than 256 rows: the sizes here take each tile form (256, 192, 128 in pairs, 128 deep) and
-each with and without a K split, with ragged last row and column tiles, one row over a tile, and all epilogues."""
+"""Products of more than 256 rows: every tile form, with the form that a size takes stated and asserted, ragged last
+row and column tiles, one row over a tile.  Codes (plain store): all four forms, with and without a K split.  bf16,
+plain store (head products, which have no scratch to split with): all four forms.  bf16 and codes, SwiGLU and residual
+epilogues: the forms of test_layer_epilogues; splits of the wide forms in bf16 layers are with the full-shape tests,
+grouped products with the mixture-of-experts tests."""
 import numpy as np
 import pytest
 import torch
@@ -7,15 +10,18 @@ import torch
 import paper_2603_04716_amd as pd
 import pd_inputs as I
 from oracle import layer as O
-from gpu_util import GpuLayer, TOL, relmax, to_dev, to_np
+from gpu_util import GpuLayer, TOL, layer_plans, relmax, tile_plan, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,K", [(257, 1040, 1536), (300, 28672, 256), (771, 6144, 256), (513, 528, 2048), (512, 28672, 256),
-                                   (1000, 4096, 1536), (770, 4112, 3072), (385, 272, 14336)])
-def test_codes_product(M, N, K):
-    """Bound: one rounding to bf16 and the order of the fp32 sums, 2^-8 of the row's largest output."""
+@pytest.mark.parametrize("M,N,K,form", [(257, 1040, 1536, "pair"), (300, 28672, 256, "192"), (771, 6144, 256, "pair"),
+                                        (513, 528, 2048, "pair"), (512, 28672, 256, "256"), (1000, 4096, 1536, "deep"),
+                                        (770, 4112, 3072, "deep"), (385, 272, 14336, "pair/split"), (257, 4096, 12288, "192/split"),
+                                        (385, 6144, 8192, "256/split"), (257, 528, 6144, "deep/split")])
+def test_codes_product(M, N, K, form):
+    """Bound: one rounding to bf16, 2^-9 of an element, and the order of the fp32 sums; 2^-8 of the row's largest output."""
+    assert tile_plan(M, N, K // 2, scratch=8 * 256 * N + M * N) == form
     rng = np.random.default_rng(M + N)
     a, b = (rng.integers(0, 256, s, dtype=np.uint8) & 0xB7 for s in ((M, K), (N, K)))
     sa = (2.0 ** rng.integers(-6, 2, M)).astype(np.float32)
@@ -26,11 +32,13 @@ def test_codes_product(M, N, K):
     got = out.float().cpu().numpy()
     rows = np.unique(np.r_[0, M - 1, M // 2, 255, 256, rng.choice(M, 12)])
     ref = O.gemm_e4m3(a[rows], sa[rows], b, sb)
-    assert max(relmax(got[r], ref[j]) for j, r in enumerate(rows)) <= 2.0 ** -7
+    assert max(relmax(got[r], ref[j]) for j, r in enumerate(rows)) <= 2.0 ** -8
 
 
-@pytest.mark.parametrize("T,d,V", [(257, 1536, 1040), (771, 256, 6144), (513, 2048, 528), (300, 256, 28672), (700, 256, 12304)])
-def test_bf16_product(T, d, V):
+@pytest.mark.parametrize("T,d,V,form", [(257, 1536, 1040, "pair"), (771, 256, 6144, "pair"), (513, 2048, 528, "pair"), (300, 256, 28672, "192"),
+                                        (700, 256, 12304, "192"), (257, 256, 5120, "deep"), (771, 256, 14336, "256")])
+def test_bf16_product(T, d, V, form):
+    assert tile_plan(T, V, d) == form
     hw = I.head_weights(d, V, seed=d + V, dtype="bf16", std=0.05)
     dev = {k: to_dev(v, "bf16") for k, v in hw.items()}
     h = pd.pd_head_create(d, V, 1e-6, "bf16", dev["g_final"], dev["w_lm"], None, T)
@@ -46,11 +54,16 @@ def test_bf16_product(T, d, V):
 
 
 @pytest.mark.parametrize("a8", [False, True])
-@pytest.mark.parametrize("rows", [257, 300, 385, 513])
-def test_layer_epilogues(a8, rows):
-    """A wide FFN (28672 gate / up columns) beside narrow products: SwiGLU and residual epilogues of the forms; the
-    bound with 8-bit activations is the one derived for the layer (6e-2)."""
-    cfg = I.small_config(dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=14336)
+@pytest.mark.parametrize("d,d_ff,rows,forms", [
+    (256, 14336, 257, ["pair", "pair", "192", "pair/split"]), (256, 14336, 300, ["pair", "pair", "192", "pair/split"]),
+    (256, 14336, 385, ["pair", "pair", "256", "pair/split"]), (256, 14336, 513, ["pair", "pair", "pair", "pair/split"]),
+    (1536, 256, 257, ["pair/split", "pair", "pair/split", "pair"]), (1536, 640, 300, ["pair/split", "pair", "deep/split", "pair"])])
+def test_layer_epilogues(a8, d, d_ff, rows, forms):
+    """Forms of QKV, O, gate / up (SwiGLU) and down (residual).  A wide FFN (28672 gate / up columns) beside narrow
+    products, and a long K; the bound with 8-bit activations is the one derived for the layer (6e-2)."""
+    cfg = I.small_config(dtype="bf16", d_model=d, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=d_ff)
+    if d == 256 or not a8:
+        assert layer_plans(cfg, rows, a8) == forms
     w = I.layer_weights(cfg, std=0.05)
     ol, gl = O.Layer(cfg, O.quantise_layer_weights(w) if a8 else w), GpuLayer(cfg, w, a8=a8)
     x = I.hidden(rows, cfg["d_model"], seed=rows, dtype="bf16")
