@@ -46,11 +46,23 @@ def test_new_token_codes(B, scales):
     gl.close()
 
 
-@pytest.mark.parametrize("B,a8", [(256, True), (257, False), (257, True), (480, True), (481, False), (960, True), (961, False)])
+def _positions(gc, B):
+    """The 8 positions of every slot, keys and values: bit patterns [slot, 2, head, position, 128]."""
+    out = torch.empty((B, 2, 2, 8, 128), dtype=torch.bfloat16, device="cuda")
+    for s in range(B):
+        pd.pd_kv_cache_get(gc, s, out[s, 0], out[s, 1])
+    torch.cuda.synchronize()
+    return out.view(torch.int16)
+
+
+@pytest.mark.parametrize("B,a8", [(256, True), (257, False), (257, True), (480, False), (480, True), (481, False), (960, False),
+                                  (960, True), (961, False)])
 def test_batches_at_the_limits_of_a_launch(B, a8):
-    """Lengths set for all slots at once, then a step: every row reads its own slot at its own length.  8-bit activations
-    (more than 256 rows): the bound derived for the layer, 6e-2."""
+    """Lengths set for all slots at once, then two steps: every row reads its own slot at its own length and is stored at
+    that position and nowhere else.  Bound where activations are held in 8 bits (more than 256 rows): the one derived
+    for the layer, 6e-2."""
     scales = (0.5, 0.125)
+    act8 = a8 and B > 256
     w = I.layer_weights(CFG, std=0.05)
     ol, gl = O.Layer(CFG, O.quantise_layer_weights(w) if a8 else w), GpuLayer(CFG, w, a8=a8)
     rng = np.random.default_rng(B)
@@ -61,10 +73,85 @@ def test_batches_at_the_limits_of_a_launch(B, a8):
         oc.set(i, k, v)
         pd.pd_kv_cache_set(gc, i, to_dev(k, "bf16"), to_dev(v, "bf16"))
         oc.lens[i] = lens[i]
-    slots = rng.permutation(B)
-    pd.pd_kv_cache_set_lens(gc, [int(s) for s in slots], [int(lens[s]) for s in slots])
-    x = I.hidden(B, CFG["d_model"], seed=3, dtype="bf16")
-    ref = O.decode_step(ol, x, [int(s) for s in slots], oc, act8=a8 and B > 256)
-    got = gl.decode(x, [int(s) for s in slots], gc)
-    assert max(relmax(got[i], ref[i]) for i in range(B)) <= (2 * 6e-2 if a8 else 2 * TOL["bf16"])
+    slots = [int(s) for s in rng.permutation(B)]
+    pd.pd_kv_cache_set_lens(gc, slots, [int(lens[s]) for s in slots])
+    before = _positions(gc, B)
+    new = torch.zeros((B, 8), dtype=torch.bool)
+    for step in range(2):
+        x = I.hidden(B, CFG["d_model"], seed=3 + step, dtype="bf16")
+        ref, got = O.decode_step(ol, x, slots, oc, act8=act8), gl.decode(x, slots, gc)
+        assert max(relmax(got[i], ref[i]) for i in range(B)) <= (6e-2 if act8 else 2 * TOL["bf16"])
+        new[torch.arange(B), torch.from_numpy(lens).long() + step] = True
+        assert [pd.pd_kv_cache_len(gc, s) for s in range(B)] == [int(n) + step + 1 for n in lens]
+        assert torch.equal((_positions(gc, B) != before).any(4).any(2).any(1).cpu(), new)
+    gl.close()
+
+
+@pytest.mark.parametrize("scales", [(0.5, 0.125), (2.0 ** -9, 4.0), (0.75, 0.0625)])
+def test_every_bf16_value_gets_the_same_code_on_every_way_in(scales):
+    """What a prefill, a chunk of a few rows and a decode step store reads back as exactly the value that pd_kv_cache_set
+    stores (double-precision conversion, compared with the oracle elsewhere), for every finite bf16 value (the sign of
+    zero aside: it is lost in a sum).  The inputs are unit vectors whose normalised rows are unit vectors again, so key
+    and value of token j are column j of the projections; position 0 does not rotate them."""
+    d, hkv = 64, 8
+    cfg = I.small_config(dtype="bf16", d_model=d, n_q_heads=8, n_kv_heads=hkv, head_dim=128, d_ff=64, rms_eps=0.0)
+    bits = np.arange(65536, dtype=np.uint32)
+    cols = (bits << 16).view(np.float32).reshape(hkv * 128, d).copy()    # [channel, token]
+    cols[~np.isfinite(cols)] = 0.0
+    w = I.layer_weights(cfg, std=0.05)
+    w["w_k"] = w["w_v"] = cols
+    w["g_attn"] = np.full(d, 0.125, np.float32)                          # rms of a unit vector: 1 / 8
+    gl = GpuLayer(cfg, w)
+    x = np.eye(d, dtype=np.float32)
+    k = cols.reshape(hkv, 128, d).transpose(2, 0, 1)                     # [token, head, channel]
+    slots = list(range(d))
+
+    def stored(fill):
+        gc = gl.cache(d, 64, fp8_scales=scales)
+        fill(gc)
+        out = torch.empty((d, 2, hkv, 1, 128), dtype=torch.bfloat16, device="cuda")
+        for s in slots:
+            pd.pd_kv_cache_get(gc, s, out[s, 0], out[s, 1])
+        torch.cuda.synchronize()
+        return out
+
+    def by_set(gc):
+        for s in slots:
+            t = to_dev(k[s].reshape(hkv, 1, 128), "bf16")
+            pd.pd_kv_cache_set(gc, s, t, t)
+
+    want = stored(by_set)
+    cu = np.arange(d + 1, dtype=np.int32)
+    assert torch.equal(stored(lambda gc: gl.prefill(x, cu, gc, slots)), want)
+    assert torch.equal(stored(lambda gc: gl.prefill_chunk(x, cu, slots, gc)), want)
+    assert torch.equal(stored(lambda gc: gl.decode(x, slots, gc)), want)
+
+    # values of one sequence of 64 tokens: whole runs of the transposed value blocks
+    gc, kv = gl.cache(1, 64, fp8_scales=scales), torch.empty((2, hkv, d, 128), dtype=torch.bfloat16, device="cuda")
+    gl.prefill(x, np.array([0, d], np.int32), gc, [0])
+    pd.pd_kv_cache_get(gc, 0, kv[0], kv[1])
+    torch.cuda.synchronize()
+    assert torch.equal(kv[1], want[:, 1, :, 0].transpose(0, 1))
+    gl.close()
+
+
+@pytest.mark.parametrize("scales", [(0.5, 0.125), (0.75, 0.0625)])
+def test_codes_of_values_that_are_not_finite(scales):
+    """Infinities are held as the largest code of their sign, NaN as NaN, on the same three ways in."""
+    d = 64
+    cfg = I.small_config(dtype="bf16", d_model=d, n_q_heads=1, n_kv_heads=1, head_dim=128, d_ff=64, rms_eps=0.0)
+    w = I.layer_weights(cfg, std=0.05)
+    w["w_v"][:3, 0] = np.inf, -np.inf, np.nan
+    w["g_attn"] = np.full(d, 0.125, np.float32)
+    gl = GpuLayer(cfg, w)
+    x = np.eye(d, dtype=np.float32)[:1]
+    one = np.array([0, 1], np.int32)
+    for fill in (lambda gc: gl.prefill(x, one, gc, [0]), lambda gc: gl.prefill_chunk(x, one, [0], gc), lambda gc: gl.decode(x, [0], gc)):
+        gc = gl.cache(1, 64, fp8_scales=scales)
+        fill(gc)
+        kv = torch.empty((2, 1, 1, 128), dtype=torch.bfloat16, device="cuda")
+        pd.pd_kv_cache_get(gc, 0, kv[0], kv[1])
+        torch.cuda.synchronize()
+        v = to_np(kv[1])[0, 0]
+        assert v[0] == 448 * scales[1] and v[1] == -448 * scales[1] and np.isnan(v[2]) and np.isfinite(v[3:]).all()
     gl.close()
