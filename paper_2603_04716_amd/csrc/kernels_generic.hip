@@ -854,14 +854,60 @@ __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(AttnArgs a)
             *(f32x4 *)(orow + 64 * b + 4 * r) = f32x4{o[b][0][r], o[b][1][r], o[b][2][r], o[b][3][r]} * inv;
 }
 
+// Which form of the fp32 attention over a cache: a few items leave the chip idle and wait for memory, where splitting
+// an item over four waves pays from some ten keys on; many items fill it, and then a workgroup per item costs 4 (head
+// size 32) to 11 (256) times as much to start as a wave, which only long rows repay - and rows that share their keys,
+// by neighbours in a sequence or heads of a group, hardly at head size 128.  Wave per item -> split, us: 16 rows x 4 heads
+// of 64, 200 keys 45 -> 9; 256 x 16 heads of 128, 1000 keys 1044 -> 695; 4096 rows x 16 heads of 128, 5 keys 139 -> 813;
+// 2048 rows of one sequence x 16 heads of 128 2782 -> 4059.
+// Either form's time is taken as sqrt(wait^2 + busy^2), wait = w0 + w1 x longest row (us), busy = items x (b0 + b1 x
+// mean row) (ns), with numbers fitted to the choice, not to the times: over 1110 launches of 4 ... 65536 items and 1 ...
+// 2100 keys, equal and ragged, the chosen form takes 0.4 % longer than the faster one on the average; 18 are more than
+// 10 % off, the worst 1.5 times (256 rows of 1 ... 61 keys, head size 256: 56 us, a wave per item 38).
+struct AttnCost {
+    double w0, w1, b0, b1_shared, b1;
+};
+static double attn_cost(const AttnCost &c, double items, double mean_keys, double max_keys, bool shared)
+{
+    const double wait = c.w0 + c.w1 * max_keys, busy = items * (c.b0 + (shared ? c.b1_shared : c.b1) * mean_keys) * 1e-3;
+    return sqrt(wait * wait + busy * busy);
+}
+static bool attn_decode_split_pays(const AttnArgs &a)
+{
+    static const struct {
+        int hd;
+        AttnCost wave, split;
+    } forms[] = {{32, {2.16, 0.427, 0.4, 0.109, 0.13}, {4.95, 0.00576, 5.33, 0.0192, 0.0255}},
+                 {64, {2.16, 0.511, 0.549, 0.144, 0.292}, {4.04, 0.0128, 10.9, 0.0239, 0.0493}},
+                 {128, {2.77, 1.29, 1.1, 0.0574, 0.328}, {11.5, 0.0234, 21.1, 0.136, 0.128}},
+                 {256, {3.38, 2.11, 1.83, 0.2, 0.657}, {16.1, 0.0493, 80.0, 0.191, 0.169}}};
+    const double items = (double)a.T * a.Hq;
+    const bool shared = a.rows_share || a.Hq > a.Hkv;
+    for (const auto &f : forms)
+        if (f.hd == a.hd)
+            return attn_cost(f.split, items, a.mean_keys, a.max_keys, shared) < attn_cost(f.wave, items, a.mean_keys, a.max_keys, shared);
+    return false;
+}
+// for tests that state which form their sizes take (host only; not part of the C ABI)
+extern "C" int pd_internal_attn_split_pays(int head_dim, int rows, int n_q_heads, int n_kv_heads, double mean_keys, int max_keys,
+                                           int rows_share)
+{
+    AttnArgs a;
+    memset(&a, 0, sizeof(a));
+    a.hd = head_dim; a.T = rows; a.Hq = n_q_heads; a.Hkv = n_kv_heads;
+    a.mean_keys = mean_keys; a.max_keys = max_keys; a.rows_share = rows_share;
+    return attn_decode_split_pays(a) ? 1 : 0;
+}
+
 hipError_t launch_attn_generic(int dtype, const AttnArgs &a, hipStream_t s)
 {
     long long items = (long long)a.T * a.Hq;
     if (items <= 0) return hipSuccess;
-    // 16-byte rows: buffers aligned, row strides whole (head sizes here are multiples of 4 elements)
+    // 16-byte rows: buffers aligned, row strides whole (head sizes of the vector forms are multiples of 4 elements)
     if (dtype == PD_F32 && a.ld % 4 == 0 && (((uintptr_t)a.qkv | (uintptr_t)a.o) & 15) == 0) {
         // a workgroup per item: a launch is limited to 2^32 - 1 threads, which four items a workgroup reach later
-        if (a.decode && (((uintptr_t)a.k_cache | (uintptr_t)a.v_cache) & 15) == 0 && items <= 0xffffffffll / 256) {
+        if (a.decode && (((uintptr_t)a.k_cache | (uintptr_t)a.v_cache) & 15) == 0 && items <= 0xffffffffll / 256 &&
+            attn_decode_split_pays(a)) {
             const unsigned n = (unsigned)items;
             if (a.hd == 32) { attn_decode_f32_kernel<8><<<n, 256, 0, s>>>(a); return hipGetLastError(); }
             if (a.hd == 64) { attn_decode_f32_kernel<16><<<n, 256, 0, s>>>(a); return hipGetLastError(); }

@@ -1030,6 +1030,12 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
     a.qkv = L->qkv; a.ld = L->Nqkv; a.o = L->o; a.T = T; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads;
     a.hd = c.head_dim; a.scale = (float)(1.0 / sqrt((double)c.head_dim)); a.tok_pos = L->tok_pos;
     a.decode = 0; a.d_cu = L->d_cu; a.n_seqs = n; a.max_seq_len = max_L;
+    for (int q = 0; q < n; ++q) {
+        const int Ls = tk->cu_seqlens[q + 1] - tk->cu_seqlens[q];
+        a.mean_keys += (double)Ls * (prefix[(size_t)q] + 0.5 * (Ls + 1)) / T;
+        if (Ls > 0) a.max_keys = std::max(a.max_keys, prefix[(size_t)q] + Ls);
+    }
+    a.rows_share = 1;
     const bool short_chunk = chunk && cache->blocked && max_L <= kShortChunk;
     const bool tile_attn = chunk ? cache->blocked && !short_chunk : L->use_mfma && attn_prefill_mfma_supported(a);
     const int vt_ld = pad[(size_t)n];
@@ -1386,6 +1392,11 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
         a.hd = c.head_dim; a.scale = (float)(1.0 / sqrt((double)c.head_dim)); a.tok_pos = L->tok_pos;
         a.tok_slot = L->d_slots; a.k_cache = cache->k; a.v_cache = cache->v; a.max_len = cache->max_len;
         a.decode = 1;
+        for (int b = 0; b < B; ++b) {
+            const int keys = cache->h_len[(size_t)bt->slots[b]] + 1;
+            a.mean_keys += (double)keys / B;
+            a.max_keys = std::max(a.max_keys, keys);
+        }
         STEP("decode_attention", launch_attn_generic(c.dtype, a, s));
     }
     st = run_tail(L, bt->hidden, B, bt->router_logits, out, s, mfma_dec && fused_rope ? &r : nullptr);

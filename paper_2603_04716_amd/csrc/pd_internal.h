@@ -415,6 +415,10 @@ struct AttnArgs {
     // chunked prefill source is the 8-bit E4M3 blocked cache: gathered values are code * scale
     int32_t kv_fp8;
     float k_scale, v_scale;
+    // for the choice of a form (launch_attn_generic): keys that a row sees on the average and at most, and whether
+    // rows next to each other read the same keys (several rows of a sequence)
+    double mean_keys;
+    int32_t max_keys, rows_share;
 };
 hipError_t launch_attn_generic(int dtype, const AttnArgs &a, hipStream_t s);
 bool attn_prefill_mfma_supported(const AttnArgs &a);

@@ -1,6 +1,8 @@
 """fp32 layers on the fp32 matrix instructions and the split attention: tile edges, K that is not a multiple of
 the 16-wide k-step, both tile sizes, every head size with its own form, one and four waves per attention row.
 Bound: the fp32 bound of the other parity tests, 1e-5 of the largest element."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -116,4 +118,36 @@ def test_chunk_attention_of_more_items_than_workgroups_fit_a_launch():
         rows = slice(s * L, (s + 1) * L)
         pd.pd_kv_cache_set_len(alone, 0, 0)
         assert relmax(got[rows], gl.prefill_chunk(x[rows], [0, L], [0], alone)) <= TOL["f32"]
+    gl.close()
+
+
+def _split(hd, rows, hq, hkv, mean, longest, share=0):
+    return bool(pd.lib.pd_internal_attn_split_pays(hd, rows, hq, hkv, C.c_double(mean), longest, share))
+
+
+def test_split_attention_where_it_pays():
+    """Sizes on both sides, each measured with both forms: a wave per item for many items with few keys or shared ones."""
+    assert _split(64, 4, 4, 4, 100, 100) and _split(64, 16, 4, 4, 200, 200) and _split(128, 256, 16, 4, 1000, 1000)
+    assert _split(256, 256, 4, 4, 200, 200) and _split(32, 4096, 8, 2, 200, 200) and _split(64, 2048, 4, 4, 1024.5, 2048, 1)
+    assert not _split(64, 4096, 4, 4, 6, 6) and not _split(128, 256, 16, 4, 31, 31) and not _split(256, 1024, 4, 1, 65, 65)
+    assert not _split(128, 2048, 16, 4, 1024.5, 2048, 1) and not _split(32, 1024, 8, 2, 2, 2) and not _split(64, 1, 4, 4, 2, 2)
+
+
+@pytest.mark.parametrize("head_dim", [32, 64, 128, 256])
+@pytest.mark.parametrize("B,keys,split", [(1, 2, False), (1, 400, True), (700, 3, False), (40, 130, True)])
+def test_decode_on_both_sides_of_the_choice(head_dim, B, keys, split):
+    """Ragged lengths up to `keys`; sampled rows where there are many."""
+    cfg = I.small_config(d_model=64, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=64)
+    lens = np.random.default_rng(B).integers(max(1, keys // 2), keys, B)
+    assert _split(head_dim, B, 4, 2, float(lens.mean()) + 1, int(lens.max()) + 1) == split
+    w = I.layer_weights(cfg, std=0.05)
+    ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
+    k, v = I.kv_fill(2, keys, head_dim, seed=7)
+    kd, vd = to_dev(k, "f32"), to_dev(v, "f32")
+    oc, gc = O.KVCache(ol, B, keys + 1), gl.cache(B, keys + 1)
+    for s, n in enumerate(lens):
+        oc.set(s, k[:, :n], v[:, :n])
+        pd.pd_kv_cache_set(gc, s, kd[:, :n].contiguous(), vd[:, :n].contiguous())
+    x = I.hidden(B, 64, seed=8)
+    assert relmax(gl.decode(x, list(range(B)), gc), O.decode_step(ol, x, list(range(B)), oc)) <= TOL["f32"]
     gl.close()
