@@ -1034,6 +1034,7 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
         const int Ls = tk->cu_seqlens[q + 1] - tk->cu_seqlens[q];
         a.mean_keys += (double)Ls * (prefix[(size_t)q] + 0.5 * (Ls + 1)) / T;
         if (Ls > 0) a.max_keys = std::max(a.max_keys, prefix[(size_t)q] + Ls);
+        a.q_tiles += (Ls + 15) / 16;
     }
     a.rows_share = 1;
     const bool short_chunk = chunk && cache->blocked && max_L <= kShortChunk;

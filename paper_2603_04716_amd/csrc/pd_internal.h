@@ -419,6 +419,7 @@ struct AttnArgs {
     // rows next to each other read the same keys (several rows of a sequence)
     double mean_keys;
     int32_t max_keys, rows_share;
+    int32_t q_tiles;         // prefill: 16-row tiles that the sequences have in all
 };
 hipError_t launch_attn_generic(int dtype, const AttnArgs &a, hipStream_t s);
 bool attn_prefill_mfma_supported(const AttnArgs &a);

@@ -151,3 +151,49 @@ def test_decode_on_both_sides_of_the_choice(head_dim, B, keys, split):
     x = I.hidden(B, 64, seed=8)
     assert relmax(gl.decode(x, list(range(B)), gc), O.decode_step(ol, x, list(range(B)), oc)) <= TOL["f32"]
     gl.close()
+
+
+def _tiles(hd, hq, lens):
+    return bool(pd.lib.pd_internal_attn_tiles_pay(hd, hq, len(lens), (C.c_int32 * len(lens))(*lens)))
+
+
+def test_tiled_attention_where_it_pays():
+    """Sizes on both sides, each measured with both forms: a wave per item for short sequences, alone or by the thousand."""
+    assert _tiles(64, 4, [96] * 4) and _tiles(128, 16, [16] * 1000) and _tiles(256, 4, [1500] * 2) and _tiles(128, 64, [2000] + [3] * 500)
+    assert _tiles(64, 4, [40]) and _tiles(128, 16, [100]) and _tiles(128, 16, [30] * 256)
+    assert not _tiles(64, 16, [1] * 4096) and not _tiles(128, 16, [3] * 1000) and not _tiles(256, 4, [10] * 1000)
+    assert not _tiles(64, 4, [1]) and not _tiles(128, 64, [100] + [1] * 1000)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128, 256])
+@pytest.mark.parametrize("lens,tiled", [([300] + [1, 0, 2] * 20, True), ([120, 3, 0, 40], True), ([2] * 300, False)])
+def test_prefill_on_both_sides_of_the_choice(head_dim, lens, tiled):
+    """Also tiles in an odd grid: 300 rows have 19, 120 rows 8, which become 9."""
+    assert _tiles(head_dim, 4, lens) == tiled
+    cfg = I.small_config(d_model=64, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=64)
+    w = I.layer_weights(cfg, std=0.05)
+    ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    x = I.hidden(int(cu[-1]), 64, seed=8)
+    assert relmax(gl.prefill(x, cu), O.prefill(ol, x, cu)) <= TOL["f32"]
+    gl.close()
+
+
+def test_time_of_a_long_sequence_among_short_ones():
+    """256 + 800 x 2 rows (16 tiles per head, all but one of a short sequence empty) against 272 + 800 x 2 (17 tiles): the
+    tiles of the short sequences are spread over the chip in both."""
+    cfg = I.small_config(d_model=64, n_q_heads=16, n_kv_heads=4, head_dim=128, d_ff=64)
+    gl = GpuLayer(cfg, I.layer_weights(cfg, std=0.05))
+
+    def ms(lens):
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        x, best = torch.zeros((int(cu[-1]), 64), device="cuda"), 1e9
+        y = torch.empty_like(x)
+        for _ in range(5):
+            pd.pd_profile_enable(gl.h, True)
+            pd.pd_prefill(gl.h, x, cu, y)
+            best = min(best, dict(pd.pd_profile_read(gl.h))["prefill_attention"])
+        return best
+
+    assert ms([256] + [2] * 800) <= 2 * ms([272] + [2] * 800)
+    gl.close()
