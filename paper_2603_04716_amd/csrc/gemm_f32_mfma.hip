@@ -142,6 +142,10 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GemmArgs a)
 bool gemm_f32_mfma_supported(const GemmArgs &a)
 {
     const long long row_tiles = ((long long)a.M + 31) / 32 + (a.group_offsets ? a.n_groups : 0);
+    // Up to 64 k a wave has one of the four k-steps that it requests; with outputs enough to fill the chip several times
+    // over that costs more than the plain form's 64 x 64 tiles do.  Plain -> this form, us, at K = 64 and 96: 10000 x 1000
+    // 65 -> 83, 88 -> 70; 5000 x 5000 123 -> 181, 171 -> 141; 2000 x 1000 (2016 tiles) 22 -> 22, 29 -> 19; 1000 x 768 16 -> 12.
+    if (a.K <= 64 && row_tiles * ((a.N + 31) / 32) >= 2048) return false;
     return row_tiles <= 65535 && a.M > 0 && a.N > 0 && a.K >= 4 && a.K % 4 == 0 && a.lda % 4 == 0 && a.ldb % 4 == 0 && a.b_group_stride % 4 == 0 &&
            (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)(a.epilogue == EPI_SWIGLU ? a.B1 : nullptr)) & 15) == 0;
 }

@@ -197,3 +197,18 @@ def test_time_of_a_long_sequence_among_short_ones():
 
     assert ms([256] + [2] * 800) <= 2 * ms([272] + [2] * 800)
     gl.close()
+
+
+@pytest.mark.parametrize("T,d", [(2016, 64), (1984, 64), (2016, 68)])
+def test_products_with_a_short_k(T, d):
+    """Beside the line between the plain form (K up to 64, from 2048 tiles on) and the matrix form: 63 x 33 and 62 x 33 tiles."""
+    V = 1050
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    x, w = torch.randn((T, d), device="cuda", generator=gen), torch.randn((V, d), device="cuda", generator=gen)
+    head = pd.pd_head_create(d, V, 1e-6, "f32", torch.ones(d, device="cuda"), w, None, T)
+    got = torch.full((T, V), float("nan"), device="cuda")
+    pd.pd_lm_head(head, x, got)
+    xd = x.double()
+    ref = (xd * torch.rsqrt(xd.square().mean(1, keepdim=True) + 1e-6)) @ w.double().T
+    assert float((got - ref).abs().max() / ref.abs().max()) <= TOL["f32"]
+    pd.pd_head_destroy(head)
