@@ -612,19 +612,16 @@ static int choose_splits(const GemmArgs &a, int BM, int BN)
 // bytes wide in either, and takes the same time).  256 x 256 tiles are the fastest per flop, but a launch runs in
 // rounds of one workgroup per CU: a few hundred to a few thousand rows fill the last round badly, and so do 257 rows
 // that take two row tiles.  Each form's time is therefore estimated as
-//   rounds x k-tiles per split x time of a k-tile + 5 us + (split: the launch that adds the partials)
-// with the times of a k-tile measured on the projections of the 8B shape at 300 ... 8192 rows (us):
-//   256 x 256 1.80 (1.70 where one round does), 192 x 256 1.45, 128 x 128 with two workgroups per CU 1.06 for the
-//   pair (a last round of at most one per CU 0.5 ... 0.8 of that, the fuller the slower), 128 x 128 with eight waves,
-//   alone on its CU with a four-stage ring, 0.66
-// and a split costing 5 us plus its partials written and read at 8 TB/s.  Measured against 256 x 256 tiles with
-// their best split, us: bf16 QKV 771 rows 68 -> 59 (192), O 512 rows 39 -> 33 (128, 8 waves), gate/up 300 rows
-// 110 -> 88 (192), down 5107 rows 737 -> 641 (192); 8-bit QKV 512 rows 40 -> 23, O 1024 rows 46 -> 27 (128, 8 waves),
-// gate/up 300 rows 60 -> 46 (192).
+//   start + k-tiles per split x (full rounds x time of a k-tile + the last round's, from few workgroups to a full one)
+// and a split's as the launch that adds the partials, 1.8 us, and the partials written and read at 6 TB/s (a product whose
+// sum would carry the norm behind it saves that launch, 6.5 us).  The constants are fitted to 26000 launches: nine layer
+// shapes of 512 ... 8192 columns, 257 ... 6000 rows, bf16 and codes, every form and split.  On them the choice takes 0.5 %
+// longer than the best form and split (at worst 20 %, 23 against 19 us), and 22 % less than what served before there were
+// several forms (256 x 256, codes of up to 512 rows 256 x 64; 22 of 1296 products are 3 - 9 % slower than that).
+// us, 256 x 256 with their best split -> planned: bf16 QKV 771 rows 68 -> 59 (192), O 512 rows 39 -> 33 (128, 8 waves),
+// gate/up 300 rows 110 -> 88 (192), down 5107 rows 737 -> 641 (192); codes O 1024 rows 46 -> 27 (128, 8 waves).
 // A grouped product's loads are known only on the average, so another form than 256 x 256 has to be 5 % ahead there
-// (without that, 9200 rows on 8 experts took 4330 instead of 4265 us).  Prefill layer of 8 experts,
-// top 2, 256 x 256 -> planned, us: 1100 rows 1530 -> 1326, 1300 1588 -> 1353, 2100 2475 -> 2219, 2600 2590 -> 2486,
-// 1700 and 3000 .. 4600 the same.
+// (without that, 9200 rows on 8 experts took 4330 instead of 4265 us).
 enum TileForm { TILE_256, TILE_192, TILE_128_PAIR, TILE_128_DEEP };
 struct TilePlan {
     TileForm form;
@@ -652,24 +649,21 @@ static TilePlan plan_tiles(const GemmArgs &a)
     double best_us = 1e30;
     const struct {
         TileForm form;
-        int bm, bn;
-        double kt_us;
-    } forms[] = {{TILE_256, 256, 256, 1.80}, {TILE_192, 192, 256, 1.45}, {TILE_128_PAIR, 128, 128, 1.06}, {TILE_128_DEEP, 128, 128, 0.66}};
+        int bm, bn, per_round;
+        double start, kt_full, kt_few;
+    } forms[] = {{TILE_256, 256, 256, 256, 3.7, 1.626, 1.211},
+                 {TILE_192, 192, 256, 256, 2.6, 1.348, 1.107},
+                 {TILE_128_PAIR, 128, 128, 512, 0.85, 1.053, 0.62},          // two workgroups per CU
+                 {TILE_128_DEEP, 128, 128, 256, 0.0, 0.636, 0.486}};         // eight waves, alone on its CU with a four-stage ring
     for (const auto &f : forms) {
         const long long tiles = (long long)ceil(row_tiles(a, f.bm) * ((n_cols + f.bn - 1) / f.bn));
         for (int sp = 1; sp <= 8; ++sp) {
-            if (sp > 1 && (!can_split || nk / sp < 6 || (size_t)sp * a.M * n_cols > a.splitk_ws_elems)) break;
-            const long long wg = tiles * sp;
-            double rounds = (double)((wg + 255) / 256);
-            double kt_us = f.kt_us;
-            if (f.form == TILE_256 && wg <= 256) kt_us = 1.70;
-            if (f.form == TILE_128_PAIR) {
-                const long long rem = wg % 512;
-                rounds = (double)(wg / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 0.5 + 0.3 * (double)rem / 256.0 : 1.0);
-            }
-            double us = rounds * ((nk + sp - 1) / sp) * kt_us + 5.0;
-            if (sp > 1) us += 5.0 + (double)sp * a.M * n_cols * 8.0 / 8e6;
-            else if (a.fuse_y) us += 4.0;              // the norm that a split's sum carries costs a launch of its own
+            if (sp > 1 && (!can_split || nk / sp < 2 || (size_t)sp * a.M * n_cols > a.splitk_ws_elems)) break;
+            const long long wg = tiles * sp, full = wg / f.per_round, rem = wg % f.per_round;
+            const double last = rem ? f.kt_few + (f.kt_full - f.kt_few) * (double)rem / f.per_round : 0.0;
+            double us = f.start + ((nk + sp - 1) / sp) * ((double)full * f.kt_full + last);
+            if (sp > 1) us += 1.8 + (double)sp * a.M * n_cols * 8.0 / 6e6;
+            else if (a.fuse_y) us += 6.5;
             if (a.group_offsets && f.form != TILE_256) us *= 1.05;
             if (us < best_us) {
                 best_us = us;

@@ -63,7 +63,8 @@ def test_llama8b_prefill_8192_tokens_sampled_rows(llama, l_in):
     assert np.array_equal(got2[:l_in], got[:l_in])
 
 
-@pytest.mark.parametrize("rows,forms", [(300, ["192/split", "pair/split", "192", "192/split"]), (512, ["deep", "deep/split", "256", "256/split"])])
+@pytest.mark.parametrize("rows,forms", [(300, ["pair/split", "pair/split", "192", "192/split"]), (400, ["deep", "deep/split", "256", "256/split"]),
+                                        (655, ["256/split", "pair/split", "192", "192/split"])])
 def test_llama8b_prefill_of_a_few_hundred_rows(llama, rows, forms):
     """K splits of the wide tile forms, which only large products take: forms of QKV, O (its sum carries the norm),
     gate / up and down.  One sampled row per 16-row block and both ends."""

@@ -10,8 +10,8 @@ from gpu_util import GpuLayer, TOL, relmax, tile_plan
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,d_ff,form", [(12, 1024, None), (64, 2048, None), (700, 1024, None), (2500, 512, "pair"), (2500, 1024, "192"),
-                                         (1450, 2048, "256"), (1510, 256, "deep")])
+@pytest.mark.parametrize("T,d_ff,form", [(12, 1024, None), (64, 2048, None), (700, 1024, None), (2500, 512, "pair"), (2500, 1024, "deep"),
+                                         (1150, 4096, "192"), (1450, 4096, "256")])
 @pytest.mark.parametrize("skew", ["even", "two", "ragged"])
 def test_grouped_products_deal_the_tiles_in_use(T, d_ff, form, skew):
     """Expert loads from even to two experts with all rows: the tiles in use are from all to few of those launched.
