@@ -717,10 +717,12 @@ static hipError_t launch_planned(const GemmArgs &a, hipStream_t s)
     case TILE_128_DEEP: return launch_cfg<128, 128, 4, 2, 4, F8>(a, s, p.splits);
     default: break;
     }
-    // 8 waves (two per SIMD hide each other's stalls) or 16: at 8192 rows, us, 8 -> 16 waves: 8-bit gate/up 854 -> 834,
-    // down 398 -> 374, O 138 -> 129, QKV 180 -> 175; bf16 O 254 -> 246, but QKV 348 -> 372, gate/up 1689 -> 1694,
-    // down 851 -> 862
-    if (F8 || (a.epilogue == EPI_RESIDUAL && a.K <= 4096)) return launch_cfg<256, 256, 4, 4, 2, F8>(a, s, p.splits);
+    // 8 waves (two per SIMD hide each other's stalls) or 16, which halve what a wave does before and behind its k-tiles:
+    // worth more the fewer k-tiles there are, more where the epilogue also reads a residual, and always with codes, whose
+    // k-tiles are as long but half as many.  8 -> 16 waves, us, at 4096 rows: codes O (K = 4096) 91 -> 84, gate/up 418 -> 405;
+    // bf16 residual K = 1024 39 -> 33, 4096 139 -> 132, 5120 295 -> 280, 14336 408 -> 407; bf16 plain K = 1024 32 -> 29, 2048
+    // 56 -> 55, 3072 164 -> 163, 4096 (8192 rows) 352 -> 354, 8192 626 -> 639; SwiGLU 1 - 3 % slower from K = 2048 on
+    if (F8 || (a.epilogue == EPI_RESIDUAL && a.K <= 4096) || (a.epilogue == EPI_NONE && a.K <= 2048)) return launch_cfg<256, 256, 4, 4, 2, F8>(a, s, p.splits);
     return launch_cfg<256, 256, 2, 4, 2, F8>(a, s, p.splits);
 }
 
