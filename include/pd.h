@@ -152,8 +152,8 @@ pd_status pd_gemm_e4m3(const void *a_codes, const float *a_scales, const void *b
  * captured over this layer before that holds the freed addresses and must not be replayed again.
  * Reserve for the largest call first, then capture.
  * The attention scratch is the layer's own and is kept until the layer is destroyed.  Where a
- * pd_prefill_chunk call makes it grow, it grows towards what the same call needs with full slots: to at
- * most twice what this call needs and at most 64 MiB more than that need, and only if the device has it.
+ * pd_prefill_chunk call makes it grow, it grows towards what the same call needs with full slots: by at
+ * most as much again as this call needs (or 16 MiB) and at most 64 MiB, and only if the device has it.
  */
 pd_status pd_layer_reserve(pd_layer *layer, int32_t max_tokens);
 

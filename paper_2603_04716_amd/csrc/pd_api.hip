@@ -908,9 +908,9 @@ static pd_status run_tail(pd_layer *L, const void *x, int T, const void *router_
 
 // At least `need` bytes of attention scratch.  Where it has to grow it takes more, towards `ahead` bytes, if they can
 // be had: a prompt fed in chunks needs a little more with every chunk, and each growth waits for the device, frees and
-// allocates.  At most as much again as the call needs and at most 64 MiB: every layer holds its own scratch, and what
-// is taken ahead is missing from caches and layers made later.  The first prompt of a layer (8B shape), us, grown call
-// by call -> this way (later prompts): 4096 tokens in chunks of 512 5210 -> 3430 (2970), 8192 11530 -> 6650 (6050).
+// allocates.  At most as much again as the call needs (or 16 MiB) and at most 64 MiB: every layer holds its own scratch,
+// and what is taken ahead is missing from caches and layers made later.  The first prompt of a layer (8B shape), us, grown call by call ->
+// this way (later prompts): 4096 tokens in chunks of 512 5210 -> 2990 (2990), 8192 11530 -> 6600 (6000).
 static pd_status reserve_attn_scratch(pd_layer *L, size_t need, size_t ahead, const char *who)
 {
     if (need <= L->vt_cap) return PD_OK;
@@ -918,7 +918,7 @@ static pd_status reserve_attn_scratch(pd_layer *L, size_t need, size_t ahead, co
     if (L->vt) (void)hipFree(L->vt);
     L->vt = nullptr;
     L->vt_cap = 0;
-    size_t bytes = std::max(need, std::min(ahead, need + std::min(need, (size_t)64 << 20)));
+    size_t bytes = std::max(need, std::min(ahead, need + std::min(std::max(need, (size_t)16 << 20), (size_t)64 << 20)));
     hipError_t e = hipMalloc(&L->vt, bytes);
     if (e != hipSuccess && bytes > need) {
         (void)hipGetLastError();
@@ -1042,6 +1042,7 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
     const int vt_ld = pad[(size_t)n];
     const size_t vt_bytes = (size_t)c.n_kv_heads * c.head_dim * vt_ld * 2;
     int n_split = 1;
+    bool split_in_ws = false;
     if (tile_attn) {
         if (chunk && !attn_prefill_mfma_supported(a)) {
             set_error("pd_prefill_chunk: blocked cache without the matrix-core attention path");
@@ -1053,10 +1054,18 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
                 max_keys = std::max(max_keys, prefix[(size_t)q] + tk->cu_seqlens[q + 1] - tk->cu_seqlens[q]);
             n_split = attn_chunk_splits(a, max_keys);
         }
-        const size_t need = chunk ? 2 * vt_bytes + attn_chunk_split_bytes(a, n_split) : vt_bytes;
+        // The partial results of a split lie in the products' split-K scratch where they fit: no product is under way
+        // between the attention and the kernel that merges them.
+        const size_t own = L->splitk_elems * sizeof(float);
+        auto beside = [&](int splits) {
+            const size_t b = attn_chunk_split_bytes(a, splits);
+            return b <= own ? (size_t)0 : b;
+        };
+        split_in_ws = beside(n_split) == 0;
+        const size_t need = chunk ? 2 * vt_bytes + beside(n_split) : vt_bytes;
         // chunks: what the same call takes once its slots are full
         const size_t full = chunk ? 2 * (size_t)c.n_kv_heads * c.head_dim * 2 * n * cache->plane_len +
-                                        attn_chunk_split_bytes(a, attn_chunk_splits(a, cache->max_len))
+                                        beside(attn_chunk_splits(a, cache->max_len))
                                   : 0;
         const pd_status rs = reserve_attn_scratch(L, need, full, "pd_prefill");
         if (rs != PD_OK) return rs;
@@ -1168,7 +1177,7 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
             a.kv_fp8 = cache->fp8; a.k_scale = (float)cache->k_scale; a.v_scale = (float)cache->v_scale;
             STEP("prefill_attention",
                  launch_attn_chunk_mfma(a, L->d_slots, (uint16_t *)((char *)L->vt + vt_bytes), (uint16_t *)L->vt,
-                                        vt_ld, L->d_pad_cu, n_split, (float *)((char *)L->vt + 2 * vt_bytes), s));
+                                        vt_ld, L->d_pad_cu, n_split, split_in_ws ? L->splitk : (float *)((char *)L->vt + 2 * vt_bytes), s));
         } else {
             STEP("prefill_attention", launch_attn_prefill_mfma(a, (uint16_t *)L->vt, vt_ld, L->d_pad_cu, s));
         }

@@ -247,8 +247,8 @@ def _used_by(call):
 
 
 def test_scratch_taken_ahead_is_bounded():
-    """A chunk's attention scratch grows ahead of the prompt, to at most twice what the call needs and by at most 64 MiB,
-    also where the slots could hold far more; chunks that fit the scratch take nothing."""
+    """A chunk's attention scratch grows ahead of the prompt, by at most as much again as the call needs (16 MiB for small
+    ones) and at most 64 MiB, also where the slots could hold far more; chunks that fit the scratch take nothing."""
     cfg = I.small_config(dtype="bf16", d_model=256, n_q_heads=16, n_kv_heads=8, head_dim=128, d_ff=512)
     d = cfg["d_model"]
     gl = GpuLayer(cfg, I.layer_weights(cfg, std=0.05))
