@@ -197,7 +197,8 @@ pd_status pd_kv_cache_set_lens(pd_kv_cache *cache, int32_t n, const int32_t *slo
                                const int32_t *lens, void *stream);
 /* Reads a slot's length (host-side mirror; no device access). */
 pd_status pd_kv_cache_len(const pd_kv_cache *cache, int32_t slot, int32_t *len);
-/* Debug/test read-back of one slot's first len positions into device tensors [n_kv_heads, len, head_dim]. */
+/* Copies one slot's first len positions out into device tensors [n_kv_heads, len, head_dim]: the hand-off to another
+ * instance, or a check. */
 pd_status pd_kv_cache_get(const pd_kv_cache *cache, int32_t slot, int32_t len, void *k, void *v,
                           void *stream);
 

@@ -1024,10 +1024,11 @@ __global__ __launch_bounds__(512) void kv_copy_block_kernel(uint16_t *ck, uint16
     const int n_pos = len - p0 < 32 ? len - p0 : 32;
     const size_t plane = ((size_t)slot * Hkv + g) * max_len_pad * 128;
     const size_t user = ((size_t)g * len + p0) * 128;
+    const int row = tid >> 4, c8 = (tid & 15) * 8;                 // this thread's 8 channels of a position
     if (blockIdx.z == 0) {
-        for (int e = tid; e < n_pos * 16; e += 512) {
-            uint4 *c = (uint4 *)(ck + plane + kblk_off(p0 + (e >> 4), (e & 15) * 8));
-            uint4 *u = (uint4 *)(k + user + (size_t)e * 8);
+        if (row < n_pos) {
+            uint4 *c = (uint4 *)(ck + plane + kblk_off(p0 + row, c8));
+            uint4 *u = (uint4 *)(k + user + (size_t)tid * 8);
             if (TO_CACHE) *c = *u;
             else *u = *c;
         }
@@ -1039,14 +1040,12 @@ __global__ __launch_bounds__(512) void kv_copy_block_kernel(uint16_t *ck, uint16
             for (int e = tid; e < n_pos * 128; e += 512) vb[vblk_off(e >> 7, e & 127)] = v[user + e];
             return;
         }
-        for (int e = tid; e < 32 * 16; e += 512)
-            *(uint4 *)(tile + (e >> 4) * kVtRow + (e & 15) * 8) = *(const uint4 *)(v + user + (size_t)e * 8);
+        *(uint4 *)(tile + row * kVtRow + c8) = *(const uint4 *)(v + user + (size_t)tid * 8);
         __syncthreads();
     }
-    // chunk e of the block: channel e / 4, positions 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3 with q = e % 4
-    for (int e = tid; e < 128 * 4; e += 512) {
-        const int d = e >> 2, q = e & 3;
-        if (4 * q >= n_pos) continue;
+    // chunk tid of the block: channel tid / 4, positions 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3 with q = tid % 4
+    const int d = tid >> 2, q = tid & 3;
+    if (4 * q < n_pos) {
         uint16_t *t = tile + 4 * q * kVtRow + d;
         uint4 x;
         if (TO_CACHE) {
@@ -1054,9 +1053,9 @@ __global__ __launch_bounds__(512) void kv_copy_block_kernel(uint16_t *ck, uint16
             x.y = t[2 * kVtRow] | ((uint32_t)t[3 * kVtRow] << 16);
             x.z = t[16 * kVtRow] | ((uint32_t)t[17 * kVtRow] << 16);
             x.w = t[18 * kVtRow] | ((uint32_t)t[19 * kVtRow] << 16);
-            *(uint4 *)(vb + (size_t)e * 8) = x;
+            *(uint4 *)(vb + (size_t)tid * 8) = x;
         } else {
-            x = *(const uint4 *)(vb + (size_t)e * 8);
+            x = *(const uint4 *)(vb + (size_t)tid * 8);
             t[0] = (uint16_t)x.x; t[kVtRow] = (uint16_t)(x.x >> 16);
             t[2 * kVtRow] = (uint16_t)x.y; t[3 * kVtRow] = (uint16_t)(x.y >> 16);
             t[16 * kVtRow] = (uint16_t)x.z; t[17 * kVtRow] = (uint16_t)(x.z >> 16);
@@ -1065,8 +1064,7 @@ __global__ __launch_bounds__(512) void kv_copy_block_kernel(uint16_t *ck, uint16
     }
     if (!TO_CACHE) {
         __syncthreads();
-        for (int e = tid; e < n_pos * 16; e += 512)
-            *(uint4 *)(v + user + (size_t)e * 8) = *(const uint4 *)(tile + (e >> 4) * kVtRow + (e & 15) * 8);
+        if (row < n_pos) *(uint4 *)(v + user + (size_t)tid * 8) = *(const uint4 *)(tile + row * kVtRow + c8);
     }
 }
 
@@ -1133,22 +1131,22 @@ __global__ __launch_bounds__(1024) void kv_read_block_fp8_kernel(const uint8_t *
     const int n_pos = len - p0 < 64 ? len - p0 : 64;
     const size_t plane = ((size_t)slot * Hkv + g) * max_len_pad * 128;
     const size_t user = ((size_t)g * len + p0) * 128;
+    const int row = tid >> 4, c8 = (tid & 15) * 8;                 // this thread's 8 channels of a position
     if (blockIdx.z == 0) {
-        for (int e = tid; e < n_pos * 16; e += 1024) {
-            const uint2 c = *(const uint2 *)(ck + plane + kblk8_off(p0 + (e >> 4), (e & 15) * 8));
-            *(uint4 *)(k + user + (size_t)e * 8) = make_uint4(e4m3_pair_to_bf16(c.x, k_scale), e4m3_pair_to_bf16(c.x >> 16, k_scale),
-                                                              e4m3_pair_to_bf16(c.y, k_scale), e4m3_pair_to_bf16(c.y >> 16, k_scale));
+        if (row < n_pos) {
+            const uint2 c = *(const uint2 *)(ck + plane + kblk8_off(p0 + row, c8));
+            *(uint4 *)(k + user + (size_t)tid * 8) = make_uint4(e4m3_pair_to_bf16(c.x, k_scale), e4m3_pair_to_bf16(c.x >> 16, k_scale),
+                                                                e4m3_pair_to_bf16(c.y, k_scale), e4m3_pair_to_bf16(c.y >> 16, k_scale));
         }
         return;
     }
-    // run e of the block (8 bytes): channel 16 (e / 128) + e / 2 % 16, half e % 2 of the positions, and inside it
-    // positions 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3 with q = e / 32 % 4
+    // run tid of the block (8 bytes): channel 16 (tid / 128) + tid / 2 % 16, half tid % 2 of the positions, and inside it
+    // positions 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3 with q = tid / 32 % 4
     const uint8_t *vb = cv + plane + (size_t)(p0 >> 6) * 8192;
-    for (int e = tid; e < 1024; e += 1024) {
-        const int d = (e >> 7) * 16 + ((e >> 1) & 15), q = (e >> 5) & 3;
-        if ((e & 1) * 32 + 4 * q >= n_pos) continue;
-        uint16_t *t = tile + ((e & 1) * 32 + 4 * q) * kVtRow + d;
-        const uint2 c = *(const uint2 *)(vb + (size_t)e * 8);
+    const int d = (tid >> 7) * 16 + ((tid >> 1) & 15), q = (tid >> 5) & 3;
+    if ((tid & 1) * 32 + 4 * q < n_pos) {
+        uint16_t *t = tile + ((tid & 1) * 32 + 4 * q) * kVtRow + d;
+        const uint2 c = *(const uint2 *)(vb + (size_t)tid * 8);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const uint32_t w = j ? c.y : c.x;
@@ -1159,8 +1157,7 @@ __global__ __launch_bounds__(1024) void kv_read_block_fp8_kernel(const uint8_t *
         }
     }
     __syncthreads();
-    for (int e = tid; e < n_pos * 16; e += 1024)
-        *(uint4 *)(v + user + (size_t)e * 8) = *(const uint4 *)(tile + (e >> 4) * kVtRow + (e & 15) * 8);
+    if (row < n_pos) *(uint4 *)(v + user + (size_t)tid * 8) = *(const uint4 *)(tile + row * kVtRow + c8);
 }
 
 hipError_t launch_kv_copy_fp8(void *cache_k, void *cache_v, const void *k, const void *v, int slot, int Hkv,
