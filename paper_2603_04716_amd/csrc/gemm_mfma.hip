@@ -1,46 +1,51 @@
 // bf16 GEMM on the CDNA4 matrix cores:  C[M,N] = epilogue(A[M,K] * B[N,K]^T), fp32 accumulation.
 //
-// Both operands are K-contiguous, which is exactly the per-lane operand layout of
-// v_mfma_f32_32x32x16_bf16 (each lane supplies 8 consecutive k of one row / column), so tiles go
-// global -> LDS with the direct-to-LDS 16-byte loads of gfx950 (no staging registers, no LDS
-// write instructions) and LDS -> registers with 16-byte reads, with no transposition anywhere.
-// A direct load puts lane i's 16 bytes at LDS offset base + 16*i, so the XOR swizzle that keeps
-// the fragment reads free of bank conflicts is applied on the global side: the lane that owns LDS
-// slot (row, s) fetches chunk s ^ ((row >> 1) & 7) of that row.  LDS holds NS stages: the loads of
-// the next NS-1 k-tiles are in flight while the matrix cores work on tile k; one barrier per tile.
+// Both operands are K-contiguous, which is exactly the per-lane operand layout of v_mfma_f32_16x16x32_bf16 (each
+// lane supplies 8 consecutive k of one row / column), so tiles go global -> LDS with the direct-to-LDS 16-byte
+// loads of gfx950 (no staging registers, no LDS write instructions) and LDS -> registers with 16-byte reads, with
+// no transposition anywhere.  A direct load puts lane i's 16 bytes at LDS offset base + 16*i, so the XOR swizzle
+// that keeps the fragment reads of A free of bank conflicts is applied on the global side: the lane that owns LDS
+// slot (row, s) fetches chunk s ^ ((row >> 1) & 7) of that row.  The weight operand B arrives in the packed block
+// layout of pd_internal.h (1 KB blocks of 16 rows x 32 k): one direct-to-LDS instruction moves one block, blocks
+// sit linearly in LDS, and a fragment is one block, read contiguously.
 //
-// The weight operand B arrives in the packed block layout of pd_internal.h (1 KB blocks of 16 rows
-// x 32 k): one direct-to-LDS instruction moves one block, blocks sit linearly in LDS, and the
-// fragment reads of 16 consecutive lanes are 256 contiguous bytes, so B needs no swizzle.
+// A workgroup is four waves, one per SIMD, and a wave's tile is as large as its registers allow (128 x 128 of a
+// 256 x 256 tile: 256 accumulator registers, 128 for two sets of fragments).  What bounds the large products is
+// power: at full matrix rate the clock falls until the card stays inside its limit, so a flop's energy counts, and
+// that is the multipliers' and the LDS reads'.  Large wave tiles read 128 KB of LDS per 64-wide k-tile of 256 x 256
+// (eight waves of 128 x 64: 192 KB, which with the incoming 64 KB also keeps the LDS busy all the time), and
+// 16x16x32 runs at a higher clock than 32x32x16 at the same rate of flops (half the accumulator traffic).
+// With one wave per SIMD nothing else covers a wave's waits, so the k-loop is written as one instruction stream:
+// between the MFMAs of half a k-tile stand the LDS reads of the next half's fragments and the direct-to-LDS
+// requests of a later tile, a few MFMAs apart (a request occupies the CU's address unit for 16 clocks and the four
+// waves issue theirs together, so closer than about five MFMAs they hold up the stream).  One barrier per k-tile.
+// Measured, gate / up of the 8B shape at 8192 rows: 2300 clocks per k-tile for 2048 of MFMA issue (3700 with eight
+// waves of 128 x 64 and 32x32x16, the reads of each fragment right ahead of its use), 1160 -> 1480 TFLOP/s; a
+// request every four MFMAs 2640 clocks, the reads' spread does not matter there.
 //
-// Epilogues: plain store, residual add, and SwiGLU.  For SwiGLU the weight is packed at layer
-// creation as alternating 32-row blocks (gate rows j..j+31, then up rows j..j+31); an MFMA output
-// block pair then holds gate and up of the same (row, column) in the same lane and register, and
-// silu(gate)*up is formed without any data exchange.
+// Epilogues: plain store, residual add, and SwiGLU.  For SwiGLU the weight is packed at layer creation as
+// alternating 32-row blocks (gate rows j..j+31, then up rows j..j+31); two blocks of 16 columns that lie 32 apart
+// then hold gate and up of the same (row, column) in the same lane and register, and silu(gate)*up is formed
+// without any data exchange.
 //
 // Optional row gather on A and per-group B matrices serve the mixture-of-experts grouped GEMM.
 //
-// Decode-sized problems (M <= 256) have too few output tiles to occupy 256 CUs while the weights
-// stream from HBM, so K is split over gridDim.y: each split writes an fp32 partial tile and a
-// second small kernel adds the splits in a fixed order and applies the epilogue (deterministic,
-// no atomics).
+// Decode-sized problems (M <= 256) have too few output tiles to occupy 256 CUs while the weights stream from HBM,
+// so K is split over gridDim.y: each split writes an fp32 partial tile and a second small kernel adds the splits in
+// a fixed order and applies the epilogue (deterministic, no atomics).
 #include <string.h>
+
+#include <type_traits>
+#include <utility>
 
 #include "pd_internal.h"
 
 namespace pd {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ i32x8 cat32(bf16x8 lo, bf16x8 hi)
-{
-    const i32x4 l = __builtin_bit_cast(i32x4, lo), h = __builtin_bit_cast(i32x4, hi);
-    return i32x8{l[0], l[1], l[2], l[3], h[0], h[1], h[2], h[3]};
-}
 
 constexpr int BK = 64;  // k per tile: 8 chunks of 16 bytes per row
 
@@ -48,21 +53,77 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >>
 
 __device__ __forceinline__ float silu_fast(float z) { return z / (1.0f + __expf(-z)); }
 
-// F8: both operands are E4M3 codes and the caller passes them as if two codes were one bf16 element
-// (K, lda, ldb halved; the weight pack is the bf16 pack of that view), so every byte moves exactly as
-// above.  Two consecutive 16-byte fragments of a lane form the 32-byte operand of
-// v_mfma_f32_32x32x64_f8f6f4: which of the 64 k of the step a byte stands for does not matter as long
-// as both operands are assembled the same way, and they are.  The fp32 sums are multiplied by the
+// acc += w x with acc in AGPRs
+__device__ __forceinline__ void mfma_agpr(f32x4 &acc, const bf16x8 &w, const bf16x8 &x)
+{
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+}
+__device__ __forceinline__ void mfma_agpr(f32x4 &acc, const i32x8 &w, const i32x8 &x)
+{
+    asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+}
+
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// f(0), ..., f(N - 1) with the index a compile-time constant
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (N > 0) static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// Stages and schedule of a tile form.  LDS holds NSA stages of the A tile and NSB of the B tile.  Positions are in
+// 64ths of half a k-tile, counted from the barrier: A's requests are spread over PA of them, B's over the PB behind; the
+// fragment reads of a half over the first RS.
+template <int BM, int BN, int WAVES, int NS>
+struct TileRing {
+    // two stages: the third of B's that the 160 KB leave room for lets B's requests run a tile ahead, so that only A's have
+    // to land within the tile
+    static constexpr bool deep = NS == 2 && BN == 256;
+    static constexpr int NSA = NS, NSB = deep ? 3 : NS;
+    static constexpr int A_LD = BM / 8 / WAVES, B_LD = BN / 8 / WAVES, LD = A_LD + B_LD;   // requests of a wave per k-tile
+    static constexpr int span = deep ? 120 : NS == 2 ? 72 : 120;
+    static constexpr int PA = deep ? 48 : span * A_LD / LD, PB = span - PA;
+    static constexpr int RS = BM * BN >= 256 * 192 ? 48 : 28;
+    static constexpr size_t lds = (size_t)(NSA * BM + NSB * BN) * BK * 2;
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    static_assert(BM % (8 * WAVES) == 0 && BN % (8 * WAVES) == 0, "loader mapping");
+    // requests issued ahead of position p
+    static constexpr int issued(int p)
+    {
+        int n = 0;
+        for (int d = 0; d < LD; ++d) n += (d < A_LD ? d * PA / A_LD : PA + (d - A_LD) * PB / B_LD) < p;
+        return n;
+    }
+    // of n fragment reads, those issued ahead of MFMA m of nm
+    static constexpr int reads(int m, int nm, int n)
+    {
+        const int r = m * n * 64 / (RS * nm);
+        return m == nm || r > n ? n : r;
+    }
+};
+
+// F8: both operands are E4M3 codes and the caller passes them as if two codes were one bf16 element (K, lda, ldb
+// halved; the weight pack is the bf16 pack of that view), so every byte moves exactly as above.  Two 16-byte
+// fragments of a lane, of the two halves of the k-tile, form the 32-byte operand of v_mfma_f32_16x16x128_f8f6f4:
+// which of the 128 k of the step a byte stands for does not matter as long as both operands are assembled the same
+// way, and they are.  An MFMA needs both halves of k, so the halves of the loop are the upper and the lower row
+// blocks of the wave's tile instead, with B's fragments in two register sets.  The fp32 sums are multiplied by the
 // scale of their activation row and of their weight row before any epilogue.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS, bool F8 = false>
-__global__ __launch_bounds__(64 * WAVES_M *WAVES_N) void gemm_mfma_kernel(GemmArgs a, int tiles_m,
-                                                                          int tiles_n, int kt_per_split)
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS, bool F8>
+__device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, int tiles_n, int kt_per_split)
 {
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // wave tile
-    constexpr int MB = WM / 32, NB = WN / 32;             // 32x32 blocks per wave
-    static_assert(EPI != EPI_SWIGLU || NB % 2 == 0, "SwiGLU pairs two column blocks");
+    constexpr int MB = WM / 16, NB = WN / 16;             // 16x16 blocks per wave
+    static_assert(MB % 2 == 0 && NB % 2 == 0 && (EPI != EPI_SWIGLU || NB % 4 == 0), "column blocks go in pairs, of gate and up");
+    constexpr int NW = WAVES_M * WAVES_N;
+    using Ring = TileRing<BM, BN, NW, NS>;
+    constexpr int NSA = Ring::NSA, NSB = Ring::NSB, A_LD = Ring::A_LD, B_LD = Ring::B_LD, LD = Ring::LD;
+    constexpr unsigned SA = BM * BK * 2, SB = BN * BK * 2, B0 = NSA * SA;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
 
     // ---- tile id: contiguous ranges of tiles per XCD, 8-row bands inside ------------------------
     // A grouped launch has a row tile per group more than its rows may need.  Only the tiles in use are dealt: dealt
@@ -77,13 +138,11 @@ __global__ __launch_bounds__(64 * WAVES_M *WAVES_N) void gemm_mfma_kernel(GemmAr
     if ((int)blockIdx.x >= n_tiles) return;
     int pid = blockIdx.x;
     {
-        const int per = n_tiles / 8, rem = n_tiles % 8;
+        const int per = n_tiles / 8;
         if (per > 0) {
             // blocks are dealt to the 8 XCDs round-robin; give each XCD one contiguous range
-            int xcd = pid % 8, j = pid / 8;
-            if (j < per) pid = xcd * per + j;
-            else pid = 8 * per + (pid - 8 * per);   // leftover tiles keep their order
-            (void)rem;
+            const int xcd = pid % 8, j = pid / 8;
+            if (j < per) pid = xcd * per + j;       // the leftover tiles behind 8 * per keep their order
         }
     }
     int tm, tn;
@@ -122,273 +181,289 @@ __global__ __launch_bounds__(64 * WAVES_M *WAVES_N) void gemm_mfma_kernel(GemmAr
     const int col0 = tn * BN;
     // rows of (packed) B; a split-K launch of a SwiGLU GEMM works on the packed columns
     const int n_cols = (EPI == EPI_SWIGLU || (EPI == EPI_PARTIAL && a.epilogue == EPI_SWIGLU)) ? 2 * a.N : a.N;
-    const __bf16 *A = (const __bf16 *)a.A;
-    const __bf16 *B = (const __bf16 *)a.B + (size_t)group * a.b_group_stride;
+    const char *A = (const char *)a.A;
+    const char *B = (const char *)a.B + (size_t)group * a.b_group_stride * 2;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int kt0 = blockIdx.y * kt_per_split;
+    const int kt1 = min(a.K / BK, kt0 + kt_per_split);
 
-    // ---- loader: wave instruction i covers 8 rows x 128 bytes = 1 KB of LDS; lane l owns slot
-    //      (row = 8*blk + l/8, s = l%8) and fetches chunk s ^ swizzle(row) of that row ------------------
-    constexpr int NW = WAVES_M * WAVES_N;
-    constexpr int A_LD = BM / 8 / NW, B_LD = BN / 8 / NW;   // load instructions per wave
-    static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "loader mapping");
-    uint32_t a_off[A_LD], b_off[B_LD];
+    // ---- loader: a request of A covers 8 rows x 128 bytes = 1 KB of LDS, lane l owns slot (row = 8*blk + l/8,
+    //      s = l%8) and fetches chunk s ^ swizzle(row) of that row; a request of B is one packed block ------------
+    uint32_t off[LD];                                 // per-lane byte offsets; the k-tile is in the scalar offset
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
-        int r = (i * NW + wave) * 8 + (lane >> 3);
+        int r = (wave * A_LD + i) * 8 + (lane >> 3);
         int c = swz(r, lane & 7);
         int gr = row0 + r;
         if (gr >= row_end) gr = row_end - 1;          // clamp: loaded but never stored
         if (a.a_gather) gr = a.a_gather[gr];
-        a_off[i] = (uint32_t)gr * (uint32_t)(a.lda * 2) + c * 16;
+        off[i] = (uint32_t)gr * (uint32_t)(a.lda * 2) + c * 16;
     }
-    // B: instruction j = i*NW + wave moves packed block (row block j/2, k block j%2 of the tile)
     const int kblocks = a.K >> 5;                      // 32-k blocks per row block
     const int last_rb = (n_cols - 1) >> 4;
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
-        const int j = i * NW + wave;
+        const int j = wave * B_LD + i;                // row block j/2 of the tile, k block j%2
         int rb = (col0 >> 4) + (j >> 1);
         if (rb > last_rb) rb = last_rb;               // clamp: loaded but never stored
-        b_off[i] = ((uint32_t)rb * (uint32_t)kblocks + (j & 1)) * 1024u + lane * 16;
+        off[A_LD + i] = ((uint32_t)rb * (uint32_t)kblocks + (j & 1)) * 1024u + lane * 16;
     }
-    typedef const void __attribute__((address_space(1))) *gptr_t;
     typedef void __attribute__((address_space(3))) *lptr_t;
-    auto issue_loads = [&](int kt, unsigned char *st) {
-        const char *ab = (const char *)A + (size_t)kt * (BK * 2);
-        const char *bb = (const char *)B + (size_t)kt * 2048;   // two 1 KB k-blocks per tile
-#pragma unroll
-        for (int i = 0; i < A_LD; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(ab + a_off[i]),
-                                             (lptr_t)(st + (i * NW + wave) * 1024), 16, 0, 0);
-#pragma unroll
-        for (int i = 0; i < B_LD; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(bb + b_off[i]),
-                                             (lptr_t)(st + A_BYTES + (i * NW + wave) * 1024), 16, 0, 0);
+    // request D of k-tile ka of A into the stage at sa, or of k-tile kb of B into the one at sb.  Offsets reach 4 GiB
+    // (gemm_mfma_supported), past a tile's last row or block they are clamped above.
+    auto request = [&](auto D, int ka, unsigned sa, int kb, unsigned sb) {
+        constexpr int d = decltype(D)::value;
+        if constexpr (d < A_LD)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)A, 0, 0xffffffff, 0x00020000),
+                                                     (lptr_t)(smem + sa + (wave * A_LD + d) * 1024), 16, off[d],
+                                                     ka * (BK * 2), 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)B, 0, 0xffffffff, 0x00020000),
+                                                     (lptr_t)(smem + sb + (wave * B_LD + d - A_LD) * 1024), 16, off[d],
+                                                     kb * 2048, 0, 0);       // two 1 KB k-blocks per tile
     };
 
-    f32x16 acc[MB][NB];
+    // Accumulators beyond what 256 registers leave room for have to stay in the AGPR half of the file: with the builtins
+    // the compiler moved some of them back and forth inside the loop, in some epilogues' kernels up to 335 moves per
+    // k-tile (2300 -> 3000 clocks).  The MFMA as an asm statement on AGPR operands leaves it no choice.  The statements
+    // hide from the compiler that they are MFMAs, so the waits between a register's last vector write and the first
+    // MFMA, and between the last MFMA and the first read, are written out; inside the loop the operands come from LDS
+    // reads, whose counter the compiler keeps for asm operands too.
+    constexpr bool kAgpr = MB * NB > 32;
+    f32x4 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto pin_acc = [&]() {
+        if constexpr (kAgpr)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    const int kt0 = blockIdx.y * kt_per_split;
-    const int kt1 = min(a.K / BK, kt0 + kt_per_split);
-    // Software pipeline over NS LDS stages: the loads of k-tile kt + NS - 1 are issued while tile
-    // kt is multiplied, so up to NS - 1 tiles are in flight per workgroup.  Direct-to-LDS loads
-    // retire in order through this wave's vector-memory counter, so "tile kt has landed" is
-    // "at most (tiles issued after kt) * loads-per-tile still outstanding", followed by a barrier
-    // that makes every wave's part visible.  The same barrier orders the refill of the stage that
-    // was multiplied in the previous iteration.
-    constexpr int LPS = A_LD + B_LD;                  // load instructions per tile per wave
-    static_assert(LPS * (NS - 1) <= 63, "vector-memory counter range");
-    auto wait_tiles_after = [&](int tiles_after) {
-        // s_waitcnt vmcnt(n): n in bits [3:0] and [15:14]; expcnt / lgkmcnt fields left at "no wait"
-#define PD_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
-        if (NS >= 7 && tiles_after >= 5) PD_VMCNT((5 * LPS) & 63);
-        else if (NS >= 6 && tiles_after >= 4) PD_VMCNT((4 * LPS) & 63);
-        else if (NS >= 5 && tiles_after >= 3) PD_VMCNT((3 * LPS) & 63);
-        else if (NS >= 4 && tiles_after >= 2) PD_VMCNT(2 * LPS);
-        else if (NS >= 3 && tiles_after >= 1) PD_VMCNT(1 * LPS);
-        else PD_VMCNT(0);
-#undef PD_VMCNT
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) asm volatile("" : "+a"(acc[i][j]));
     };
-#pragma unroll
-    for (int s = 0; s < NS - 1; ++s)
-        if (kt0 + s < kt1) issue_loads(kt0 + s, smem + s * STAGE);
-    if (NS == 2) __syncthreads();
 
-    // fragment addresses inside a stage: row and the two chunk parities of this lane
-    const int frow = lane & 31, fhalf = lane >> 5;
-    // Fragment reads of one 16-wide k-step, then its MFMAs; with two waves per SIMD the other
-    // wave's matrix work covers this wave's LDS latency (measured: explicit register double
-    // buffering of the fragments changes nothing).
-    auto load_frags = [&](const unsigned char *st, int kk, bf16x8 (&fa)[MB], bf16x8 (&fb)[NB]) {
-        const int c = kk * 2 + fhalf;
+    // ---- fragments.  bf16: set h holds k half h of the tile.  F8: whole operands, their 16-byte parts the two
+    //      halves; two sets of B's -----------------------------------------------------------------------------------
+    const int fr = lane & 15, kg = lane >> 4;
+    bf16x8 xf[2][MB], wf[2][NB];                      // bf16
+    i32x8 x8[MB], w8[2][NB];                          // F8
+    const unsigned char *xa[2];
 #pragma unroll
-        for (int i = 0; i < MB; ++i) {
-            int r = wm * WM + i * 32 + frow;
-            fa[i] = *(const bf16x8 *)(st + r * 128 + swz(r, c) * 16);
+    for (int h = 0; h < 2; ++h) xa[h] = smem + (wm * WM + fr) * 128 + swz(fr, 4 * h + kg) * 16;
+    const unsigned char *wa = smem + wn * NB * 2048 + lane * 16;
+    auto half_into = [&](i32x8 &r, const unsigned char *from, auto H) {
+        const i32x4 t = *(const i32x4 *)from;
+        const i32x8 w = __builtin_shufflevector(t, t, 0, 1, 2, 3, -1, -1, -1, -1);
+        if constexpr (decltype(H)::value == 0) r = w;
+        else r = __builtin_shufflevector(r, w, 0, 1, 2, 3, 8, 9, 10, 11);
+    };
+    auto read_x = [&](auto I, auto H, unsigned sa) {
+        constexpr int i = decltype(I)::value, h = decltype(H)::value;
+        if constexpr (F8) half_into(x8[i], xa[h] + sa + i * 2048, H);
+        else xf[h][i] = *(const bf16x8 *)(xa[h] + sa + i * 2048);
+    };
+    auto read_w = [&](auto J, auto H, auto S, unsigned sb) {
+        constexpr int j = decltype(J)::value, h = decltype(H)::value;
+        if constexpr (F8) half_into(w8[decltype(S)::value][j], wa + sb + j * 2048 + h * 1024, H);
+        else wf[h][j] = *(const bf16x8 *)(wa + sb + j * 2048 + h * 1024);
+    };
+    constexpr std::integral_constant<int, 0> c0{};
+    constexpr std::integral_constant<int, 1> c1{};
+    // Fragment reads of a half, in the order in which the MFMAs want them.  The second half's are of the same tile;
+    // the first half's (FIRST) of the next one, for F8 with B's whole tile into set S.
+    constexpr int N_FIRST = F8 ? MB + 2 * NB : MB + NB, N_SECOND = F8 ? MB : MB + NB;
+    auto read_frag = [&](auto FIRST, auto R, auto S, unsigned sa, unsigned sb) {
+        constexpr int r = decltype(R)::value;
+        if constexpr (F8) {
+            if constexpr (!decltype(FIRST)::value) read_x(std::integral_constant<int, MB / 2 + r / 2>{}, std::integral_constant<int, r % 2>{}, sa);
+            else if constexpr (r < 2) read_x(c0, R, sa);
+            else if constexpr (r < 2 + 2 * NB) read_w(std::integral_constant<int, (r - 2) / 2>{}, std::integral_constant<int, r % 2>{}, S, sb);
+            else read_x(std::integral_constant<int, (r - 2 * NB) / 2>{}, std::integral_constant<int, r % 2>{}, sa);
+        } else {
+            constexpr std::integral_constant<int, decltype(FIRST)::value ? 0 : 1> h{};
+            if constexpr (r == 0) read_x(c0, h, sa);
+            else if constexpr (r <= NB) read_w(std::integral_constant<int, r - 1>{}, h, c0, sb);
+            else read_x(std::integral_constant<int, r - NB>{}, h, sa);
         }
+    };
+    constexpr int NM = F8 ? MB / 2 * NB : MB * NB;    // MFMAs of a half, of 32 and of 16 clocks
+    // the weights are the MFMA's A operand: a lane then holds four consecutive columns of one row of C
+    auto mma = [&](auto Mi, auto H, auto S) {
+        constexpr int m = decltype(Mi)::value, h = decltype(H)::value, s = decltype(S)::value;
+        constexpr int ii = m / NB, j = ii % 2 ? NB - 1 - m % NB : m % NB;
+        constexpr int i = F8 ? h * (MB / 2) + ii : ii;
+        if constexpr (F8 && kAgpr) mfma_agpr(acc[i][j], w8[s][j], x8[i]);
+        else if constexpr (F8) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(w8[s][j], x8[i], acc[i][j], 0, 0, 0, 0, 0, 0);
+        else if constexpr (kAgpr) mfma_agpr(acc[i][j], wf[h][j], xf[h][i]);
+        else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][j], xf[h][i], acc[i][j], 0, 0, 0);
+    };
+
+    // ---- k-loop.  The barrier stands between the halves of k-tile kt.  Ahead of it every wave has read all it needs of
+    //      tile kt's stages and waited for its own requests of tile kt + 1, so behind it those stages take the next
+    //      requests (a round: tile kt + NSA of A, kt + NSB of B, in this order, the last of them behind the other half of
+    //      the next iteration) and tile kt + 1 may be read.  Direct-to-LDS loads retire in order through the wave's
+    //      vector-memory counter, so "tile kt + 1 has landed" is "at most WAIT requests outstanding": all of the rounds
+    //      behind the one that asked for it, and, with a further stage of B, that round's own requests of B.  Past the last
+    //      tile the last one is requested again, so that the counts stay the same to the end.
+#define PD_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
+#define PD_VMCNT_LGKM0(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (((n) >> 4) << 14))
+    constexpr int D1 = Ring::issued(64);              // requests of a round ahead of the iteration's end
+    constexpr int WAIT = (NSA - 2) * LD + (NSB > NSA ? B_LD : 0);
+    static_assert(NSA >= 2 && WAIT + LD <= 63, "vector-memory counter range");
+    static_for<NSB - 1>([&](auto R) {
+        constexpr int ta = decltype(R)::value - NSB + NSA, tb = decltype(R)::value;
+        static_for<LD>([&](auto D) {
+            if constexpr (decltype(D)::value >= A_LD || ta >= 0) request(D, min(kt0 + ta, kt1 - 1), ta * SA, min(kt0 + tb, kt1 - 1), B0 + tb * SB);
+        });
+    });
+    int kap = min(kt0 + NSA - 1, kt1 - 1), kbp = min(kt0 + NSB - 1, kt1 - 1);    // the round under way
+    unsigned sap = (NSA - 1) * SA, sbp = B0 + (NSB - 1) * SB;
+    static_for<D1>([&](auto D) { request(D, kap, sap, kbp, sbp); });
+    PD_VMCNT(WAIT + D1);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    static_for<N_FIRST>([&](auto R) { read_frag(c1, R, c0, 0u, B0); });
+    unsigned sa = 0, sb = B0;
+    pin_acc();
+    if constexpr (kAgpr) asm volatile("s_nop 7");
+    auto k_tile = [&](int kt, auto S) {
+        constexpr int s = decltype(S)::value;
+        static_for<NM>([&](auto Mi) {
+            constexpr int m = decltype(Mi)::value;
+            constexpr int d0 = m == 0 ? D1 : Ring::issued(64 + m * 64 / NM), d1 = m == NM - 1 ? LD : Ring::issued(64 + (m + 1) * 64 / NM);
+            constexpr int r0 = Ring::reads(m, NM, N_SECOND), r1 = Ring::reads(m + 1, NM, N_SECOND);
+            static_for<d1 - d0>([&](auto O) { request(std::integral_constant<int, d0 + decltype(O)::value>{}, kap, sap, kbp, sbp); });
+            static_for<r1 - r0>([&](auto O) { read_frag(c0, std::integral_constant<int, r0 + decltype(O)::value>{}, c0, sa, sb); });
+            mma(Mi, c0, S);
+            __builtin_amdgcn_sched_barrier(0);        // the stream stays in this order
+        });
+        PD_VMCNT_LGKM0(WAIT);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned sa1 = sa + SA == NSA * SA ? 0u : sa + SA, sb1 = sb + SB == B0 + NSB * SB ? B0 : sb + SB;
+        kap = min(kt + NSA, kt1 - 1);
+        kbp = min(kt + NSB, kt1 - 1);
+        sap = sa;
+        sbp = sb;
+        static_for<NM>([&](auto Mi) {
+            constexpr int m = decltype(Mi)::value;
+            constexpr int d0 = m == 0 ? 0 : Ring::issued(m * 64 / NM), d1 = m == NM - 1 ? D1 : Ring::issued((m + 1) * 64 / NM);
+            constexpr int r0 = Ring::reads(m, NM, N_FIRST), r1 = Ring::reads(m + 1, NM, N_FIRST);
+            static_for<d1 - d0>([&](auto O) { request(std::integral_constant<int, d0 + decltype(O)::value>{}, kap, sap, kbp, sbp); });
+            static_for<r1 - r0>([&](auto O) {
+                read_frag(c1, std::integral_constant<int, r0 + decltype(O)::value>{}, std::integral_constant<int, F8 ? 1 - s : 0>{}, sa1, sb1);
+            });
+            mma(Mi, c1, S);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        sa = sa1;
+        sb = sb1;
+    };
+    if constexpr (F8) {
+        for (int kt = kt0; kt < kt1; kt += 2) {       // two register sets of B's fragments
+            k_tile(kt, c0);
+            if (kt + 1 < kt1) k_tile(kt + 1, c1);
+        }
+    } else {
+        for (int kt = kt0; kt < kt1; ++kt) k_tile(kt, c0);
+    }
+    PD_VMCNT(0);                                      // the repeated requests: none may outlive the workgroup's LDS
+    if constexpr (kAgpr) asm volatile("s_nop 15\n\ts_nop 15");
+    pin_acc();
+#undef PD_VMCNT
+#undef PD_VMCNT_LGKM0
+
+    // ---- epilogue: lane holds row (lane % 16) of each block, columns 4*(lane/16) .. +3 -------------------------
+    if constexpr (F8) {
+        f32x4 sbv[NB];
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-            // column wn*WN + 32j + frow, k chunk c of the tile, in the linear packed blocks
-            const int rbl = ((wn * WN + j * 32) >> 4) + (frow >> 4);
-            fb[j] = *(const bf16x8 *)(st + A_BYTES + (rbl * 2 + (c >> 2)) * 1024 + (c & 3) * 256 + (frow & 15) * 16);
+            // columns past the last block (a multiple of 16 of them exist) are not stored
+            const int n = min(col0 + wn * WN + j * 16, n_cols - 16) + 4 * kg;
+            sbv[j] = *(const f32x4 *)(a.b_scale + (size_t)group * n_cols + n);
         }
-    };
-    auto mma = [&](bf16x8 (&fa)[MB], bf16x8 (&fb)[NB]) {
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < MB; ++i) {
+            int mr = min(row0 + wm * WM + i * 16 + fr, row_end - 1);
+            if (a.a_gather) mr = a.a_gather[mr];        // the scale belongs to the row the codes came from
+            const float sav = a.a_scale[mr];
 #pragma unroll
             for (int j = 0; j < NB; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    };
-    auto compute = [&](const unsigned char *st) {
-        if (F8) {
 #pragma unroll
-            for (int kk = 0; kk < BK / 16; kk += 2) {
-                bf16x8 fa[2][MB], fb[2][NB];
-                load_frags(st, kk, fa[0], fb[0]);
-                load_frags(st, kk + 1, fa[1], fb[1]);
-                i32x8 pb[NB];
-#pragma unroll
-                for (int j = 0; j < NB; ++j) pb[j] = cat32(fb[0][j], fb[1][j]);
-#pragma unroll
-                for (int i = 0; i < MB; ++i) {
-                    const i32x8 pa = cat32(fa[0][i], fa[1][i]);
-#pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(pa, pb[j], acc[i][j], 0, 0, 0, 0, 0, 0);
-                }
-            }
-            return;
-        }
-#pragma unroll
-        for (int kk = 0; kk < BK / 16; ++kk) {
-            bf16x8 fa[MB], fb[NB];
-            load_frags(st, kk, fa, fb);
-            mma(fa, fb);
-        }
-    };
-    if (NS == 2) {
-        // double buffer: the barrier that ends an iteration also waits for the loads issued at its
-        // start; the compiler may sink trailing MFMAs below it, which hides the barrier wait
-        for (int kt = kt0; kt + 1 < kt1; ++kt) {
-            issue_loads(kt + 1, smem + ((kt + 1 - kt0) & 1) * STAGE);
-            __builtin_amdgcn_sched_barrier(0);     // keep the loads ahead of the compute phase
-            compute(smem + ((kt - kt0) & 1) * STAGE);
-            __syncthreads();
-        }
-        compute(smem + ((kt1 - 1 - kt0) & 1) * STAGE);
-    } else {
-        for (int kt = kt0; kt < kt1; ++kt) {
-            const int issued_after = min(NS - 2, kt1 - 1 - kt);   // tiles already issued beyond kt
-            wait_tiles_after(issued_after);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            if (kt + NS - 1 < kt1) issue_loads(kt + NS - 1, smem + ((kt + NS - 1 - kt0) % NS) * STAGE);
-            __builtin_amdgcn_sched_barrier(0);     // keep the loads ahead of the compute phase
-            compute(smem + ((kt - kt0) % NS) * STAGE);
+                for (int r = 0; r < 4; ++r) acc[i][j][r] *= sav * sbv[j][r];
         }
     }
-
-    // ---- epilogue: lane holds column (lane % 32) of each block; register r is row
-    //      8*(r/4) + 4*(lane/32) + r%4 ----------------------------------------------------------------
-    if (F8) {
-        float sb[NB];
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-            sb[j] = a.b_scale[(size_t)group * n_cols + min(col0 + wn * WN + j * 32 + frow, n_cols - 1)];
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = row0 + wm * WM + i * 32 + 8 * (r >> 2) + 4 * fhalf + (r & 3);
-                int mr = min(m, row_end - 1);
-                if (a.a_gather) mr = a.a_gather[mr];        // the scale belongs to the row the codes came from
-                const float sa = a.a_scale[mr];
-#pragma unroll
-                for (int j = 0; j < NB; ++j) acc[i][j][r] *= sa * sb[j];
-            }
-    }
-    if (EPI == EPI_PARTIAL) {
+    if constexpr (EPI == EPI_PARTIAL) {
         float *P = a.splitk_ws + (size_t)blockIdx.y * a.M * n_cols;
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < MB; ++i) {
+            const int m = row0 + wm * WM + i * 16 + fr;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = row0 + wm * WM + i * 32 + 8 * (r >> 2) + 4 * fhalf + (r & 3);
-                if (m >= row_end) continue;
-#pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    const int n = col0 + wn * WN + j * 32 + frow;
-                    if (n < n_cols) P[(size_t)m * n_cols + n] = acc[i][j][r];
-                }
+            for (int j = 0; j < NB; ++j) {
+                const int n = col0 + wn * WN + j * 16 + 4 * kg;
+                if (m < row_end && n < n_cols) *(f32x4 *)(P + (size_t)m * n_cols + n) = acc[i][j];
             }
+        }
         return;
     }
     uint16_t *C = (uint16_t *)a.C;
     const uint16_t *R = (const uint16_t *)a.R;
-    // Row-contiguous stores: the accumulators hold one column per lane, which would make every store
-    // (and residual load) a 2-byte access.  Each wave instead passes its 32-row blocks through a
-    // private 8 KB of the (now idle) operand stages as fp32 and reads them back with 4 consecutive
-    // columns per lane, so a wave instruction moves whole 128-byte row segments; the residual is
-    // added in fp32 before the one rounding to bf16.
-    constexpr bool kStage = WN == 64 && NB == 2;
-    if (kStage && a.N % 4 == 0 && a.ldc % 4 == 0 && (EPI != EPI_RESIDUAL || a.ldr % 4 == 0)) {
-        constexpr int OC = EPI == EPI_SWIGLU ? 32 : 64;   // output columns of a staged block
-        constexpr int LPR = OC / 4, RPI = 64 / LPR;      // lanes per row, rows per wave instruction
-        __syncthreads();                                  // every wave is done with the operand stages
-        float *stg = (float *)smem + wave * 2048;
-        const int out_col0 = EPI == EPI_SWIGLU ? ((col0 + wn * WN) >> 6) * 32 : col0 + wn * WN;
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = 8 * (r >> 2) + 4 * fhalf + (r & 3);
-                if (EPI == EPI_SWIGLU) {
-                    stg[row * OC + frow] = silu_fast(acc[i][0][r]) * acc[i][1][r];
-                } else {
-                    stg[row * OC + frow] = acc[i][0][r];
-                    stg[row * OC + 32 + frow] = acc[i][1][r];
-                }
-            }
-#pragma unroll
-            for (int it = 0; it < 32 / RPI; ++it) {
-                const int row = it * RPI + lane / LPR, cg = (lane % LPR) * 4;
-                const f32x4 v = *(const f32x4 *)(stg + row * OC + cg);
-                const int m = row0 + wm * WM + i * 32 + row, n = out_col0 + cg;
-                if (m < row_end && n < a.N) {
-                    float o0 = v[0], o1 = v[1], o2 = v[2], o3 = v[3];
-                    if (EPI == EPI_RESIDUAL) {
-                        const uint2 rr = *(const uint2 *)(R + (size_t)m * a.ldr + n);
-                        o0 += bfbits2f(rr.x & 0xffffu); o1 += bfbits2f(rr.x >> 16);
-                        o2 += bfbits2f(rr.y & 0xffffu); o3 += bfbits2f(rr.y >> 16);
-                    }
-                    uint2 o;
-                    o.x = pack2bf(o0, o1);
-                    o.y = pack2bf(o2, o3);
-                    *(uint2 *)(C + (size_t)m * a.ldc + n) = o;
-                }
-            }
-        }
-        return;
-    }
+    // Two neighbouring blocks of 16 columns: the lane groups 4*(lane/16) exchange a block's half in pairs, after which
+    // a lane holds 8 consecutive columns of one block and stores (and loads the residual) 16 bytes; the residual is
+    // added in fp32 ahead of the one rounding to bf16.
+    constexpr int OB = EPI == EPI_SWIGLU ? NB / 2 : NB;   // output blocks of the wave
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
+        const int m = row0 + wm * WM + i * 16 + fr;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int m = row0 + wm * WM + i * 32 + 8 * (r >> 2) + 4 * fhalf + (r & 3);
-            if (m >= row_end) continue;
-            if (EPI == EPI_SWIGLU) {
+        for (int o = 0; o < OB; o += 2) {
+            float v[8];                                   // the lane's four columns of block o, then of block o + 1
 #pragma unroll
-                for (int j = 0; j < NB; j += 2) {
-                    const int np = col0 + wn * WN + j * 32;       // packed column of the gate block
-                    const int f = (np >> 6) * 32 + frow;
-                    if (f < a.N) {
-                        float v = silu_fast(acc[i][j][r]) * acc[i][j + 1][r];
-                        C[(size_t)m * a.ldc + f] = f2bf(v).x;
-                    }
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if constexpr (EPI == EPI_SWIGLU) v[4 * b + r] = silu_fast(acc[i][2 * o + b][r]) * acc[i][2 * o + 2 + b][r];
+                    else v[4 * b + r] = acc[i][o + b][r];
                 }
+            // lane group kg: block o + kg % 2, columns 8 * (kg / 2) .. +7
+            const int n = (EPI == EPI_SWIGLU ? (col0 + wn * WN) / 2 : col0 + wn * WN) + (o + (kg & 1)) * 16 + 8 * (kg >> 1);
+            const bool in = m < row_end && n < a.N;
+            uint4 out;
+            if constexpr (EPI == EPI_RESIDUAL) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[r]), __float_as_uint(v[4 + r]), false, false);
+                    v[r] = __uint_as_float(p[0]);
+                    v[4 + r] = __uint_as_float(p[1]);
+                }
+                uint4 rr = make_uint4(0, 0, 0, 0);
+                if (in) rr = *(const uint4 *)(R + (size_t)m * a.ldr + n);
+                out.x = pack2bf(v[0] + bfbits2f(rr.x & 0xffffu), v[1] + bfbits2f(rr.x >> 16));
+                out.y = pack2bf(v[2] + bfbits2f(rr.y & 0xffffu), v[3] + bfbits2f(rr.y >> 16));
+                out.z = pack2bf(v[4] + bfbits2f(rr.z & 0xffffu), v[5] + bfbits2f(rr.z >> 16));
+                out.w = pack2bf(v[6] + bfbits2f(rr.w & 0xffffu), v[7] + bfbits2f(rr.w >> 16));
             } else {
-#pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    const int n = col0 + wn * WN + j * 32 + frow;
-                    if (n < a.N) {
-                        float v = acc[i][j][r];
-                        if (EPI == EPI_RESIDUAL) v += bfbits2f(R[(size_t)m * a.ldr + n]);
-                        C[(size_t)m * a.ldc + n] = f2bf(v).x;
-                    }
-                }
+                auto p = __builtin_amdgcn_permlane16_swap(pack2bf(v[0], v[1]), pack2bf(v[4], v[5]), false, false);
+                auto q = __builtin_amdgcn_permlane16_swap(pack2bf(v[2], v[3]), pack2bf(v[6], v[7]), false, false);
+                out = make_uint4(p[0], q[0], p[1], q[1]);
             }
+            if (in) *(uint4 *)(C + (size_t)m * a.ldc + n) = out;
         }
     }
+}
+
+// Tiles of up to 256 x 128 stay inside 256 registers; asked to, the compiler leaves the AGPRs (and moves to and from them)
+// alone.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS, bool F8 = false>
+__global__ __launch_bounds__(64 * WAVES_M *WAVES_N, BM *BN > 256 * 128 ? 1 : 2) void gemm_mfma_kernel(GemmArgs a, int tiles_m, int tiles_n,
+                                                                                                   int kt_per_split)
+{
+    gemm_mfma_body<BM, BN, WAVES_M, WAVES_N, EPI, NS, F8>(a, tiles_m, tiles_n, kt_per_split);
 }
 
 // out = epilogue(sum over splits of the fp32 partials); 4 consecutive output columns per thread.
@@ -544,13 +619,13 @@ bool gemm_mfma_supported(const GemmArgs &a)
     return true;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int NS = 2, bool F8 = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NS, bool F8 = false>
 static hipError_t launch_cfg(const GemmArgs &a, hipStream_t s, int splits = 1)
 {
     const int n_cols = a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N;
     const int tiles_n = (n_cols + BN - 1) / BN;
     const int tiles_m = (a.M + BM - 1) / BM + (a.group_offsets ? a.n_groups : 0);
-    const size_t smem = NS * (size_t)(BM + BN) * BK * 2;
+    constexpr size_t smem = TileRing<BM, BN, WAVES_M * WAVES_N, NS>::lds;
     const int nk = a.K / BK;
     const int kt_per = (nk + splits - 1) / splits;
     splits = (nk + kt_per - 1) / kt_per;               // no empty split
@@ -654,7 +729,7 @@ static TilePlan plan_tiles(const GemmArgs &a)
     } forms[] = {{TILE_256, 256, 256, 256, 3.7, 1.626, 1.211},
                  {TILE_192, 192, 256, 256, 2.6, 1.348, 1.107},
                  {TILE_128_PAIR, 128, 128, 512, 0.85, 1.053, 0.62},          // two workgroups per CU
-                 {TILE_128_DEEP, 128, 128, 256, 0.0, 0.636, 0.486}};         // eight waves, alone on its CU with a four-stage ring
+                 {TILE_128_DEEP, 128, 128, 256, 0.0, 0.636, 0.486}};         // alone on its CU with a four-stage ring
     for (const auto &f : forms) {
         const long long tiles = (long long)ceil(row_tiles(a, f.bm) * ((n_cols + f.bn - 1) / f.bn));
         for (int sp = 1; sp <= 8; ++sp) {
@@ -712,18 +787,11 @@ static hipError_t launch_planned(const GemmArgs &a, hipStream_t s)
 {
     const TilePlan p = plan_tiles(a);
     switch (p.form) {
-    case TILE_192: return launch_cfg<192, 256, 2, 4, 2, F8>(a, s, p.splits);
+    case TILE_192: return launch_cfg<192, 256, 2, 2, 2, F8>(a, s, p.splits);
     case TILE_128_PAIR: return launch_cfg<128, 128, 2, 2, 2, F8>(a, s, p.splits);
-    case TILE_128_DEEP: return launch_cfg<128, 128, 4, 2, 4, F8>(a, s, p.splits);
-    default: break;
+    case TILE_128_DEEP: return launch_cfg<128, 128, 2, 2, 4, F8>(a, s, p.splits);
+    default: return launch_cfg<256, 256, 2, 2, 2, F8>(a, s, p.splits);
     }
-    // 8 waves (two per SIMD hide each other's stalls) or 16, which halve what a wave does before and behind its k-tiles:
-    // worth more the fewer k-tiles there are, more where the epilogue also reads a residual, and always with codes, whose
-    // k-tiles are as long but half as many.  8 -> 16 waves, us, at 4096 rows: codes O (K = 4096) 91 -> 84, gate/up 418 -> 405;
-    // bf16 residual K = 1024 39 -> 33, 4096 139 -> 132, 5120 295 -> 280, 14336 408 -> 407; bf16 plain K = 1024 32 -> 29, 2048
-    // 56 -> 55, 3072 164 -> 163, 4096 (8192 rows) 352 -> 354, 8192 626 -> 639; SwiGLU 1 - 3 % slower from K = 2048 on
-    if (F8 || (a.epilogue == EPI_RESIDUAL && a.K <= 4096) || (a.epilogue == EPI_NONE && a.K <= 2048)) return launch_cfg<256, 256, 4, 4, 2, F8>(a, s, p.splits);
-    return launch_cfg<256, 256, 2, 4, 2, F8>(a, s, p.splits);
 }
 
 hipError_t launch_gemm_mfma_f8(const GemmArgs &a, hipStream_t s)
@@ -740,14 +808,14 @@ hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s)
     const int n_cols = a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N;
     const bool wide = n_cols >= 16384;                            // enough column tiles without splitting K
     if (rows > 128) {
-        if (wide) return launch_cfg<256, 128, 4, 2, 3>(a, s, 1);
-        return launch_cfg<256, 64, 8, 1, 3>(a, s, choose_splits(a, 256, 64));
+        if (wide) return launch_cfg<256, 128, 2, 2, 3>(a, s, 1);
+        return launch_cfg<256, 64, 4, 1, 4>(a, s, choose_splits(a, 256, 64));
     }
     if (rows > 64) {
-        if (wide) return launch_cfg<128, 128, 2, 2, 3>(a, s, 1);     // measured 52 vs 62 us on the gate/up shape
-        return launch_cfg<128, 64, 4, 1, 4>(a, s, choose_splits(a, 128, 64));
+        if (wide) return launch_cfg<128, 128, 2, 2, 4>(a, s, 1);
+        return launch_cfg<128, 64, 4, 1, 6>(a, s, choose_splits(a, 128, 64));
     }
-    return launch_cfg<64, 128, 2, 2, 4>(a, s, wide ? 1 : choose_splits(a, 64, 128));
+    return launch_cfg<64, 128, 2, 2, 6>(a, s, wide ? 1 : choose_splits(a, 64, 128));
 }
 
 }  // namespace pd
