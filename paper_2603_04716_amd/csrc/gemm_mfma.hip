@@ -35,6 +35,7 @@
 // a fixed order and applies the epilogue (deterministic, no atomics).
 #include <string.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -51,7 +52,13 @@ constexpr int BK = 64;  // k per tile: 8 chunks of 16 bytes per row
 
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
 
-__device__ __forceinline__ float silu_fast(float z) { return z / (1.0f + __expf(-z)); }
+// z / (1 + exp(-z)): the quotient by the hardware reciprocal and one correction from its remainder, which is the
+// division's result without its scaling steps (the divisor lies in 1 .. 2^127; the exponent stops where it would overflow)
+__device__ __forceinline__ float silu_fast(float z)
+{
+    const float d = 1.0f + __expf(fminf(-z, 87.0f)), r = __builtin_amdgcn_rcpf(d), q = z * r;
+    return fmaf(fmaf(-d, q, z), r, q);
+}
 
 // acc += w x with acc in AGPRs
 __device__ __forceinline__ void mfma_agpr(f32x4 &acc, const bf16x8 &w, const bf16x8 &x)
@@ -75,21 +82,20 @@ __device__ __forceinline__ void static_for(F f)
     if constexpr (N > 0) static_for_seq(f, std::make_integer_sequence<int, N>{});
 }
 
-// Stages and schedule of a tile form.  LDS holds NSA stages of the A tile and NSB of the B tile.  Positions are in
-// 64ths of half a k-tile, counted from the barrier: A's requests are spread over PA of them, B's over the PB behind; the
-// fragment reads of a half over the first RS.
+// Stages and schedule of a tile form.  LDS holds NS stages of the A tile, and of the B tile as many as the rest of the
+// workgroup's share (a CU's 160 KB, or half of it) takes: the weights come from HBM, the rows mostly from an L2, so what
+// can be requested further ahead is the weights.  Positions are in 64ths of half a k-tile, counted from the barrier: A's
+// requests are spread over PA of them, B's over the PB behind; the fragment reads of a half over the first RS.
 template <int BM, int BN, int WAVES, int NS>
 struct TileRing {
-    // two stages: the third of B's that the 160 KB leave room for lets B's requests run a tile ahead, so that only A's have
-    // to land within the tile
-    static constexpr bool deep = NS == 2 && BN == 256;
-    static constexpr int NSA = NS, NSB = deep ? 3 : NS;
+    static constexpr bool pair = BM * BN <= 128 * 128 && NS == 2;     // two workgroups share a CU
+    static constexpr int share = (pair ? 80 : 160) * 1024, SA = BM * BK * 2, SB = BN * BK * 2;
+    static constexpr int NSA = NS, NSB = (share - NSA * SA) / SB < 8 ? (share - NSA * SA) / SB : 8;
     static constexpr int A_LD = BM / 8 / WAVES, B_LD = BN / 8 / WAVES, LD = A_LD + B_LD;   // requests of a wave per k-tile
-    static constexpr int span = deep ? 120 : NS == 2 ? 72 : 120;
-    static constexpr int PA = deep ? 48 : span * A_LD / LD, PB = span - PA;
+    static constexpr int PA = 48, PB = 72;
     static constexpr int RS = BM * BN >= 256 * 192 ? 48 : 28;
-    static constexpr size_t lds = (size_t)(NSA * BM + NSB * BN) * BK * 2;
-    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    static constexpr size_t lds = (size_t)(NSA * SA + NSB * SB);
+    static_assert(NSB > NSA || (NSA == 2 && NSB == 2), "B at least as far ahead as A");
     static_assert(BM % (8 * WAVES) == 0 && BN % (8 * WAVES) == 0, "loader mapping");
     // requests issued ahead of position p
     static constexpr int issued(int p)
@@ -118,11 +124,11 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
 {
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // wave tile
     constexpr int MB = WM / 16, NB = WN / 16;             // 16x16 blocks per wave
-    static_assert(MB % 2 == 0 && NB % 2 == 0 && (EPI != EPI_SWIGLU || NB % 4 == 0), "column blocks go in pairs, of gate and up");
+    static_assert((!F8 || MB % 2 == 0) && NB % (EPI == EPI_SWIGLU ? 4 : 2) == 0, "blocks go in pairs, gate and up in pairs of pairs");
     constexpr int NW = WAVES_M * WAVES_N;
     using Ring = TileRing<BM, BN, NW, NS>;
     constexpr int NSA = Ring::NSA, NSB = Ring::NSB, A_LD = Ring::A_LD, B_LD = Ring::B_LD, LD = Ring::LD;
-    constexpr unsigned SA = BM * BK * 2, SB = BN * BK * 2, B0 = NSA * SA;
+    constexpr unsigned SA = Ring::SA, SB = Ring::SB, B0 = NSA * SA;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     // ---- tile id: contiguous ranges of tiles per XCD, 8-row bands inside ------------------------
@@ -136,53 +142,45 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
     }
     const int n_tiles = tiles_m * tiles_n;
     if ((int)blockIdx.x >= n_tiles) return;
-    int pid = blockIdx.x;
-    {
+    struct Tile {
+        int row0, row_end, col0, group;
+    };
+    auto tile_at = [&](int pid) {
         const int per = n_tiles / 8;
         if (per > 0) {
             // blocks are dealt to the 8 XCDs round-robin; give each XCD one contiguous range
             const int xcd = pid % 8, j = pid / 8;
             if (j < per) pid = xcd * per + j;       // the leftover tiles behind 8 * per keep their order
         }
-    }
-    int tm, tn;
-    {
         constexpr int GM = 8;
-        int band = pid / (GM * tiles_n);
-        int first = band * GM;
-        int rows = tiles_m - first < GM ? tiles_m - first : GM;
-        int in = pid - band * GM * tiles_n;
-        tm = first + in % rows;
-        tn = in / rows;
-    }
-
-    // ---- rows of this tile (virtual m-tiles map to groups for the grouped GEMM) -----------------
-    int row0, row_end, group = 0;
-    if (a.group_offsets) {
-        int acc = 0;
-        row0 = -1;
-        row_end = 0;
-        for (int g = 0; g < a.n_groups; ++g) {
-            int lo = a.group_offsets[g], hi = a.group_offsets[g + 1];
-            int nt = (hi - lo + BM - 1) / BM;
-            if (tm < acc + nt) {
-                group = g;
-                row0 = lo + (tm - acc) * BM;
-                row_end = hi;
-                break;
+        const int band = pid / (GM * tiles_n);
+        const int first = band * GM;
+        const int rows = tiles_m - first < GM ? tiles_m - first : GM;
+        const int in = pid - band * GM * tiles_n;
+        const int tm = first + in % rows;
+        Tile t;
+        t.col0 = in / rows * BN;
+        t.row0 = tm * BM;
+        t.row_end = a.M;
+        t.group = 0;
+        if (a.group_offsets) {                        // virtual m-tiles map to groups
+            int acc = 0;
+            for (int g = 0; g < a.n_groups; ++g) {
+                const int lo = a.group_offsets[g], hi = a.group_offsets[g + 1];
+                const int nt = (hi - lo + BM - 1) / BM;
+                if (tm < acc + nt) {
+                    t.group = g;
+                    t.row0 = lo + (tm - acc) * BM;
+                    t.row_end = hi;
+                    break;
+                }
+                acc += nt;
             }
-            acc += nt;
         }
-        if (row0 < 0) return;
-    } else {
-        row0 = tm * BM;
-        row_end = a.M;
-    }
-    const int col0 = tn * BN;
+        return t;
+    };
     // rows of (packed) B; a split-K launch of a SwiGLU GEMM works on the packed columns
     const int n_cols = (EPI == EPI_SWIGLU || (EPI == EPI_PARTIAL && a.epilogue == EPI_SWIGLU)) ? 2 * a.N : a.N;
-    const char *A = (const char *)a.A;
-    const char *B = (const char *)a.B + (size_t)group * a.b_group_stride * 2;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -192,36 +190,58 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
 
     // ---- loader: a request of A covers 8 rows x 128 bytes = 1 KB of LDS, lane l owns slot (row = 8*blk + l/8,
     //      s = l%8) and fetches chunk s ^ swizzle(row) of that row; a request of B is one packed block ------------
-    uint32_t off[LD];                                 // per-lane byte offsets; the k-tile is in the scalar offset
+    // A lane's offsets from the tile's first row and column block stay the same from tile to tile; the tile's place is in
+    // the (scalar) base, the k-tile in the scalar offset, and the buffer ends with the tile's last row or block, so rows
+    // and columns past it read as zeros (they are never stored).  Gathered rows have offsets of their own per tile.
+    uint32_t off[LD];
+    const int kblocks = a.K >> 5;                      // 32-k blocks per row block
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
-        int r = (wave * A_LD + i) * 8 + (lane >> 3);
-        int c = swz(r, lane & 7);
-        int gr = row0 + r;
-        if (gr >= row_end) gr = row_end - 1;          // clamp: loaded but never stored
-        if (a.a_gather) gr = a.a_gather[gr];
-        off[i] = (uint32_t)gr * (uint32_t)(a.lda * 2) + c * 16;
+        const int r = (wave * A_LD + i) * 8 + (lane >> 3);
+        off[i] = (uint32_t)r * (uint32_t)(a.lda * 2) + swz(r, lane & 7) * 16;
     }
-    const int kblocks = a.K >> 5;                      // 32-k blocks per row block
-    const int last_rb = (n_cols - 1) >> 4;
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
         const int j = wave * B_LD + i;                // row block j/2 of the tile, k block j%2
-        int rb = (col0 >> 4) + (j >> 1);
-        if (rb > last_rb) rb = last_rb;               // clamp: loaded but never stored
-        off[A_LD + i] = ((uint32_t)rb * (uint32_t)kblocks + (j & 1)) * 1024u + lane * 16;
+        off[A_LD + i] = ((uint32_t)(j >> 1) * (uint32_t)kblocks + (j & 1)) * 1024u + lane * 16;
     }
+    const char *abase, *bbase;
+    uint32_t abytes, bbytes;
+    // lane number the compiler knows nothing about: what is computed from it per tile is not kept in registers meanwhile
+    auto opaque_lane = [&]() {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
+    auto aim_a = [&](const Tile &t) {
+        if (a.a_gather) {
+            abase = (const char *)a.A;
+            abytes = 0xffffffffu;
+            const int l = opaque_lane();
+#pragma unroll
+            for (int i = 0; i < A_LD; ++i) {
+                const int r = (wave * A_LD + i) * 8 + (l >> 3);
+                off[i] = (uint32_t)a.a_gather[min(t.row0 + r, t.row_end - 1)] * (uint32_t)(a.lda * 2) + swz(r, l & 7) * 16;
+            }
+        } else {
+            abase = (const char *)a.A + (size_t)t.row0 * (size_t)(a.lda * 2);
+            abytes = (uint32_t)(t.row_end - t.row0) * (uint32_t)(a.lda * 2);
+        }
+    };
+    auto aim_b = [&](const Tile &t) {
+        bbase = (const char *)a.B + ((size_t)t.group * a.b_group_stride + (size_t)t.col0 * a.K) * 2;
+        bbytes = (uint32_t)((n_cols - t.col0 + 15) >> 4) * (uint32_t)kblocks * 1024u;
+    };
     typedef void __attribute__((address_space(3))) *lptr_t;
-    // request D of k-tile ka of A into the stage at sa, or of k-tile kb of B into the one at sb.  Offsets reach 4 GiB
-    // (gemm_mfma_supported), past a tile's last row or block they are clamped above.
+    // request D of k-tile ka of A into the stage at sa, or of k-tile kb of B into the one at sb
     auto request = [&](auto D, int ka, unsigned sa, int kb, unsigned sb) {
         constexpr int d = decltype(D)::value;
         if constexpr (d < A_LD)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)A, 0, 0xffffffff, 0x00020000),
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)abase, 0, abytes, 0x00020000),
                                                      (lptr_t)(smem + sa + (wave * A_LD + d) * 1024), 16, off[d],
                                                      ka * (BK * 2), 0, 0);
         else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)B, 0, 0xffffffff, 0x00020000),
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)bbase, 0, bbytes, 0x00020000),
                                                      (lptr_t)(smem + sb + (wave * B_LD + d - A_LD) * 1024), 16, off[d],
                                                      kb * 2048, 0, 0);       // two 1 KB k-blocks per tile
     };
@@ -232,12 +252,8 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
     // hide from the compiler that they are MFMAs, so the waits between a register's last vector write and the first
     // MFMA, and between the last MFMA and the first read, are written out; inside the loop the operands come from LDS
     // reads, whose counter the compiler keeps for asm operands too.
-    constexpr bool kAgpr = MB * NB > 32;
+    constexpr bool kAgpr = MB * NB > (F8 ? 16 : 32);
     f32x4 acc[MB][NB];
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto pin_acc = [&]() {
         if constexpr (kAgpr)
 #pragma unroll
@@ -305,15 +321,25 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
     // ---- k-loop.  The barrier stands between the halves of k-tile kt.  Ahead of it every wave has read all it needs of
     //      tile kt's stages and waited for its own requests of tile kt + 1, so behind it those stages take the next
     //      requests (a round: tile kt + NSA of A, kt + NSB of B, in this order, the last of them behind the other half of
-    //      the next iteration) and tile kt + 1 may be read.  Direct-to-LDS loads retire in order through the wave's
-    //      vector-memory counter, so "tile kt + 1 has landed" is "at most WAIT requests outstanding": all of the rounds
-    //      behind the one that asked for it, and, with a further stage of B, that round's own requests of B.  Past the last
-    //      tile the last one is requested again, so that the counts stay the same to the end.
+    //      the next iteration) and tile kt + 1 may be read.  Vector-memory operations retire in order through the wave's
+    //      counter, so "tile kt + 1 has landed" is "at most WAIT requests outstanding": all of the rounds behind the one
+    //      that asked for it, and, with a further stage of B, that round's own requests of B.
+    //      A workgroup that has another tile of C to do requests that one's first k-tiles behind the last of this one, and
+    //      reads their first fragments, so the pipeline stays full through the epilogue; otherwise the last k-tile is
+    //      requested again, so that the counts stay the same to the end.  Gate / up of the 8B shape at 8192 rows, 14 tiles of
+    //      C per workgroup: @@@ us.
 #define PD_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
 #define PD_VMCNT_LGKM0(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (((n) >> 4) << 14))
     constexpr int D1 = Ring::issued(64);              // requests of a round ahead of the iteration's end
     constexpr int WAIT = (NSA - 2) * LD + (NSB > NSA ? B_LD : 0);
     static_assert(NSA >= 2 && WAIT + LD <= 63, "vector-memory counter range");
+    int pid = blockIdx.x;
+    Tile t = tile_at(pid), next = t;
+    pid += gridDim.x;
+    bool more = pid < n_tiles;
+    if (more) next = tile_at(pid);
+    aim_a(t);
+    aim_b(t);
     static_for<NSB - 1>([&](auto R) {
         constexpr int ta = decltype(R)::value - NSB + NSA, tb = decltype(R)::value;
         static_for<LD>([&](auto D) {
@@ -328,8 +354,6 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
     asm volatile("" ::: "memory");
     static_for<N_FIRST>([&](auto R) { read_frag(c1, R, c0, 0u, B0); });
     unsigned sa = 0, sb = B0;
-    pin_acc();
-    if constexpr (kAgpr) asm volatile("s_nop 7");
     auto k_tile = [&](int kt, auto S) {
         constexpr int s = decltype(S)::value;
         static_for<NM>([&](auto Mi) {
@@ -346,8 +370,16 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         const unsigned sa1 = sa + SA == NSA * SA ? 0u : sa + SA, sb1 = sb + SB == B0 + NSB * SB ? B0 : sb + SB;
-        kap = min(kt + NSA, kt1 - 1);
-        kbp = min(kt + NSB, kt1 - 1);
+        kap = kt + NSA;
+        kbp = kt + NSB;
+        if (kbp >= kt1) {
+            if (more && kbp == kt1) aim_b(next);
+            kbp = more ? kt0 + kbp - kt1 : kt1 - 1;
+        }
+        if (kap >= kt1) {
+            if (more && kap == kt1) aim_a(next);
+            kap = more ? kt0 + kap - kt1 : kt1 - 1;
+        }
         sap = sa;
         sbp = sb;
         static_for<NM>([&](auto Mi) {
@@ -364,6 +396,13 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
         sa = sa1;
         sb = sb1;
     };
+    for (;;) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    pin_acc();
+    if constexpr (kAgpr) asm volatile("s_nop 7");
     if constexpr (F8) {
         for (int kt = kt0; kt < kt1; kt += 2) {       // two register sets of B's fragments
             k_tile(kt, c0);
@@ -372,24 +411,25 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
     } else {
         for (int kt = kt0; kt < kt1; ++kt) k_tile(kt, c0);
     }
-    PD_VMCNT(0);                                      // the repeated requests: none may outlive the workgroup's LDS
+    if (!more) PD_VMCNT(0);                           // the repeated requests: none may outlive the workgroup's LDS
     if constexpr (kAgpr) asm volatile("s_nop 15\n\ts_nop 15");
     pin_acc();
 #undef PD_VMCNT
 #undef PD_VMCNT_LGKM0
 
     // ---- epilogue: lane holds row (lane % 16) of each block, columns 4*(lane/16) .. +3 -------------------------
+    const int el = opaque_lane(), er = el & 15, eg = el >> 4;
     if constexpr (F8) {
         f32x4 sbv[NB];
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             // columns past the last block (a multiple of 16 of them exist) are not stored
-            const int n = min(col0 + wn * WN + j * 16, n_cols - 16) + 4 * kg;
-            sbv[j] = *(const f32x4 *)(a.b_scale + (size_t)group * n_cols + n);
+            const int n = min(t.col0 + wn * WN + j * 16, n_cols - 16) + 4 * eg;
+            sbv[j] = *(const f32x4 *)(a.b_scale + (size_t)t.group * n_cols + n);
         }
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
-            int mr = min(row0 + wm * WM + i * 16 + fr, row_end - 1);
+            int mr = min(t.row0 + wm * WM + i * 16 + er, t.row_end - 1);
             if (a.a_gather) mr = a.a_gather[mr];        // the scale belongs to the row the codes came from
             const float sav = a.a_scale[mr];
 #pragma unroll
@@ -402,15 +442,14 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
         float *P = a.splitk_ws + (size_t)blockIdx.y * a.M * n_cols;
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
-            const int m = row0 + wm * WM + i * 16 + fr;
+            const int m = t.row0 + wm * WM + i * 16 + er;
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                const int n = col0 + wn * WN + j * 16 + 4 * kg;
-                if (m < row_end && n < n_cols) *(f32x4 *)(P + (size_t)m * n_cols + n) = acc[i][j];
+                const int n = t.col0 + wn * WN + j * 16 + 4 * eg;
+                if (m < t.row_end && n < n_cols) *(f32x4 *)(P + (size_t)m * n_cols + n) = acc[i][j];
             }
         }
-        return;
-    }
+    } else {
     uint16_t *C = (uint16_t *)a.C;
     const uint16_t *R = (const uint16_t *)a.R;
     // Two neighbouring blocks of 16 columns: the lane groups 4*(lane/16) exchange a block's half in pairs, after which
@@ -419,7 +458,7 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
     constexpr int OB = EPI == EPI_SWIGLU ? NB / 2 : NB;   // output blocks of the wave
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-        const int m = row0 + wm * WM + i * 16 + fr;
+        const int m = t.row0 + wm * WM + i * 16 + er;
 #pragma unroll
         for (int o = 0; o < OB; o += 2) {
             float v[8];                                   // the lane's four columns of block o, then of block o + 1
@@ -431,8 +470,8 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
                     else v[4 * b + r] = acc[i][o + b][r];
                 }
             // lane group kg: block o + kg % 2, columns 8 * (kg / 2) .. +7
-            const int n = (EPI == EPI_SWIGLU ? (col0 + wn * WN) / 2 : col0 + wn * WN) + (o + (kg & 1)) * 16 + 8 * (kg >> 1);
-            const bool in = m < row_end && n < a.N;
+            const int n = (EPI == EPI_SWIGLU ? (t.col0 + wn * WN) / 2 : t.col0 + wn * WN) + (o + (eg & 1)) * 16 + 8 * (eg >> 1);
+            const bool in = m < t.row_end && n < a.N;
             uint4 out;
             if constexpr (EPI == EPI_RESIDUAL) {
 #pragma unroll
@@ -455,13 +494,20 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
             if (in) *(uint4 *)(C + (size_t)m * a.ldc + n) = out;
         }
     }
+    }
+    if (!more) break;
+    t = next;
+    pid += gridDim.x;
+    more = pid < n_tiles;
+    if (more) next = tile_at(pid);
+    }
 }
 
-// Tiles of up to 256 x 128 stay inside 256 registers; asked to, the compiler leaves the AGPRs (and moves to and from them)
-// alone.
+// Tiles of up to 256 x 128 (codes, whose fragments take more: 128 x 128) stay inside 256 registers; asked to, the compiler
+// leaves the AGPRs, and moves to and from them, alone.
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS, bool F8 = false>
-__global__ __launch_bounds__(64 * WAVES_M *WAVES_N, BM *BN > 256 * 128 ? 1 : 2) void gemm_mfma_kernel(GemmArgs a, int tiles_m, int tiles_n,
-                                                                                                   int kt_per_split)
+__global__ __launch_bounds__(64 * WAVES_M *WAVES_N, BM *BN > (F8 ? 128 : 256) * 128 ? 1 : 2)
+void gemm_mfma_kernel(GemmArgs a, int tiles_m, int tiles_n, int kt_per_split)
 {
     gemm_mfma_body<BM, BN, WAVES_M, WAVES_N, EPI, NS, F8>(a, tiles_m, tiles_n, kt_per_split);
 }
@@ -629,7 +675,13 @@ static hipError_t launch_cfg(const GemmArgs &a, hipStream_t s, int splits = 1)
     const int nk = a.K / BK;
     const int kt_per = (nk + splits - 1) / splits;
     splits = (nk + kt_per - 1) / kt_per;               // no empty split
-    const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)splits);
+    // One workgroup per CU (two of a form that shares it) takes every further tile of C itself, unless K is too short for
+    // the ring or, with codes, ends in the other register set.
+    using Ring = TileRing<BM, BN, WAVES_M * WAVES_N, NS>;
+    const int slots = Ring::pair ? 512 : 256;
+    int grid_x = tiles_m * tiles_n;
+    if (splits == 1 && nk > Ring::NSB && (!F8 || nk % 2 == 0)) grid_x = std::min(grid_x, slots);
+    const dim3 grid((unsigned)grid_x, (unsigned)splits);
     const dim3 block(64 * WAVES_M * WAVES_N);
 #define LAUNCH(EPI)                                                                              \
     do {                                                                                         \
@@ -661,19 +713,16 @@ static hipError_t launch_cfg(const GemmArgs &a, hipStream_t s, int splits = 1)
     return hipGetLastError();
 }
 
-// Split count for decode-sized problems: about one workgroup per CU (measured: more splits lose
-// to the fp32 partial traffic, fewer leave CUs without a weight stream), at least 4 k-tiles per
-// split, partials (written and read back) below about the weight bytes, and they must fit the
-// scratch buffer.
-static int choose_splits(const GemmArgs &a, int BM, int BN)
+// Split count of a grouped product of few rows per group: about one workgroup per CU (more splits lose to the fp32
+// partial traffic, fewer leave CUs without a weight stream), at least 4 k-tiles per split, partials (written and read
+// back) below about the weight bytes, and they must fit the scratch buffer.
+static int grouped_splits(const GemmArgs &a, int BN)
 {
     if (!a.splitk_ws || a.N % 4 != 0 || a.ldc % 4 != 0 || (a.epilogue == EPI_RESIDUAL && a.ldr % 4 != 0))
         return 1;
     const int n_cols = a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N;
-    // row tiles that do work: for a grouped problem at most one per group and per row (rows are few here)
-    int row_tiles = (a.M + BM - 1) / BM;
-    if (a.group_offsets) row_tiles = a.M < a.n_groups ? a.M : a.n_groups;
-    const int tiles = row_tiles * ((n_cols + BN - 1) / BN);
+    if (n_cols >= 16384) return 1;                 // enough column tiles without splitting K
+    const int tiles = (a.M < a.n_groups ? a.M : a.n_groups) * ((n_cols + BN - 1) / BN);   // at most a row tile per group and row
     const int nk = a.K / BK;
     int splits = 256 / tiles;                      // never more workgroups than CUs: a second, nearly
     if (splits > nk / 4) splits = nk / 4;          // empty round costs more than the idle CUs
@@ -683,21 +732,26 @@ static int choose_splits(const GemmArgs &a, int BM, int BN)
     return splits < 1 ? 1 : splits;
 }
 
-// Tile and K split of a dense product of more than 256 rows, for both operand widths (a k-tile is 64 x 2
+// Tile and K split of a product of more than 256 rows (or rows per group), and of a dense one of fewer, for both operand widths (a k-tile is 64 x 2
 // bytes wide in either, and takes the same time).  256 x 256 tiles are the fastest per flop, but a launch runs in
 // rounds of one workgroup per CU: a few hundred to a few thousand rows fill the last round badly, and so do 257 rows
 // that take two row tiles.  Each form's time is therefore estimated as
 //   start + k-tiles per split x (full rounds x time of a k-tile + the last round's, from few workgroups to a full one)
-// and a split's as the launch that adds the partials, 1.8 us, and the partials written and read at 6 TB/s (a product whose
-// sum would carry the norm behind it saves that launch, 6.5 us).  The constants are fitted to 26000 launches: nine layer
-// shapes of 512 ... 8192 columns, 257 ... 6000 rows, bf16 and codes, every form and split.  On them the choice takes 0.5 %
-// longer than the best form and split (at worst 20 %, 23 against 19 us), and 22 % less than what served before there were
-// several forms (256 x 256, codes of up to 512 rows 256 x 64; 22 of 1296 products are 3 - 9 % slower than that).
-// us, 256 x 256 with their best split -> planned: bf16 QKV 771 rows 68 -> 59 (192), O 512 rows 39 -> 33 (128, 8 waves),
-// gate/up 300 rows 110 -> 88 (192), down 5107 rows 737 -> 641 (192); codes O 1024 rows 46 -> 27 (128, 8 waves).
+// and a split's as the launch that adds the partials and the partials written and read (a product whose sum would carry
+// the norm behind it saves that launch, 6.5 us).  The constants for 32 k-tiles and more are fitted to 5400 launches of the
+// kernels as they are now: 18 shapes of 1024 ... 28672 columns and K = 1024 ... 14336, 257 ... 6000 rows, bf16 and codes,
+// every form and split.  On them the choice takes 0.8 % longer than the best form and split (at worst 14 %); with the
+// constants for fewer k-tiles, which were fitted to these and to shorter products when all forms took longer per k-tile
+// (there 256 x 128 is never ahead), it took 2.5 % longer.  A product whose sum carries a norm keeps those too: the fit does
+// not know that sum's time, and they are within 3 % there.  us, before -> with this fit: bf16 QKV 771 rows 57 -> 48
+// (256 x 128), down 512 rows 84 -> 64 (256 x 128, four splits).
+// Up to 256 rows the weights are streamed once and the tiles are smaller: fitted to 4500 launches of 17 shapes, 18 ... 256
+// rows, up to 12 splits.  On them the choice takes 0.3 % longer than the best (at worst 12 %); one form for each of up to 64,
+// 128 and 256 rows, 128 or 64 columns wide, with as many splits as one round of workgroups holds, took 19 % longer.
+// us, before -> now: 256 rows QKV 31 -> 27, O 23.6 -> 21.3, gate/up 72 -> 64, down 50 -> 44; 64 rows O 16.0 -> 13.4.
 // A grouped product's loads are known only on the average, so another form than 256 x 256 has to be 5 % ahead there
 // (without that, 9200 rows on 8 experts took 4330 instead of 4265 us).
-enum TileForm { TILE_256, TILE_192, TILE_128_PAIR, TILE_128_DEEP };
+enum TileForm { TILE_256, TILE_192, TILE_128_PAIR, TILE_128_DEEP, TILE_256_128, TILE_128_64, TILE_64_128, TILE_64 };
 struct TilePlan {
     TileForm form;
     int splits;
@@ -722,22 +776,38 @@ static TilePlan plan_tiles(const GemmArgs &a)
     const bool can_split = a.splitk_ws && !a.group_offsets && !a.a_gather && a.N % 4 == 0 && a.ldc % 4 == 0 && (a.epilogue != EPI_RESIDUAL || a.ldr % 4 == 0);
     TilePlan best = {TILE_256, 1};
     double best_us = 1e30;
-    const struct {
+    const struct Form {
         TileForm form;
         int bm, bn, per_round;
         double start, kt_full, kt_few;
-    } forms[] = {{TILE_256, 256, 256, 256, 3.7, 1.626, 1.211},
+    } few_k[] = {{TILE_256, 256, 256, 256, 3.7, 1.626, 1.211},
                  {TILE_192, 192, 256, 256, 2.6, 1.348, 1.107},
                  {TILE_128_PAIR, 128, 128, 512, 0.85, 1.053, 0.62},          // two workgroups per CU
-                 {TILE_128_DEEP, 128, 128, 256, 0.0, 0.636, 0.486}};         // alone on its CU with a four-stage ring
-    for (const auto &f : forms) {
+                 {TILE_128_DEEP, 128, 128, 256, 0.0, 0.636, 0.486}},         // alone on its CU with a deeper ring
+      many_k[] = {{TILE_256, 256, 256, 256, 1.235, 1.080, 1.306},
+                  {TILE_192, 192, 256, 256, 3.609, 0.891, 0.943},
+                  {TILE_128_PAIR, 128, 128, 512, 0.392, 0.832, 0.904},
+                  {TILE_128_DEEP, 128, 128, 256, 0.021, 0.460, 0.769},
+                  {TILE_256_128, 256, 128, 256, 2.968, 0.698, 0.830}},
+      few_rows[] = {{TILE_256_128, 256, 128, 256, 3.0, 0.490, 0.861},
+                    {TILE_128_DEEP, 128, 128, 256, 3.29, 0.445, 0.475},
+                    {TILE_128_64, 128, 64, 256, 1.88, 0.312, 0.472},
+                    {TILE_64_128, 64, 128, 256, 4.44, 0.402, 0.306},
+                    {TILE_64, 64, 64, 256, 0.83, 0.232, 0.273}};
+    // codes come in larger calls, but for pd_gemm_e4m3
+    const bool few = a.M <= 256 && !a.a_scale, many = nk >= 32 && !a.fuse_y;
+    const double add = few ? 4.04 : many ? 5.06 : 1.8, partials = few ? 3.2e6 : many ? 4.96e6 : 6e6;     // us, bytes per us
+    const Form *forms = few ? few_rows : many ? many_k : few_k;
+    const int n_forms = few || many ? 5 : 4, max_splits = few ? 12 : 8, min_k_tiles = few ? 4 : 2;
+    for (int i = 0; i < n_forms; ++i) {
+        const Form &f = forms[i];
         const long long tiles = (long long)ceil(row_tiles(a, f.bm) * ((n_cols + f.bn - 1) / f.bn));
-        for (int sp = 1; sp <= 8; ++sp) {
-            if (sp > 1 && (!can_split || nk / sp < 2 || (size_t)sp * a.M * n_cols > a.splitk_ws_elems)) break;
+        for (int sp = 1; sp <= max_splits; ++sp) {
+            if (sp > 1 && (!can_split || nk / sp < min_k_tiles || (size_t)sp * a.M * n_cols > a.splitk_ws_elems)) break;
             const long long wg = tiles * sp, full = wg / f.per_round, rem = wg % f.per_round;
             const double last = rem ? f.kt_few + (f.kt_full - f.kt_few) * (double)rem / f.per_round : 0.0;
             double us = f.start + ((nk + sp - 1) / sp) * ((double)full * f.kt_full + last);
-            if (sp > 1) us += 1.8 + (double)sp * a.M * n_cols * 8.0 / 6e6;
+            if (sp > 1) us += add + (double)sp * a.M * n_cols * 8.0 / partials;
             else if (a.fuse_y) us += 6.5;
             if (a.group_offsets && f.form != TILE_256) us *= 1.05;
             if (us < best_us) {
@@ -789,9 +859,19 @@ static hipError_t launch_planned(const GemmArgs &a, hipStream_t s)
     switch (p.form) {
     case TILE_192: return launch_cfg<192, 256, 2, 2, 2, F8>(a, s, p.splits);
     case TILE_128_PAIR: return launch_cfg<128, 128, 2, 2, 2, F8>(a, s, p.splits);
-    case TILE_128_DEEP: return launch_cfg<128, 128, 2, 2, 4, F8>(a, s, p.splits);
-    default: return launch_cfg<256, 256, 2, 2, 2, F8>(a, s, p.splits);
+    case TILE_128_DEEP: return launch_cfg<128, 128, 2, 2, 3, F8>(a, s, p.splits);
+    case TILE_256_128: return launch_cfg<256, 128, 2, 2, 3, F8>(a, s, p.splits);
+    default: break;
     }
+    if constexpr (!F8) {                                      // calls of up to 256 rows multiply no codes
+        switch (p.form) {
+        case TILE_128_64: return launch_cfg<128, 64, 4, 1, 4>(a, s, p.splits);
+        case TILE_64_128: return launch_cfg<64, 128, 2, 2, 4>(a, s, p.splits);
+        case TILE_64: return launch_cfg<64, 64, 4, 1, 4>(a, s, p.splits);
+        default: break;
+        }
+    }
+    return launch_cfg<256, 256, 2, 2, 2, F8>(a, s, p.splits);
 }
 
 hipError_t launch_gemm_mfma_f8(const GemmArgs &a, hipStream_t s)
@@ -801,21 +881,13 @@ hipError_t launch_gemm_mfma_f8(const GemmArgs &a, hipStream_t s)
 
 hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s)
 {
-    // rows that share a weight matrix: for a grouped problem the mean group size picks the tile
-    // (larger groups take several row tiles)
-    const int rows = a.group_offsets ? (a.M + a.n_groups - 1) / a.n_groups : a.M;
+    if (!a.group_offsets) return launch_planned<false>(a, s);
+    // rows that share a weight matrix: the mean group size picks the tile (larger groups take several row tiles)
+    const int rows = (a.M + a.n_groups - 1) / a.n_groups;
     if (rows > 256) return launch_planned<false>(a, s);
-    const int n_cols = a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N;
-    const bool wide = n_cols >= 16384;                            // enough column tiles without splitting K
-    if (rows > 128) {
-        if (wide) return launch_cfg<256, 128, 2, 2, 3>(a, s, 1);
-        return launch_cfg<256, 64, 4, 1, 4>(a, s, choose_splits(a, 256, 64));
-    }
-    if (rows > 64) {
-        if (wide) return launch_cfg<128, 128, 2, 2, 4>(a, s, 1);
-        return launch_cfg<128, 64, 4, 1, 6>(a, s, choose_splits(a, 128, 64));
-    }
-    return launch_cfg<64, 128, 2, 2, 6>(a, s, wide ? 1 : choose_splits(a, 64, 128));
+    if (rows > 128) return launch_cfg<256, 128, 2, 2, 3>(a, s, grouped_splits(a, 128));
+    if (rows > 64) return launch_cfg<128, 128, 2, 2, 3>(a, s, grouped_splits(a, 128));
+    return launch_cfg<64, 128, 2, 2, 4>(a, s, grouped_splits(a, 128));
 }
 
 }  // namespace pd
