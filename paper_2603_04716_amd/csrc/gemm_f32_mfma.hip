@@ -11,6 +11,10 @@
 // Measured against the 64 x 64 FMA tile of kernels_generic.hip: 4 x 256 <- 1024 133 -> 11 us, 4 x 768 <- 256
 // 39 -> 6 us (a launch), 1 x 6144 <- 2048 264 -> 15 us, 1000 x 6144 <- 2048 754 -> 366 us, 4096 x 6144 <- 2048
 // 2794 -> 1421 us (73 TFLOP/s, bound by the operand reads: a 32 x 32 tile fetches 4 bytes per 32 flop).
+//
+// NORM: the rows of A are normalised on the way.  Every workgroup reads whole rows of A (K is the row), so it sums their
+// squares beside the product, multiplies the operand by the gain and the finished sums by the row's factor: the norm's
+// launch, 2 - 3 us of a step of some 40, is saved for a few vector instructions per load.
 #include "pd_internal.h"
 
 namespace pd {
@@ -20,12 +24,16 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float silu_precise(float z) { return z / (1.0f + expf(-z)); }
 
 // MB x MB blocks of 16 x 16 per workgroup, W waves along K
-template <int MB, int W, int EPI>
+template <int MB, int W, int EPI, bool NORM = false>
 __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GemmArgs a)
 {
+    static_assert(!NORM || MB == 1, "one row per lane");
     constexpr int BT = 16 * MB, NM = EPI == EPI_SWIGLU ? 2 : 1;   // NM: weight matrices (gate and up)
-    constexpr int U = 4;                                          // 16-wide k-steps requested at a time
+    // 16-wide k-steps requested at a time; with eight waves (K >= 512) eight, one round trip up to K = 1024 (4 x 256 <- 1024
+    // with four: 6.8 us, 6.3 now)
+    constexpr int U = MB == 1 && W == 8 ? 8 : 4;
     __shared__ f32x4 red[W][NM * MB * MB][64];
+    __shared__ float sq[NORM ? W : 1][16];
 
     int row0, row_end, group = 0;
     if (a.group_offsets) {
@@ -70,10 +78,11 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GemmArgs a)
 #pragma unroll
             for (int j = 0; j < MB; ++j) acc[m][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    float ss = 0.f;                                               // NORM: this lane's part of its row's sum of squares
     const int steps = (a.K + 15) / 16, per = (steps + W - 1) / W;
     const int s1 = min(steps, (wave + 1) * per);
     for (int s0 = wave * per; s0 < s1; s0 += U) {
-        f32x4 fa[U][MB], fb[U][NM][MB];
+        f32x4 fa[U][MB], fb[U][NM][MB], fg[NORM ? U : 1];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int k = (s0 + u) * 16 + kg, kc = min(k, a.K - 4);
@@ -83,6 +92,7 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GemmArgs a)
             for (int i = 0; i < MB; ++i) {
                 const f32x4 va = *(const f32x4 *)(ap[i] + kc);
                 fa[u][i] = ok ? va : zero;
+                if (NORM) fg[u] = *(const f32x4 *)(a.norm_g + kc);
 #pragma unroll
                 for (int m = 0; m < NM; ++m) {
                     const f32x4 vb = *(const f32x4 *)(bp[m][i] + kc);
@@ -90,6 +100,13 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GemmArgs a)
                 }
             }
         }
+        if (NORM)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const f32x4 x = fa[u][0];
+                ss += (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
+                fa[u][0] = x * fg[u];
+            }
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -109,6 +126,11 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GemmArgs a)
         for (int i = 0; i < MB; ++i)
 #pragma unroll
             for (int j = 0; j < MB; ++j) red[wave][(m * MB + i) * MB + j][lane] = acc[m][i][j];
+    if (NORM) {
+        ss += __shfl_xor(ss, 16, 64);
+        ss += __shfl_xor(ss, 32, 64);
+        if (lane < 16) sq[wave][lane] = ss;
+    }
     __syncthreads();
     float *C = (float *)a.C;
     const float *R = (const float *)a.R;
@@ -130,6 +152,14 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GemmArgs a)
             const int m = row0 + 16 * (blk / MB) + 4 * (l >> 4) + r;
             if (m >= row_end) break;
             float x = v[r];
+            if (NORM) {
+                float t = sq[0][4 * (l >> 4) + r];
+#pragma unroll
+                for (int z = 1; z < W; ++z) t += sq[z][4 * (l >> 4) + r];
+                const float inv = rsqrtf(t / (float)a.K + a.norm_eps);
+                x *= inv;
+                w[r] *= inv;
+            }
             if (EPI == EPI_RESIDUAL) x += R[(size_t)m * a.ldr + c];
             if (EPI == EPI_SWIGLU) x = silu_precise(x) * w[r];
             C[(size_t)m * a.ldc + c] = x;
@@ -150,11 +180,25 @@ bool gemm_f32_mfma_supported(const GemmArgs &a)
            (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)(a.epilogue == EPI_SWIGLU ? a.B1 : nullptr)) & 15) == 0;
 }
 
+// K is the whole row, and the small tiles are taken (see launch_gemm_f32_mfma)
+static bool small_tiles(const GemmArgs &a) { return (long long)((a.M + 31) / 32) * ((a.N + 31) / 32) < 512; }
+bool gemm_f32_norm_supported(const GemmArgs &a)
+{
+    return gemm_f32_mfma_supported(a) && small_tiles(a) && !a.a_gather && !a.group_offsets && a.epilogue != EPI_RESIDUAL &&
+           ((uintptr_t)a.norm_g & 15) == 0;
+}
+
 template <int MB, int W>
 static hipError_t launch_f32(const GemmArgs &a, hipStream_t s)
 {
     const dim3 grid((unsigned)((a.N + 16 * MB - 1) / (16 * MB)),
                     (unsigned)((a.M + 16 * MB - 1) / (16 * MB) + (a.group_offsets ? a.n_groups : 0)));
+    if constexpr (MB == 1)
+        if (a.norm_g) {
+            if (a.epilogue == EPI_SWIGLU) gemm_f32_mfma_kernel<1, W, EPI_SWIGLU, true><<<grid, 64 * W, 0, s>>>(a);
+            else gemm_f32_mfma_kernel<1, W, EPI_NONE, true><<<grid, 64 * W, 0, s>>>(a);
+            return hipGetLastError();
+        }
     switch (a.epilogue) {
     case EPI_NONE: gemm_f32_mfma_kernel<MB, W, EPI_NONE><<<grid, 64 * W, 0, s>>>(a); break;
     case EPI_RESIDUAL: gemm_f32_mfma_kernel<MB, W, EPI_RESIDUAL><<<grid, 64 * W, 0, s>>>(a); break;
@@ -165,9 +209,8 @@ static hipError_t launch_f32(const GemmArgs &a, hipStream_t s)
 
 hipError_t launch_gemm_f32_mfma(const GemmArgs &a, hipStream_t s)
 {
-    const long long tiles32 = (long long)((a.M + 31) / 32) * ((a.N + 31) / 32);
     // two workgroups per CU: below that the small tile's four times as many workgroups are worth its extra reads
-    if (tiles32 >= 512) return launch_f32<2, 4>(a, s);
+    if (!small_tiles(a)) return launch_f32<2, 4>(a, s);
     // small tiles: eight waves once each of them has a full round of k-steps to itself
     return a.K >= 512 ? launch_f32<1, 8>(a, s) : launch_f32<1, 4>(a, s);
 }

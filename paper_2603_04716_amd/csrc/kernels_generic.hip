@@ -395,6 +395,26 @@ hipError_t launch_decode_meta(const int32_t *d_slots, int B, int32_t *d_len, int
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void decode_meta_upload_kernel(IntChunk sv, int32_t *slots_out, int B, int32_t *len, int32_t *pos)
+{
+    const int b = threadIdx.x;
+    if (b >= B) return;
+    const int s = sv.v[b], p = len[s];
+    slots_out[b] = s;
+    pos[b] = p;
+    len[s] = p + 1;  // slots are distinct
+}
+
+hipError_t launch_decode_meta_upload(const int32_t *host_slots, int32_t *d_slots, int B, int32_t *d_len, int32_t *d_pos,
+                                     hipStream_t s)
+{
+    if (B < 1 || B > 256) return hipErrorInvalidValue;
+    IntChunk sv;
+    memcpy(sv.v, host_slots, (size_t)B * sizeof(int32_t));
+    decode_meta_upload_kernel<<<1, 256, 0, s>>>(sv, d_slots, B, d_len, d_pos);
+    return hipGetLastError();
+}
+
 __global__ void prefill_set_len_kernel(const int32_t *__restrict__ slots,
                                        const int32_t *__restrict__ cu, int n, int32_t *len, int add)
 {
@@ -632,36 +652,103 @@ __device__ __forceinline__ float finite_from(float m) { return m == -INFINITY ? 
 // row groups are added once at the end.  The waves' (max, sum, output) merge in LDS in wave order.
 // Measured against the generic form's wave per item: 4 rows, 4 heads of 64, 150 keys 35 -> 8 us; 64 rows,
 // 16 heads of 128, 1000 keys 994 -> 220 us.
-template <int LPR>
-__global__ __launch_bounds__(256) void attn_decode_f32_kernel(AttnArgs a)
+//
+// ROPE (one row per sequence): q and the new key arrive unrotated.  The first waves rotate them into LDS (the arithmetic of
+// rope_kv_kernel) and one workgroup per kv head stores the new key and value into the cache; every workgroup takes the new
+// token from LDS, so none reads the position that another one writes.  4 rows, 4 heads of 64,
+// 100 keys: rotation 3.4 + attention 6.7 us -> 7.3.
+template <int LPR, bool ROPE>
+__global__ __launch_bounds__(256) void attn_decode_f32_kernel(AttnArgs a, RopeArgs ra)
 {
     constexpr int hd = 4 * LPR, RPI = 64 / LPR, W = 4;
-    __shared__ float4 qs[LPR];
+    // Values of a 64-key chunk are requested together with its keys where the registers hold them: one round trip fewer
+    constexpr bool kAhead = LPR <= 16;
+    __shared__ float4 qs[LPR], kn[ROPE ? LPR : 1], vn[ROPE ? LPR : 1];
     __shared__ float4 os[4][LPR];
     __shared__ float ml[4][2];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int t = blockIdx.x / a.Hq, h = blockIdx.x % a.Hq;
     const int g = h / (a.Hq / a.Hkv);
-    if (wave == 0 && lane < LPR) {
+    const int pos = a.tok_pos[t], n_keys = pos + 1;
+    const size_t base = (((size_t)a.tok_slot[t] * a.Hkv + g) * a.max_len) * hd;
+    const float *Kb = (const float *)a.k_cache + base, *Vb = (const float *)a.v_cache + base;
+    const int last = ROPE ? max(pos - 1, 0) : n_keys - 1;         // last position that is read from the cache
+    const int vrow = lane / LPR, vch = lane % LPR;
+    float4 kv[kAhead ? LPR : 1], va[kAhead ? LPR : 1];
+    auto request = [&](int c0) {                                  // keys (a row per lane) and values of the chunk at c0
+        if constexpr (kAhead) {
+            const float4 *kr = (const float4 *)(Kb + (size_t)min(c0 + lane, last) * hd);
+#pragma unroll
+            for (int i = 0; i < LPR; ++i) kv[i] = kr[i];
+#pragma unroll
+            for (int u = 0; u < LPR; ++u) va[u] = ((const float4 *)(Vb + (size_t)min(c0 + u * RPI + vrow, last) * hd))[vch];
+        }
+    };
+    if (wave * 64 < n_keys) request(wave * 64);                   // on their way while the query is prepared
+    if (ROPE) {
+        // wave 0: q, wave 1: the new key, wave 2: the new value
+        if (wave < 3 && lane < LPR) {
+            const float *row = (const float *)a.qkv + (size_t)t * a.ld;
+            const float4 *src = (const float4 *)(row + (size_t)(wave == 0 ? h : wave == 1 ? a.Hq + g : a.Hq + a.Hkv + g) * hd);
+            float4 x = src[lane];
+            if (wave < 2) {
+                const float4 y = src[lane ^ (LPR / 2)];           // the other half's channels
+                const bool lo = lane < LPR / 2;
+                const int i0 = 4 * (lane & (LPR / 2 - 1));
+                const float own[4] = {x.x, x.y, x.z, x.w}, other[4] = {y.x, y.y, y.z, y.w};
+                float r[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float c, s;
+                    if (pos < ra.table_len) {
+                        const float2 f = ra.table[(size_t)pos * (hd / 2) + i0 + e];
+                        c = f.x;
+                        s = f.y;
+                    } else {
+                        double sv, cv;
+                        sincos((double)pos * ra.inv_freq[i0 + e], &sv, &cv);
+                        c = (float)cv;
+                        s = (float)sv;
+                    }
+                    r[e] = lo ? fmaf(own[e], c, -(other[e] * s)) : fmaf(own[e], c, other[e] * s);
+                }
+                x = make_float4(r[0], r[1], r[2], r[3]);
+            }
+            if (wave == 0) {
+                x.x *= a.scale; x.y *= a.scale; x.z *= a.scale; x.w *= a.scale;
+                qs[lane] = x;
+            } else {
+                if (wave == 1) kn[lane] = x;
+                else vn[lane] = x;
+                if (h % (a.Hq / a.Hkv) == 0)
+                    ((float4 *)((float *)(wave == 1 ? ra.k_cache : ra.v_cache) + base + (size_t)pos * hd))[lane] = x;
+            }
+        }
+    } else if (wave == 0 && lane < LPR) {
         float4 q = ((const float4 *)((const float *)a.qkv + (size_t)t * a.ld + (size_t)h * hd))[lane];
         q.x *= a.scale; q.y *= a.scale; q.z *= a.scale; q.w *= a.scale;
         qs[lane] = q;
     }
     __syncthreads();
 
-    const int n_keys = a.tok_pos[t] + 1;
-    const size_t base = (((size_t)a.tok_slot[t] * a.Hkv + g) * a.max_len) * hd;
-    const float *Kb = (const float *)a.k_cache + base, *Vb = (const float *)a.v_cache + base;
-    const int vrow = lane / LPR, vch = lane % LPR;
     float m = -INFINITY, l = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int c0 = wave * 64; c0 < n_keys; c0 += 64 * W) {
         const int s = c0 + lane;
-        const float4 *kr = (const float4 *)(Kb + (size_t)min(s, n_keys - 1) * hd);
+        const float4 *kr = (const float4 *)(Kb + (size_t)min(s, last) * hd);
+        const bool fresh = ROPE && s == pos;
+        auto value = [&](int j) {                                 // this lane's four channels of key c0 + j
+            return ROPE && c0 + j == pos ? vn[vch] : ((const float4 *)(Vb + (size_t)min(c0 + j, last) * hd))[vch];
+        };
         float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int i = 0; i < LPR; ++i) {
-            const float4 k4 = kr[i], q4 = qs[i];
+            float4 k4 = kAhead ? kv[kAhead ? i : 0] : kr[i];
+            const float4 q4 = qs[i];
+            if (ROPE) {
+                const float4 f4 = kn[ROPE ? i : 0];
+                if (fresh) k4 = f4;
+            }
             d.x = fmaf(q4.x, k4.x, d.x); d.y = fmaf(q4.y, k4.y, d.y);
             d.z = fmaf(q4.z, k4.z, d.z); d.w = fmaf(q4.w, k4.w, d.w);
         }
@@ -673,19 +760,27 @@ __global__ __launch_bounds__(256) void attn_decode_f32_kernel(AttnArgs a)
         m = m_new;
         o.x *= corr; o.y *= corr; o.z *= corr; o.w *= corr;
         const int cnt = min(n_keys - c0, 64);
-        for (int j0 = 0; j0 < cnt; j0 += 8 * RPI) {
-            float4 v[8];
+        auto add = [&](int j, const float4 &v) {
+            const float pj = __shfl(p, j & 63, 64);
+            if (j < cnt) {
+                o.x = fmaf(pj, v.x, o.x); o.y = fmaf(pj, v.y, o.y);
+                o.z = fmaf(pj, v.z, o.z); o.w = fmaf(pj, v.w, o.w);
+            }
+        };
+        if constexpr (kAhead) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                v[u] = ((const float4 *)(Vb + (size_t)min(c0 + j0 + u * RPI + vrow, n_keys - 1) * hd))[vch];
+            for (int u = 0; u < LPR; ++u) {
+                const int j = u * RPI + vrow;
+                add(j, ROPE && c0 + j == pos ? vn[ROPE ? vch : 0] : va[u]);
+            }
+            if (c0 + 64 * W < n_keys) request(c0 + 64 * W);
+        } else {
+            for (int j0 = 0; j0 < cnt; j0 += 8 * RPI) {
+                float4 v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int j = j0 + u * RPI + vrow;
-                const float pj = __shfl(p, j & 63, 64);
-                if (j < cnt) {
-                    o.x = fmaf(pj, v[u].x, o.x); o.y = fmaf(pj, v[u].y, o.y);
-                    o.z = fmaf(pj, v[u].z, o.z); o.w = fmaf(pj, v[u].w, o.w);
-                }
+                for (int u = 0; u < 8; ++u) v[u] = value(j0 + u * RPI + vrow);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) add(j0 + u * RPI + vrow, v[u]);
             }
         }
     }
@@ -950,20 +1045,47 @@ extern "C" int pd_internal_attn_tiles_pay(int head_dim, int n_q_heads, int n_seq
     return attn_prefill_tiles_pay(a) ? 1 : 0;
 }
 
+template <bool ROPE>
+static hipError_t launch_attn_decode_f32(const AttnArgs &a, const RopeArgs &r, hipStream_t s)
+{
+    const unsigned n = (unsigned)((long long)a.T * a.Hq);
+    switch (a.hd) {
+    case 32: attn_decode_f32_kernel<8, ROPE><<<n, 256, 0, s>>>(a, r); break;
+    case 64: attn_decode_f32_kernel<16, ROPE><<<n, 256, 0, s>>>(a, r); break;
+    case 128: attn_decode_f32_kernel<32, ROPE><<<n, 256, 0, s>>>(a, r); break;
+    case 256: attn_decode_f32_kernel<64, ROPE><<<n, 256, 0, s>>>(a, r); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// 16-byte rows: buffers aligned, row strides whole (head sizes of the vector forms are multiples of 4 elements); a workgroup
+// per item: a launch is limited to 2^32 - 1 threads, which four items a workgroup reach later
+static bool attn_decode_f32_pays(const AttnArgs &a)
+{
+    const long long items = (long long)a.T * a.Hq;
+    return items > 0 && a.ld % 4 == 0 && (((uintptr_t)a.qkv | (uintptr_t)a.o | (uintptr_t)a.k_cache | (uintptr_t)a.v_cache) & 15) == 0 &&
+           a.decode && items <= 0xffffffffll / 256 && attn_decode_split_pays(a);
+}
+
+bool attn_decode_rope_f32_supported(const AttnArgs &a, const RopeArgs &r)
+{
+    return attn_decode_f32_pays(a) && !a.rows_share && !r.blocked && !r.fp8 && r.tok_slot && r.max_len == a.max_len;
+}
+
+hipError_t launch_attn_decode_rope_f32(const AttnArgs &a, const RopeArgs &r, hipStream_t s)
+{
+    return launch_attn_decode_f32<true>(a, r, s);
+}
+
 hipError_t launch_attn_generic(int dtype, const AttnArgs &a, hipStream_t s)
 {
     long long items = (long long)a.T * a.Hq;
     if (items <= 0) return hipSuccess;
     // 16-byte rows: buffers aligned, row strides whole (head sizes of the vector forms are multiples of 4 elements)
     if (dtype == PD_F32 && a.ld % 4 == 0 && (((uintptr_t)a.qkv | (uintptr_t)a.o) & 15) == 0) {
-        // a workgroup per item: a launch is limited to 2^32 - 1 threads, which four items a workgroup reach later
-        if (a.decode && (((uintptr_t)a.k_cache | (uintptr_t)a.v_cache) & 15) == 0 && items <= 0xffffffffll / 256 &&
-            attn_decode_split_pays(a)) {
-            const unsigned n = (unsigned)items;
-            if (a.hd == 32) { attn_decode_f32_kernel<8><<<n, 256, 0, s>>>(a); return hipGetLastError(); }
-            if (a.hd == 64) { attn_decode_f32_kernel<16><<<n, 256, 0, s>>>(a); return hipGetLastError(); }
-            if (a.hd == 128) { attn_decode_f32_kernel<32><<<n, 256, 0, s>>>(a); return hipGetLastError(); }
-            if (a.hd == 256) { attn_decode_f32_kernel<64><<<n, 256, 0, s>>>(a); return hipGetLastError(); }
+        if (attn_decode_f32_pays(a)) {
+            return launch_attn_decode_f32<false>(a, RopeArgs(), s);
         } else if (!a.decode && a.Hq <= 65535 && attn_prefill_tiles_pay(a)) {
             const dim3 n(attn_tile_grid(a).nx, (unsigned)a.Hq, (unsigned)a.n_seqs);
             if (a.hd == 64) { attn_prefill_f32_kernel<64><<<n, 256, 0, s>>>(a); return hipGetLastError(); }

@@ -831,6 +831,19 @@ static hipError_t norm_for_gemm(const pd_layer *L, const void *x, const void *g,
     return launch_rmsnorm(c.dtype, x, g, y, T, c.d_model, c.rms_eps, s);
 }
 
+// fp32 products on small tiles normalise their rows themselves: g then reads the rows x and the norm's launch falls away.
+static bool norm_in_gemm(const pd_layer *L, GemmArgs &g, const void *x, const void *gain)
+{
+    if (L->cfg.dtype != PD_F32) return false;
+    GemmArgs n = g;
+    n.A = x;
+    n.norm_g = (const float *)gain;
+    n.norm_eps = L->cfg.rms_eps;
+    if (!gemm_f32_norm_supported(n)) return false;
+    g = n;
+    return true;
+}
+
 static bool cache_matches(const pd_layer *L, const pd_kv_cache *c)
 {
     return c->dtype == L->cfg.dtype && c->Hkv == L->cfg.n_kv_heads && c->hd == L->cfg.head_dim;
@@ -861,14 +874,16 @@ static pd_status run_tail(pd_layer *L, const void *x, int T, const void *router_
         memset(&g, 0, sizeof(g));
         g.A = L->h; g.lda = d; g.B = L->w_gate; g.B1 = L->w_up; g.ldb = d; g.C = L->act; g.ldc = F;
         g.M = T; g.N = F; g.K = d; g.epilogue = EPI_SWIGLU; g.n_groups = 1;
-        if (norm_fused) {
-        } else if (append) {
-            L->a8_src = nullptr;
-            STEP("rmsnorm_ffn", launch_rmsnorm_append(*append, L->h, L->g_ffn, L->y, T, d, c.rms_eps, s));
-        } else {
-            STEP("rmsnorm_ffn", norm_for_gemm(L, L->h, L->g_ffn, L->y, T, s));
+        if (!norm_in_gemm(L, g, L->h, L->g_ffn)) {
+            if (norm_fused) {
+            } else if (append) {
+                L->a8_src = nullptr;
+                STEP("rmsnorm_ffn", launch_rmsnorm_append(*append, L->h, L->g_ffn, L->y, T, d, c.rms_eps, s));
+            } else {
+                STEP("rmsnorm_ffn", norm_for_gemm(L, L->h, L->g_ffn, L->y, T, s));
+            }
+            g.A = L->y;
         }
-        g.A = L->y;
         STEP("gate_up_swiglu", run_gemm(L, g, s));
         memset(&g, 0, sizeof(g));
         g.A = L->act; g.lda = F; g.B = L->w_down; g.ldb = F; g.C = out; g.ldc = d; g.R = L->h; g.ldr = d;
@@ -1076,11 +1091,11 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
         const int cnt[4] = {n + 1, n + 1, keep ? n : 0, chunk ? n : 0};
         HIP_TRY(launch_prefill_meta(dst, src, cnt, n, T, L->tok_seq, L->tok_pos, L->tok_slot, s), PD_ERR_DEVICE);
     }
-    STEP("rmsnorm_attn", norm_for_gemm(L, tk->hidden, L->g_attn, L->y, T, s));
     GemmArgs g;
     memset(&g, 0, sizeof(g));
     g.A = L->y; g.lda = c.d_model; g.B = L->w_qkv; g.ldb = c.d_model; g.C = L->qkv; g.ldc = L->Nqkv;
     g.M = T; g.N = L->Nqkv; g.K = c.d_model; g.epilogue = EPI_NONE; g.n_groups = 1;
+    if (!norm_in_gemm(L, g, tk->hidden, L->g_attn)) STEP("rmsnorm_attn", norm_for_gemm(L, tk->hidden, L->g_attn, L->y, T, s));
     STEP("qkv_proj", run_gemm(L, g, s));
     RopeArgs r;
     r.qkv = L->qkv; r.ld = L->Nqkv; r.T = T; r.Hq = c.n_q_heads; r.Hkv = c.n_kv_heads; r.hd = c.head_dim;
@@ -1351,6 +1366,8 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
         HIP_TRY(launch_decode_meta_chunks_upload(bt->slots, L->d_slots, B, cache->d_len, L->tok_pos, L->chunk_cu,
                                                  L->chunk_seq, chunk_keys, s),
                 PD_ERR_DEVICE);
+    } else if (!mfma_dec && B <= 256) {
+        HIP_TRY(launch_decode_meta_upload(bt->slots, L->d_slots, B, cache->d_len, L->tok_pos, s), PD_ERR_DEVICE);
     } else {
         HIP_TRY(launch_write_ints(L->d_slots, bt->slots, B, s), PD_ERR_DEVICE);
         if (mfma_dec)
@@ -1364,8 +1381,11 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
     memset(&g, 0, sizeof(g));
     g.A = bt->hidden; g.lda = c.d_model; g.B = L->w_qkv; g.ldb = c.d_model; g.C = L->qkv; g.ldc = L->Nqkv;
     g.M = B; g.N = L->Nqkv; g.K = c.d_model; g.epilogue = EPI_NONE; g.n_groups = 1;
-    if (!meta_in_norm) STEP("rmsnorm_attn", norm_for_gemm(L, bt->hidden, L->g_attn, L->y, B, s));
-    g.A = L->y;
+    if (!meta_in_norm && !norm_in_gemm(L, g, bt->hidden, L->g_attn)) {
+        STEP("rmsnorm_attn", norm_for_gemm(L, bt->hidden, L->g_attn, L->y, B, s));
+        g.A = L->y;
+    }
+    if (meta_in_norm) g.A = L->y;
     STEP("qkv_proj", run_gemm(L, g, s));
     RopeArgs r;
     r.qkv = L->qkv; r.ld = L->Nqkv; r.T = B; r.Hq = c.n_q_heads; r.Hkv = c.n_kv_heads; r.hd = c.head_dim;
@@ -1379,7 +1399,23 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
     // append to the cache rides in the launch of the second RMSNorm.  Otherwise a launch of its own
     // rotates in place and appends first.
     const bool fused_rope = mfma_dec && c.d_model % 8 == 0 && !(L->a8 && B > kA8Rows);
-    if (!fused_rope) STEP("rope_kv_append", launch_rope_kv(c.dtype, r, s));
+    // Over a plain cache an fp32 layer's attention does both itself.
+    AttnArgs a;
+    bool rope_in_f32 = false;
+    if (!mfma_dec) {
+        memset(&a, 0, sizeof(a));
+        a.qkv = L->qkv; a.ld = L->Nqkv; a.o = L->o; a.T = B; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads;
+        a.hd = c.head_dim; a.scale = (float)(1.0 / sqrt((double)c.head_dim)); a.tok_pos = L->tok_pos;
+        a.tok_slot = L->d_slots; a.k_cache = cache->k; a.v_cache = cache->v; a.max_len = cache->max_len;
+        a.decode = 1;
+        for (int b = 0; b < B; ++b) {
+            const int keys = cache->h_len[(size_t)bt->slots[b]] + 1;
+            a.mean_keys += (double)keys / B;
+            a.max_keys = std::max(a.max_keys, keys);
+        }
+        rope_in_f32 = c.dtype == PD_F32 && attn_decode_rope_f32_supported(a, r);
+    }
+    if (!fused_rope && !rope_in_f32) STEP("rope_kv_append", launch_rope_kv(c.dtype, r, s));
     if (mfma_dec) {
         DecodeAttnArgs da;
         memset(&da, 0, sizeof(da));
@@ -1395,18 +1431,9 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
         da.part_o = L->dec_part;
         da.part_ml = L->dec_part + (size_t)total_chunks * c.n_q_heads * 128;
         STEP("decode_attention", launch_decode_attn_mfma(da, s));
+    } else if (rope_in_f32) {
+        STEP("decode_attention", launch_attn_decode_rope_f32(a, r, s));
     } else {
-        AttnArgs a;
-        memset(&a, 0, sizeof(a));
-        a.qkv = L->qkv; a.ld = L->Nqkv; a.o = L->o; a.T = B; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads;
-        a.hd = c.head_dim; a.scale = (float)(1.0 / sqrt((double)c.head_dim)); a.tok_pos = L->tok_pos;
-        a.tok_slot = L->d_slots; a.k_cache = cache->k; a.v_cache = cache->v; a.max_len = cache->max_len;
-        a.decode = 1;
-        for (int b = 0; b < B; ++b) {
-            const int keys = cache->h_len[(size_t)bt->slots[b]] + 1;
-            a.mean_keys += (double)keys / B;
-            a.max_keys = std::max(a.max_keys, keys);
-        }
         STEP("decode_attention", launch_attn_generic(c.dtype, a, s));
     }
     st = run_tail(L, bt->hidden, B, bt->router_logits, out, s, mfma_dec && fused_rope ? &r : nullptr);

@@ -250,6 +250,10 @@ struct GemmArgs {
     float fuse_eps;
     const RopeArgs *fuse_append;
     int *fuse_done;
+    // fp32 products on small tiles (gemm_f32_norm_supported): A holds rows that are normalised on the way,
+    // A <- rmsnorm(A; norm_g, norm_eps) over all K columns
+    const float *norm_g;
+    float norm_eps;
 };
 
 // ---- launchers (each returns hipGetLastError() after the launch) ------------------------------
@@ -258,6 +262,7 @@ hipError_t launch_rmsnorm(int dtype, const void *x, const void *g, void *y, int 
 hipError_t launch_gemm_generic(int dtype, const GemmArgs &a, hipStream_t s);   // fp32: through the next where it can
 bool gemm_f32_mfma_supported(const GemmArgs &a);
 hipError_t launch_gemm_f32_mfma(const GemmArgs &a, hipStream_t s);
+bool gemm_f32_norm_supported(const GemmArgs &a);                 // a.norm_g set: the norm rides in the product
 bool gemm_mfma_supported(const GemmArgs &a);
 hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s);   // bf16 only
 bool gemm_mfma_f8_supported(const GemmArgs &a);                   // E4M3 x E4M3, dense
@@ -296,6 +301,9 @@ hipError_t launch_prefill_meta(int32_t *const dst[4], const int32_t *const host_
 hipError_t launch_scatter_ints(int32_t *dst, const int32_t *host_idx, const int32_t *host_val, int n,
                                hipStream_t s);
 // decode meta: for b in [0,B): pos[b] = len[slot[b]]; len[slot[b]] += 1
+// the same with up to 256 slots taken from the host array (and stored to d_slots): one launch
+hipError_t launch_decode_meta_upload(const int32_t *host_slots, int32_t *d_slots, int B, int32_t *d_len, int32_t *d_pos,
+                                     hipStream_t s);
 hipError_t launch_decode_meta(const int32_t *d_slots, int B, int32_t *d_len, int32_t *d_pos,
                               hipStream_t s);
 // prefill: len[slot[s]] = cu[s+1]-cu[s]  (add != 0: += instead of =)
@@ -422,6 +430,10 @@ struct AttnArgs {
     int32_t q_tiles;         // prefill: 16-row tiles that the sequences have in all
 };
 hipError_t launch_attn_generic(int dtype, const AttnArgs &a, hipStream_t s);
+// fp32 decode step over a plain cache with the rotary embedding and the cache append in the attention's launch: qkv holds
+// unrotated rows, and the new token's key and value join from there.  Where the attention takes another form: not supported.
+bool attn_decode_rope_f32_supported(const AttnArgs &a, const RopeArgs &r);
+hipError_t launch_attn_decode_rope_f32(const AttnArgs &a, const RopeArgs &r, hipStream_t s);
 bool attn_prefill_mfma_supported(const AttnArgs &a);
 // bf16, hd = 128.  vt: V transposed (launch_rope_tile), [Hkv][128][vt_ld] with vt_ld = padded token count
 // (each sequence start rounded up to a multiple of 64), zero past each sequence's end; pad_cu: device
