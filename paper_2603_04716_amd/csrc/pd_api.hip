@@ -1085,17 +1085,28 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
         const pd_status rs = reserve_attn_scratch(L, need, full, "pd_prefill");
         if (rs != PD_OK) return rs;
     }
+    PrefillDone done;
     {
         int32_t *const dst[4] = {L->d_cu, L->d_pad_cu, L->d_slots, L->d_prefix};
         const int32_t *const src[4] = {tk->cu_seqlens, pad.data(), tk->slots, prefix.data()};
         const int cnt[4] = {n + 1, n + 1, keep ? n : 0, chunk ? n : 0};
-        HIP_TRY(launch_prefill_meta(dst, src, cnt, n, T, L->tok_seq, L->tok_pos, L->tok_slot, s), PD_ERR_DEVICE);
+        // the first norm rides along where its rows stay bf16
+        PrefillNorm norm = PrefillNorm();
+        if (c.dtype == PD_BF16 && !(L->a8 && c.n_experts == 0 && T > kA8Rows))
+            norm = PrefillNorm{tk->hidden, L->g_attn, L->y, c.d_model, c.rms_eps};
+        int32_t *const len = keep ? cache->d_len : nullptr;
+        if (norm.x) prof_begin(L, "rmsnorm_attn", s);
+        HIP_TRY(launch_prefill_meta(dst, src, cnt, n, T, L->tok_seq, L->tok_pos, L->tok_slot, len, chunk ? 1 : 0, norm, &done, s),
+                PD_ERR_DEVICE);
+        if (done.norm) prof_end(L, s);
+        else if (norm.x && L->prof_on && !L->prof_names.empty()) L->prof_names.pop_back();
+        if (done.norm) L->a8_src = nullptr;
     }
     GemmArgs g;
     memset(&g, 0, sizeof(g));
     g.A = L->y; g.lda = c.d_model; g.B = L->w_qkv; g.ldb = c.d_model; g.C = L->qkv; g.ldc = L->Nqkv;
     g.M = T; g.N = L->Nqkv; g.K = c.d_model; g.epilogue = EPI_NONE; g.n_groups = 1;
-    if (!norm_in_gemm(L, g, tk->hidden, L->g_attn)) STEP("rmsnorm_attn", norm_for_gemm(L, tk->hidden, L->g_attn, L->y, T, s));
+    if (!done.norm && !norm_in_gemm(L, g, tk->hidden, L->g_attn)) STEP("rmsnorm_attn", norm_for_gemm(L, tk->hidden, L->g_attn, L->y, T, s));
     STEP("qkv_proj", run_gemm(L, g, s));
     RopeArgs r;
     r.qkv = L->qkv; r.ld = L->Nqkv; r.T = T; r.Hq = c.n_q_heads; r.Hkv = c.n_kv_heads; r.hd = c.head_dim;
@@ -1202,7 +1213,7 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
     st = run_tail(L, tk->hidden, T, tk->router_logits, out, s);
     if (st != PD_OK) return st;
     if (keep) {
-        HIP_TRY(launch_prefill_set_len(L->d_slots, L->d_cu, n, cache->d_len, chunk ? 1 : 0, s), PD_ERR_DEVICE);
+        if (!done.len) HIP_TRY(launch_prefill_set_len(L->d_slots, L->d_cu, n, cache->d_len, chunk ? 1 : 0, s), PD_ERR_DEVICE);
         for (int q = 0; q < n; ++q)
             cache->h_len[(size_t)tk->slots[q]] = prefix[(size_t)q] + tk->cu_seqlens[q + 1] - tk->cu_seqlens[q];
     }
