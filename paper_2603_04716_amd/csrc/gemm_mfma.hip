@@ -732,8 +732,8 @@ static int grouped_splits(const GemmArgs &a, int BN)
     return splits < 1 ? 1 : splits;
 }
 
-// Tile and K split of a product of more than 256 rows (or rows per group), and of a dense one of fewer, for both operand widths (a k-tile is 64 x 2
-// bytes wide in either, and takes the same time).  256 x 256 tiles are the fastest per flop, but a launch runs in
+// Tile and K split of a product of more than 256 rows (or 160 rows per group), and of a dense one of fewer, for both
+// operand widths (a k-tile is 64 x 2 bytes wide in either, and takes the same time).  256 x 256 tiles are the fastest per flop, but a launch runs in
 // rounds of one workgroup per CU: a few hundred to a few thousand rows fill the last round badly, and so do 257 rows
 // that take two row tiles.  Each form's time is therefore estimated as
 //   start + k-tiles per split x (full rounds x time of a k-tile + the last round's, from few workgroups to a full one)
@@ -882,11 +882,18 @@ hipError_t launch_gemm_mfma_f8(const GemmArgs &a, hipStream_t s)
 hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s)
 {
     if (!a.group_offsets) return launch_planned<false>(a, s);
-    // rows that share a weight matrix: the mean group size picks the tile (larger groups take several row tiles)
+    // Rows that share a weight matrix: the mean group size picks the tile.  A group that outgrows its row tile takes a second
+    // one, which reads the weights again, and groups spread around the mean by about its square root; a taller tile
+    // costs little while the launch is bound by the weight stream.  So 128-row tiles from 33 rows on (8 experts of 4096 x
+    // 14336, one layer: the same 631 - 655 us with either up to 52 rows, where no group had 64; 63 rows on the average, three
+    // routings, 768 / 825 / 813 us with 64-row tiles, 672 / 673 / 675 with these), 256-row tiles where a tenth of the groups or so
+    // would outgrow 128 (mean + 2 x its root: 105 rows 686 us, with the taller tile 721; 110 rows 823 / 838 and 725 / 729;
+    // 128 rows 921 / 902 and 743 / 740), and the estimate of plan_tiles, which counts those second tiles, from 161 rows on (175 rows
+    // 836 -> 783 us, 225 rows 888 -> 863, 237 rows 903 -> 909, 250 rows 1168 -> 1003, 255 rows 1289 -> 1042).
     const int rows = (a.M + a.n_groups - 1) / a.n_groups;
-    if (rows > 256) return launch_planned<false>(a, s);
-    if (rows > 128) return launch_cfg<256, 128, 2, 2, 3>(a, s, grouped_splits(a, 128));
-    if (rows > 64) return launch_cfg<128, 128, 2, 2, 3>(a, s, grouped_splits(a, 128));
+    if (rows > 160) return launch_planned<false>(a, s);
+    if (rows > 107) return launch_cfg<256, 128, 2, 2, 3>(a, s, grouped_splits(a, 128));
+    if (rows > 32) return launch_cfg<128, 128, 2, 2, 3>(a, s, grouped_splits(a, 128));
     return launch_cfg<64, 128, 2, 2, 4>(a, s, grouped_splits(a, 128));
 }
 
