@@ -32,8 +32,8 @@ DECODE_REPS = 3                    # decode steps per batch size per step; media
 # the FETCH_SIZE / WRITE_SIZE counters scaled by a plain copy (paper_2603_04716_amd/traffic_probe.py).
 # Valid only for the kernel source the counters were taken on.
 TRAFFIC = {"source": os.path.join("paper_2603_04716_amd", "csrc", "gemm_mfma.hip"),
-           "sha256": "f36e88aab575f12cb2937e37e74d4f08980c308af0af2d531b8b0c086eded7cb",
-           "bytes_per_launch": 3054.1e6}
+           "sha256": "d53a4a94b0a0f4f003b242bd4e1a4386d9b8d7948d0645631e3d0bf057a20ea0",
+           "bytes_per_launch": 3054.3e6}
 
 
 def counted_traffic():
