@@ -132,10 +132,12 @@ static int pick_chunk_keys(const std::vector<int32_t> &keys, int n_kv_heads, siz
 static const int kShortChunk = 8;   // chunks up to this many tokens use the decode attention kernel per row
 static const int kRopeTableLen = 32768;   // positions with precomputed rotary factors
 
+// A failure that has been reported is taken back from the runtime, or the next launch's check would report it again.
 #define HIP_TRY(expr, status)                                                        \
     do {                                                                             \
         hipError_t e__ = (expr);                                                     \
         if (e__ != hipSuccess) {                                                     \
+            (void)hipGetLastError();                                                 \
             set_error("%s failed: %s", #expr, hipGetErrorString(e__));               \
             return (e__ == hipErrorOutOfMemory) ? PD_ERR_OOM : (status);             \
         }                                                                            \
@@ -355,6 +357,7 @@ static pd_status layer_create(const pd_layer_config *cfg, const pd_layer_weights
     do {                                                                               \
         hipError_t e__ = (expr);                                                       \
         if (e__ != hipSuccess) {                                                       \
+            (void)hipGetLastError();                                                   \
             set_error("pd_layer_create: %s failed: %s", #expr, hipGetErrorString(e__)); \
             return fail(e__ == hipErrorOutOfMemory ? PD_ERR_OOM : PD_ERR_DEVICE);      \
         }                                                                              \
@@ -617,6 +620,7 @@ extern "C" pd_status pd_layer_reserve(pd_layer *L, int32_t max_tokens)
     char *nw = nullptr;
     hipError_t e = hipMalloc((void **)&nw, w.total);
     if (e != hipSuccess) {
+        (void)hipGetLastError();
         set_error("pd_layer_reserve: cannot allocate %zu bytes of workspace: %s", w.total, hipGetErrorString(e));
         return PD_ERR_OOM;
     }
@@ -676,6 +680,7 @@ static pd_status cache_create(const pd_layer *L, int32_t max_seqs, int32_t max_l
         if (c->v) (void)hipFree(c->v);
         if (c->d_len) (void)hipFree(c->d_len);
         delete c;
+        (void)hipGetLastError();
         return e == hipErrorOutOfMemory ? PD_ERR_OOM : PD_ERR_DEVICE;
     }
     c->h_len.assign((size_t)max_seqs, 0);
@@ -941,6 +946,7 @@ static pd_status reserve_attn_scratch(pd_layer *L, size_t need, size_t ahead, co
         e = hipMalloc(&L->vt, bytes);
     }
     if (e != hipSuccess) {
+        (void)hipGetLastError();
         L->vt = nullptr;
         set_error("%s: cannot allocate %zu bytes of attention scratch", who, need);
         return PD_ERR_OOM;
@@ -1594,6 +1600,7 @@ static pd_status head_create(int32_t d_model, int32_t vocab, float rms_eps, pd_d
         if (e__ != hipSuccess) {                                                       \
             set_error("pd_head_create: %s failed: %s", #expr, hipGetErrorString(e__)); \
             free_head(h);                                                              \
+            (void)hipGetLastError();                                                   \
             return e__ == hipErrorOutOfMemory ? PD_ERR_OOM : PD_ERR_DEVICE;            \
         }                                                                              \
     } while (0)

@@ -1,0 +1,24 @@
+"""The library's host code (csrc/pd_api.hip and the launchers) run on the CPU, over a stand-in for the HIP runtime: what a
+call leaves behind when one of its launches or allocations fails."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB_DIR = os.path.join(ROOT, "paper_2603_04716_amd")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("launches") / "driver")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-Wall", "-Wno-missing-field-initializers", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
+                    "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "host_launches_driver.cpp"),
+                    os.path.join(LIB_DIR, "libpd_mi355x.so"), "-rdynamic", f"-Wl,-rpath,{LIB_DIR}",
+                    "-Wl,--unresolved-symbols=ignore-in-shared-libs", "-o", exe], check=True)
+    return exe
+
+
+def test_a_call_succeeds_after_one_that_failed(driver):
+    r = subprocess.run([driver], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
