@@ -332,7 +332,7 @@ hipError_t launch_token_meta(const int32_t *d_cu, const int32_t *d_slots, const 
 // leaves (nothing in between reads them): a launch of 3 - 5 us of its own before.
 __device__ __forceinline__ void prefill_meta_body(int block, const IntDst4 &d, const IntChunk &c, int n_seqs, int T,
                                                   int32_t *__restrict__ tok_seq, int32_t *__restrict__ tok_pos,
-                                                  int32_t *__restrict__ tok_slot, int32_t *len, int add)
+                                                  int32_t *__restrict__ tok_slot, int32_t *len, int32_t *len_was, int add)
 {
     if (block == 0) {
         const int i = threadIdx.x;
@@ -341,8 +341,9 @@ __device__ __forceinline__ void prefill_meta_body(int block, const IntDst4 &d, c
             d.dst[k][i - d.start[k]] = c.v[i];
         }
         if (len && i < n_seqs) {
-            const int s = c.v[d.start[2] + i];     // slots are distinct
-            len[s] = (add ? len[s] : 0) + c.v[i + 1] - c.v[i];
+            const int s = c.v[d.start[2] + i], was = len[s];     // slots are distinct
+            len_was[i] = was;
+            len[s] = (add ? was : 0) + c.v[i + 1] - c.v[i];
         }
     }
     const int t = block * 256 + threadIdx.x;
@@ -360,23 +361,23 @@ __device__ __forceinline__ void prefill_meta_body(int block, const IntDst4 &d, c
 
 __global__ __launch_bounds__(256) void prefill_meta_kernel(IntDst4 d, IntChunk c, int n_seqs, int T, int32_t *__restrict__ tok_seq,
                                                            int32_t *__restrict__ tok_pos, int32_t *__restrict__ tok_slot,
-                                                           int32_t *len, int add)
+                                                           int32_t *len, int32_t *len_was, int add)
 {
-    prefill_meta_body(blockIdx.x, d, c, n_seqs, T, tok_seq, tok_pos, tok_slot, len, add);
+    prefill_meta_body(blockIdx.x, d, c, n_seqs, T, tok_seq, tok_pos, tok_slot, len, len_was, add);
 }
 
 // That and the call's first RMSNorm (bf16 rows, d a multiple of 8) in one launch: neither needs the other.  A chunk of 512
 // tokens: 4.9 + 5.4 us -> 5.6.
 __global__ __launch_bounds__(256) void prefill_meta_norm_kernel(IntDst4 d, IntChunk c, int n_seqs, int T, int32_t *__restrict__ tok_seq,
                                                                 int32_t *__restrict__ tok_pos, int32_t *__restrict__ tok_slot,
-                                                                int32_t *len, int add, const uint4 *__restrict__ x,
+                                                                int32_t *len, int32_t *len_was, int add, const uint4 *__restrict__ x,
                                                                 const uint4 *__restrict__ g, uint4 *__restrict__ y, int d8,
                                                                 float d_inv, float eps)
 {
     __shared__ float red[4];
     const int meta = (T + 255) / 256;
     if ((int)blockIdx.x < meta) {
-        prefill_meta_body(blockIdx.x, d, c, n_seqs, T, tok_seq, tok_pos, tok_slot, len, add);
+        prefill_meta_body(blockIdx.x, d, c, n_seqs, T, tok_seq, tok_pos, tok_slot, len, len_was, add);
         return;
     }
     const size_t row = blockIdx.x - meta;
@@ -385,7 +386,7 @@ __global__ __launch_bounds__(256) void prefill_meta_norm_kernel(IntDst4 d, IntCh
 
 hipError_t launch_prefill_meta(int32_t *const dst[4], const int32_t *const host_src[4], const int n[4],
                                int n_seqs, int T, int32_t *tok_seq, int32_t *tok_pos, int32_t *tok_slot,
-                               int32_t *len, int add, const PrefillNorm &norm, PrefillDone *done, hipStream_t s)
+                               int32_t *len, int32_t *len_was, int add, const PrefillNorm &norm, PrefillDone *done, hipStream_t s)
 {
     *done = PrefillDone();
     const int total = n[0] + n[1] + n[2] + n[3];
@@ -408,11 +409,11 @@ hipError_t launch_prefill_meta(int32_t *const dst[4], const int32_t *const host_
     const unsigned meta = (unsigned)((T + 255) / 256);
     if (!n[2]) len = nullptr;
     if (norm.x && norm.d % 8 == 0) {
-        prefill_meta_norm_kernel<<<meta + (unsigned)T, 256, 0, s>>>(d, c, n_seqs, T, tok_seq, tok_pos, tok_slot, len, add, (const uint4 *)norm.x,
-                                                                    (const uint4 *)norm.g, (uint4 *)norm.y, norm.d / 8, 1.0f / (float)norm.d, norm.eps);
+        prefill_meta_norm_kernel<<<meta + (unsigned)T, 256, 0, s>>>(d, c, n_seqs, T, tok_seq, tok_pos, tok_slot, len, len_was, add,
+                                                                    (const uint4 *)norm.x, (const uint4 *)norm.g, (uint4 *)norm.y, norm.d / 8, 1.0f / (float)norm.d, norm.eps);
         done->norm = true;
     } else {
-        prefill_meta_kernel<<<meta, 256, 0, s>>>(d, c, n_seqs, T, tok_seq, tok_pos, tok_slot, len, add);
+        prefill_meta_kernel<<<meta, 256, 0, s>>>(d, c, n_seqs, T, tok_seq, tok_pos, tok_slot, len, len_was, add);
     }
     done->len = len != nullptr;
     return hipGetLastError();
@@ -467,6 +468,18 @@ hipError_t launch_prefill_set_len(const int32_t *d_slots, const int32_t *d_cu, i
                                   int32_t *d_len, int add, hipStream_t s)
 {
     prefill_set_len_kernel<<<(n_seqs + 255) / 256, 256, 0, s>>>(d_slots, d_cu, n_seqs, d_len, add);
+    return hipGetLastError();
+}
+
+__global__ void prefill_restore_len_kernel(const int32_t *__restrict__ slots, const int32_t *__restrict__ was, int n, int32_t *len)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) len[slots[i]] = was[i];
+}
+
+hipError_t launch_prefill_restore_len(const int32_t *d_slots, const int32_t *d_len_was, int n_seqs, int32_t *d_len, hipStream_t s)
+{
+    prefill_restore_len_kernel<<<(n_seqs + 255) / 256, 256, 0, s>>>(d_slots, d_len_was, n_seqs, d_len);
     return hipGetLastError();
 }
 

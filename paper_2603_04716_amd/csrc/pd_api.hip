@@ -37,6 +37,7 @@ struct pd_layer {
     double *inv_freq;
     float2 *rope_table;       // (cos, sin) for positions < kRopeTableLen
     int32_t *d_cu, *d_slots, *d_pad_cu, *d_prefix;  // [4097] each
+    int32_t *d_len_was;       // [4097]: cache lengths that the prefill call in progress found (see LenGuard)
     int32_t *units;           // [4][ws_tokens]: slot, first position, first row, token count of multi-token units
     void *vt;                 // transposed-V scratch for the MFMA attention, vt_cap bytes
     size_t vt_cap;
@@ -271,7 +272,8 @@ static void free_layer(pd_layer *L)
     void *ptrs[] = {L->q_qkv, L->q_o, L->q_gate, L->q_down, L->s_qkv, L->s_o, L->s_gate, L->s_down,
                     L->t_qkv, L->t_o, L->t_gate, L->t_down,
                     L->g_attn, L->g_ffn, L->w_qkv, L->w_o, L->w_gate, L->w_up, L->w_down,
-                    L->w_router, L->inv_freq, L->rope_table, L->d_cu, L->d_slots, L->d_pad_cu, L->d_prefix, L->vt, L->ws};
+                    L->w_router, L->inv_freq, L->rope_table, L->d_cu, L->d_slots, L->d_pad_cu, L->d_prefix,
+                    L->d_len_was, L->vt, L->ws};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (hipEvent_t e : L->prof_ev) (void)hipEventDestroy(e);
@@ -373,6 +375,7 @@ static pd_status layer_create(const pd_layer_config *cfg, const pd_layer_weights
     CREATE_TRY(hipMalloc(&L->d_slots, sizeof(int32_t) * (kMaxSeqs + 1)));
     CREATE_TRY(hipMalloc(&L->d_pad_cu, sizeof(int32_t) * (kMaxSeqs + 1)));
     CREATE_TRY(hipMalloc(&L->d_prefix, sizeof(int32_t) * (kMaxSeqs + 1)));
+    CREATE_TRY(hipMalloc(&L->d_len_was, sizeof(int32_t) * (kMaxSeqs + 1)));
     CREATE_TRY(hipMemcpy(L->g_attn, w->g_attn, d * esz, hipMemcpyDeviceToDevice));
     CREATE_TRY(hipMemcpy(L->g_ffn, w->g_ffn, d * esz, hipMemcpyDeviceToDevice));
     if (L->packed) {
@@ -955,6 +958,21 @@ static pd_status reserve_attn_scratch(pd_layer *L, size_t need, size_t ahead, co
     return PD_OK;
 }
 
+// The first launch of a prefill call already brings the device's cache lengths up to what the call leaves.  Where a later
+// step fails, the host's lengths stay as they were, and this puts the device's back to what that launch found: decode steps
+// take their positions from the device's lengths and their capacity check from the host's.
+struct LenGuard {
+    const pd_layer *L;
+    pd_kv_cache *cache;
+    int n;
+    hipStream_t s;
+    bool armed;
+    ~LenGuard()
+    {
+        if (armed) (void)launch_prefill_restore_len(L->d_slots, L->d_len_was, n, cache->d_len, s);
+    }
+};
+
 // Shared body of pd_prefill (chunk = false: positions from 0, a cache slot is overwritten) and
 // pd_prefill_chunk (chunk = true: positions behind the slot's cached prefix, appended).
 static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *cache, void *out,
@@ -1091,6 +1109,57 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
         const pd_status rs = reserve_attn_scratch(L, need, full, "pd_prefill");
         if (rs != PD_OK) return rs;
     }
+    // Short chunks: the units of the decode attention kernel
+    std::vector<int32_t> u_slot, u_pos, u_row, u_cnt, ccu;
+    int nu = 0, chunk_keys = 0, total_chunks = 0;
+    float *part = nullptr;
+    if (short_chunk) {
+        // A few new tokens per sequence over a blocked cache (multi-token decode): the decode
+        // attention kernel streams the cache once per unit of a few tokens instead of gathering the
+        // prefix for the prefill kernel.
+        // Units of up to 16 / group consecutive tokens of one sequence share one pass over the cache:
+        // their (token, head) pairs are the 16 MFMA columns of the decode attention kernel.
+        const int tb = 16 / (c.n_q_heads / c.n_kv_heads);
+        std::vector<int32_t> u_keys;
+        for (int q = 0; q < n; ++q) {
+            const int Ls = tk->cu_seqlens[q + 1] - tk->cu_seqlens[q];
+            for (int i0 = 0; i0 < Ls; i0 += tb) {
+                const int cnt = Ls - i0 < tb ? Ls - i0 : tb;
+                u_slot.push_back(tk->slots[q]);
+                u_pos.push_back(prefix[(size_t)q] + i0);
+                u_row.push_back(tk->cu_seqlens[q] + i0);
+                u_cnt.push_back(cnt);
+                u_keys.push_back(prefix[(size_t)q] + i0 + cnt);
+            }
+        }
+        nu = (int)u_slot.size();
+        // Partial results are rows of 130 floats, [chunk][kv head][16 columns]; the workspace part holds
+        // what a one-token decode step of ws_tokens rows needs.  Every unit needs at least one chunk, so a
+        // call of many short sequences can need more than that: the rest comes from the attention scratch
+        // buffer (unused on this path), grown on demand like for an ordinary prefill.
+        const size_t rows_per_chunk = (size_t)c.n_kv_heads * 16;
+        const size_t ws_rows = decode_chunk_bound(L, L->ws_tokens) * c.n_q_heads;
+        size_t max_chunks = ws_rows / rows_per_chunk;
+        const size_t floor_chunks = (size_t)nu + (size_t)(8192 / c.n_kv_heads + 1);
+        if (max_chunks < floor_chunks) max_chunks = floor_chunks;
+        chunk_keys = pick_chunk_keys(u_keys, c.n_kv_heads, max_chunks);
+        ccu.resize((size_t)nu + 1);
+        ccu[0] = 0;
+        for (int u = 0; u < nu; ++u)
+            ccu[(size_t)u + 1] = ccu[(size_t)u] + (u_pos[(size_t)u] + u_cnt[(size_t)u] + chunk_keys - 1) / chunk_keys;
+        total_chunks = ccu[(size_t)nu];
+        if ((size_t)total_chunks > max_chunks) {
+            set_error("pd_prefill_chunk: internal chunk bound exceeded (%d chunks)", total_chunks);
+            return PD_ERR_DEVICE;
+        }
+        part = L->dec_part;
+        if ((size_t)total_chunks * rows_per_chunk > ws_rows) {
+            const size_t need = (size_t)total_chunks * rows_per_chunk * 130 * sizeof(float);
+            const pd_status rs = reserve_attn_scratch(L, need, 0, "pd_prefill_chunk");
+            if (rs != PD_OK) return rs;
+            part = (float *)L->vt;
+        }
+    }
     PrefillDone done;
     {
         int32_t *const dst[4] = {L->d_cu, L->d_pad_cu, L->d_slots, L->d_prefix};
@@ -1102,12 +1171,14 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
             norm = PrefillNorm{tk->hidden, L->g_attn, L->y, c.d_model, c.rms_eps};
         int32_t *const len = keep ? cache->d_len : nullptr;
         if (norm.x) prof_begin(L, "rmsnorm_attn", s);
-        HIP_TRY(launch_prefill_meta(dst, src, cnt, n, T, L->tok_seq, L->tok_pos, L->tok_slot, len, chunk ? 1 : 0, norm, &done, s),
+        HIP_TRY(launch_prefill_meta(dst, src, cnt, n, T, L->tok_seq, L->tok_pos, L->tok_slot, len, L->d_len_was, chunk ? 1 : 0, norm,
+                                    &done, s),
                 PD_ERR_DEVICE);
         if (done.norm) prof_end(L, s);
         else if (norm.x && L->prof_on && !L->prof_names.empty()) L->prof_names.pop_back();
         if (done.norm) L->a8_src = nullptr;
     }
+    LenGuard lens = {L, cache, n, s, done.len};
     GemmArgs g;
     memset(&g, 0, sizeof(g));
     g.A = L->y; g.lda = c.d_model; g.B = L->w_qkv; g.ldb = c.d_model; g.C = L->qkv; g.ldc = L->Nqkv;
@@ -1141,51 +1212,6 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
         a.max_len = cache->max_len;
         STEP("prefill_attention", launch_attn_generic(c.dtype, a, s));
     } else if (short_chunk) {
-        // A few new tokens per sequence over a blocked cache (multi-token decode): the decode
-        // attention kernel streams the cache once per unit of a few tokens instead of gathering the
-        // prefix for the prefill kernel.
-        // Units of up to 16 / group consecutive tokens of one sequence share one pass over the cache:
-        // their (token, head) pairs are the 16 MFMA columns of the decode attention kernel.
-        const int tb = 16 / (c.n_q_heads / c.n_kv_heads);
-        std::vector<int32_t> u_slot, u_pos, u_row, u_cnt, u_keys;
-        for (int q = 0; q < n; ++q) {
-            const int Ls = tk->cu_seqlens[q + 1] - tk->cu_seqlens[q];
-            for (int i0 = 0; i0 < Ls; i0 += tb) {
-                const int cnt = Ls - i0 < tb ? Ls - i0 : tb;
-                u_slot.push_back(tk->slots[q]);
-                u_pos.push_back(prefix[(size_t)q] + i0);
-                u_row.push_back(tk->cu_seqlens[q] + i0);
-                u_cnt.push_back(cnt);
-                u_keys.push_back(prefix[(size_t)q] + i0 + cnt);
-            }
-        }
-        const int nu = (int)u_slot.size();
-        // Partial results are rows of 130 floats, [chunk][kv head][16 columns]; the workspace part holds
-        // what a one-token decode step of ws_tokens rows needs.  Every unit needs at least one chunk, so a
-        // call of many short sequences can need more than that: the rest comes from the attention scratch
-        // buffer (unused on this path), grown on demand like for an ordinary prefill.
-        const size_t rows_per_chunk = (size_t)c.n_kv_heads * 16;
-        const size_t ws_rows = decode_chunk_bound(L, L->ws_tokens) * c.n_q_heads;
-        size_t max_chunks = ws_rows / rows_per_chunk;
-        const size_t floor_chunks = (size_t)nu + (size_t)(8192 / c.n_kv_heads + 1);
-        if (max_chunks < floor_chunks) max_chunks = floor_chunks;
-        const int chunk_keys = pick_chunk_keys(u_keys, c.n_kv_heads, max_chunks);
-        std::vector<int32_t> ccu((size_t)nu + 1);
-        ccu[0] = 0;
-        for (int u = 0; u < nu; ++u)
-            ccu[(size_t)u + 1] = ccu[(size_t)u] + (u_pos[(size_t)u] + u_cnt[(size_t)u] + chunk_keys - 1) / chunk_keys;
-        const int total_chunks = ccu[(size_t)nu];
-        if ((size_t)total_chunks > max_chunks) {
-            set_error("pd_prefill_chunk: internal chunk bound exceeded (%d chunks)", total_chunks);
-            return PD_ERR_DEVICE;
-        }
-        float *part = L->dec_part;
-        if ((size_t)total_chunks * rows_per_chunk > ws_rows) {
-            const size_t need = (size_t)total_chunks * rows_per_chunk * 130 * sizeof(float);
-            const pd_status rs = reserve_attn_scratch(L, need, 0, "pd_prefill_chunk");
-            if (rs != PD_OK) return rs;
-            part = (float *)L->vt;
-        }
         const size_t ws_t = (size_t)L->ws_tokens;
         HIP_TRY(launch_write_ints(L->chunk_cu, ccu.data(), nu + 1, s), PD_ERR_DEVICE);
         HIP_TRY(launch_write_ints(L->units, u_slot.data(), nu, s), PD_ERR_DEVICE);
@@ -1223,6 +1249,7 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
         for (int q = 0; q < n; ++q)
             cache->h_len[(size_t)tk->slots[q]] = prefix[(size_t)q] + tk->cu_seqlens[q + 1] - tk->cu_seqlens[q];
     }
+    lens.armed = false;
     L->last_rows = T;
     return PD_OK;
 }

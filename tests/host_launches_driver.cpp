@@ -1,10 +1,11 @@
 // Driver for tests/test_host_launches.py: the library's host code on a stand-in for the HIP runtime.  The runtime's
 // entry points that the library imports are defined here, and an executable's definitions come before a shared
 // library's: "device" memory is host memory, a launch is counted and refused where the GPU would refuse its grid, and
-// nothing else is carried out.  Test infrastructure only.
+// of the kernels only those that write sequence arrays and cache lengths are carried out.  Test infrastructure only.
 //
-// failures  every launch and every allocation of a prefill call fails in turn: the call has to return an error, and the same
-//           call has to succeed afterwards.
+// failures  every launch and every allocation of a prefill call fails in turn: the call has to return an error, the
+//           cache lengths on the device and on the host have to be what they were, and the same call has to
+//           succeed afterwards with the lengths that it would have left at once.
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -31,6 +32,7 @@ static int32_t *g_written;                  // where the last write_ints launch 
 static struct { dim3 grid, block; size_t shared; hipStream_t stream; } g_config;
 
 struct Chunk { int32_t v[960]; };           // the library's by-value arrays of 256 and 960 entries start alike
+struct Dst4 { int32_t *dst[4]; int32_t start[5]; };
 
 static void carry_out(const std::string &name, void **args)
 {
@@ -39,6 +41,26 @@ static void carry_out(const std::string &name, void **args)
     if (is("write_ints_kernel")) {
         g_written = ARG(int32_t *, 0);
         memcpy(g_written, ((const Chunk *)args[1])->v, sizeof(int32_t) * (size_t)ARG(int, 2));
+    } else if (is("write_ints4_kernel") || is("prefill_meta_kernel") || is("prefill_meta_norm_kernel")) {
+        const Dst4 &d = ARG(Dst4, 0);
+        const int32_t *v = ((const Chunk *)args[1])->v;
+        for (int k = 0; k < 4; ++k)
+            for (int i = d.start[k]; i < d.start[k + 1]; ++i) d.dst[k][i - d.start[k]] = v[i];
+        if (is("write_ints4_kernel")) return;
+        int32_t *len = ARG(int32_t *, 7), *was = ARG(int32_t *, 8);
+        for (int i = 0; len && i < ARG(int, 2); ++i) {
+            const int s = v[d.start[2] + i];
+            was[i] = len[s];
+            len[s] = (ARG(int, 9) ? len[s] : 0) + v[i + 1] - v[i];
+        }
+    } else if (is("prefill_set_len_kernel")) {
+        const int32_t *slots = ARG(const int32_t *, 0), *cu = ARG(const int32_t *, 1);
+        int32_t *len = ARG(int32_t *, 3);
+        for (int i = 0; i < ARG(int, 2); ++i) len[slots[i]] = (ARG(int, 4) ? len[slots[i]] : 0) + cu[i + 1] - cu[i];
+    } else if (is("prefill_restore_len_kernel")) {
+        const int32_t *slots = ARG(const int32_t *, 0), *was = ARG(const int32_t *, 1);
+        int32_t *len = ARG(int32_t *, 3);
+        for (int i = 0; i < ARG(int, 2); ++i) len[slots[i]] = was[i];
     }
 #undef ARG
 }
@@ -158,7 +180,17 @@ static void failures(const Case &k)
         pd_kv_cache *c = nullptr;
         CHECK(pd_kv_cache_create(L, n, max_len, &c) == PD_OK, "%s", pd_last_error());
         for (int s = n - 1; s >= 0; --s) CHECK(pd_kv_cache_set_len(c, slots[(size_t)s], k.before[(size_t)s], nullptr) == PD_OK, "%s", pd_last_error());
+        const int32_t *d_len = g_written - slots[0];
         CHECK(pd_layer_reserve(L, cu.back()) == PD_OK, "%s", pd_last_error());
+        auto lens_are = [&](bool after) {
+            for (int s = 0; s < n; ++s) {
+                const int want = after ? (k.chunk ? k.before[(size_t)s] : 0) + k.rows[(size_t)s] : k.before[(size_t)s];
+                int32_t h = -1;
+                pd_kv_cache_len(c, slots[(size_t)s], &h);
+                CHECK(d_len[slots[(size_t)s]] == want && h == want, "%s, step %ld of %ld launches + %ld allocations: sequence %d has %d on the device, %d on the host, not %d",
+                      k.name, step, launches, mallocs, s, d_len[slots[(size_t)s]], h, want);
+            }
+        };
         auto call = [&] { return k.chunk ? pd_prefill_chunk(L, &tk, c, out.data(), nullptr) : pd_prefill(L, &tk, c, out.data(), nullptr); };
         g_launches = g_mallocs = 0;
         g_fail_launch = step < launches ? step : -1;
@@ -170,10 +202,14 @@ static void failures(const Case &k)
             launches = g_launches;
             mallocs = g_mallocs;
             CHECK(launches >= 4 && mallocs >= k.min_mallocs, "%s: %ld launches, %ld allocations", k.name, launches, mallocs);
+            lens_are(true);
         } else if (st != PD_OK) {
+            lens_are(false);
             CHECK(call() == PD_OK, "%s", pd_last_error());
+            lens_are(true);
         } else {                            // a larger scratch than needed was refused, and the needed one taken
             CHECK(step >= launches, "%s: launch %ld failed and the call did not say so", k.name, step);
+            lens_are(true);
         }
         pd_kv_cache_destroy(c);
         pd_layer_destroy(L);
