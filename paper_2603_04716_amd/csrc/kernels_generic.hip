@@ -471,15 +471,15 @@ hipError_t launch_prefill_set_len(const int32_t *d_slots, const int32_t *d_cu, i
     return hipGetLastError();
 }
 
-__global__ void prefill_restore_len_kernel(const int32_t *__restrict__ slots, const int32_t *__restrict__ was, int n, int32_t *len)
+__global__ void restore_len_kernel(const int32_t *__restrict__ slots, const int32_t *__restrict__ was, int n, int32_t *len)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) len[slots[i]] = was[i];
 }
 
-hipError_t launch_prefill_restore_len(const int32_t *d_slots, const int32_t *d_len_was, int n_seqs, int32_t *d_len, hipStream_t s)
+hipError_t launch_restore_len(const int32_t *d_slots, const int32_t *d_was, int n_seqs, int32_t *d_len, hipStream_t s)
 {
-    prefill_restore_len_kernel<<<(n_seqs + 255) / 256, 256, 0, s>>>(d_slots, d_len_was, n_seqs, d_len);
+    restore_len_kernel<<<(n_seqs + 255) / 256, 256, 0, s>>>(d_slots, d_was, n_seqs, d_len);
     return hipGetLastError();
 }
 

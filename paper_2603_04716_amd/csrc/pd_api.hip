@@ -857,6 +857,21 @@ static bool cache_matches(const pd_layer *L, const pd_kv_cache *c)
     return c->dtype == L->cfg.dtype && c->Hkv == L->cfg.n_kv_heads && c->hd == L->cfg.head_dim;
 }
 
+// The first launch of a call already brings the device's cache lengths up to what the call leaves.  Where a later step
+// fails, the host's lengths stay as they were, and this puts the device's back to what that launch found (was, one per
+// sequence): decode steps take their positions from the device's lengths and their capacity check from the host's.
+struct LenGuard {
+    const int32_t *d_slots, *was;
+    int n;
+    int32_t *d_len;
+    hipStream_t s;
+    bool armed;
+    ~LenGuard()
+    {
+        if (armed) (void)launch_restore_len(d_slots, was, n, d_len, s);
+    }
+};
+
 // Everything after the attention output: O projection + residual, RMSNorm, FFN or MoE.
 // append (decode step with the fused rotary embedding, bf16 layers): the step's cache append rides in the
 // launch of the second RMSNorm.
@@ -957,21 +972,6 @@ static pd_status reserve_attn_scratch(pd_layer *L, size_t need, size_t ahead, co
     L->vt_cap = bytes;
     return PD_OK;
 }
-
-// The first launch of a prefill call already brings the device's cache lengths up to what the call leaves.  Where a later
-// step fails, the host's lengths stay as they were, and this puts the device's back to what that launch found: decode steps
-// take their positions from the device's lengths and their capacity check from the host's.
-struct LenGuard {
-    const pd_layer *L;
-    pd_kv_cache *cache;
-    int n;
-    hipStream_t s;
-    bool armed;
-    ~LenGuard()
-    {
-        if (armed) (void)launch_prefill_restore_len(L->d_slots, L->d_len_was, n, cache->d_len, s);
-    }
-};
 
 // Shared body of pd_prefill (chunk = false: positions from 0, a cache slot is overwritten) and
 // pd_prefill_chunk (chunk = true: positions behind the slot's cached prefix, appended).
@@ -1178,7 +1178,7 @@ static pd_status prefill_common(pd_layer *L, const pd_tokens *tk, pd_kv_cache *c
         else if (norm.x && L->prof_on && !L->prof_names.empty()) L->prof_names.pop_back();
         if (done.norm) L->a8_src = nullptr;
     }
-    LenGuard lens = {L, cache, n, s, done.len};
+    LenGuard lens = {L->d_slots, L->d_len_was, n, done.len ? cache->d_len : nullptr, s, done.len};
     GemmArgs g;
     memset(&g, 0, sizeof(g));
     g.A = L->y; g.lda = c.d_model; g.B = L->w_qkv; g.ldb = c.d_model; g.C = L->qkv; g.ldc = L->Nqkv;
@@ -1421,6 +1421,7 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
         else
             HIP_TRY(launch_decode_meta(L->d_slots, B, cache->d_len, L->tok_pos, s), PD_ERR_DEVICE);
     }
+    LenGuard lens = {L->d_slots, L->tok_pos, B, cache->d_len, s, true};   // the lengths found are the new tokens' positions
     GemmArgs g;
     memset(&g, 0, sizeof(g));
     g.A = bt->hidden; g.lda = c.d_model; g.B = L->w_qkv; g.ldb = c.d_model; g.C = L->qkv; g.ldc = L->Nqkv;
@@ -1482,6 +1483,7 @@ static pd_status decode_step_impl(pd_layer *L, const pd_batch *bt, pd_kv_cache *
     }
     st = run_tail(L, bt->hidden, B, bt->router_logits, out, s, mfma_dec && fused_rope ? &r : nullptr);
     if (st != PD_OK) return st;
+    lens.armed = false;
     for (int b = 0; b < B; ++b) cache->h_len[(size_t)bt->slots[b]] += 1;
     L->last_rows = B;
     return PD_OK;

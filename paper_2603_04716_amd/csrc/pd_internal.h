@@ -296,7 +296,7 @@ hipError_t launch_write_ints4(int32_t *const dst[4], const int32_t *const host_s
 // or none, 3 = prefixes or none) together with the per-token sequence index / position / slot.  Where the arrays fit
 // the launch's arguments it also updates the cache's lengths (len, as launch_prefill_set_len; null: none) and normalises the
 // call's bf16 rows (norm.x null: none); done says which of the two it did.  The lengths it found go to len_was [n_seqs], for
-// launch_prefill_restore_len where a later step of the call fails.
+// launch_restore_len where a later step of the call fails.
 struct PrefillNorm {
     const void *x, *g;
     void *y;
@@ -309,7 +309,6 @@ struct PrefillDone {
 hipError_t launch_prefill_meta(int32_t *const dst[4], const int32_t *const host_src[4], const int n[4],
                                int n_seqs, int T, int32_t *tok_seq, int32_t *tok_pos, int32_t *tok_slot,
                                int32_t *len, int32_t *len_was, int add, const PrefillNorm &norm, PrefillDone *done, hipStream_t s);
-hipError_t launch_prefill_restore_len(const int32_t *d_slots, const int32_t *d_len_was, int n_seqs, int32_t *d_len, hipStream_t s);
 // dst[idx[i]] = val[i] for i < n (host arrays, carried by value in the kernel arguments)
 hipError_t launch_scatter_ints(int32_t *dst, const int32_t *host_idx, const int32_t *host_val, int n,
                                hipStream_t s);
@@ -319,6 +318,8 @@ hipError_t launch_decode_meta_upload(const int32_t *host_slots, int32_t *d_slots
                                      hipStream_t s);
 hipError_t launch_decode_meta(const int32_t *d_slots, int B, int32_t *d_len, int32_t *d_pos,
                               hipStream_t s);
+// len[slot[i]] = was[i]
+hipError_t launch_restore_len(const int32_t *d_slots, const int32_t *d_was, int n_seqs, int32_t *d_len, hipStream_t s);
 // prefill: len[slot[s]] = cu[s+1]-cu[s]  (add != 0: += instead of =)
 hipError_t launch_prefill_set_len(const int32_t *d_slots, const int32_t *d_cu, int n_seqs,
                                   int32_t *d_len, int add, hipStream_t s);

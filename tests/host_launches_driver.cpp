@@ -3,7 +3,7 @@
 // library's: "device" memory is host memory, a launch is counted and refused where the GPU would refuse its grid, and
 // of the kernels only those that write sequence arrays and cache lengths are carried out.  Test infrastructure only.
 //
-// failures  every launch and every allocation of a prefill call fails in turn: the call has to return an error, the
+// failures  every launch and every allocation of a prefill call or a decode step fails in turn: the call has to return an error, the
 //           cache lengths on the device and on the host have to be what they were, and the same call has to
 //           succeed afterwards with the lengths that it would have left at once.
 #include <hip/hip_runtime_api.h>
@@ -57,7 +57,17 @@ static void carry_out(const std::string &name, void **args)
         const int32_t *slots = ARG(const int32_t *, 0), *cu = ARG(const int32_t *, 1);
         int32_t *len = ARG(int32_t *, 3);
         for (int i = 0; i < ARG(int, 2); ++i) len[slots[i]] = (ARG(int, 4) ? len[slots[i]] : 0) + cu[i + 1] - cu[i];
-    } else if (is("prefill_restore_len_kernel")) {
+    } else if (is("decode_meta_")) {
+        const bool by_value = !is("decode_meta_kernel") && !is("ILb0");
+        const int at = is("decode_meta_chunks_kernel") ? 1 : 0;      // the by-value slots' argument
+        const int32_t *slots = by_value ? ((const Chunk *)args[at])->v : ARG(const int32_t *, 0);
+        const int b0 = is("decode_meta_kernel") ? 1 : at + 2, B = ARG(int, b0);
+        int32_t *len = ARG(int32_t *, b0 + 1), *pos = ARG(int32_t *, b0 + 2);
+        for (int b = 0; b < B; ++b) {
+            if (by_value) ARG(int32_t *, at + 1)[b] = slots[b];
+            pos[b] = len[slots[b]]++;
+        }
+    } else if (is("restore_len_kernel")) {
         const int32_t *slots = ARG(const int32_t *, 0), *was = ARG(const int32_t *, 1);
         int32_t *len = ARG(int32_t *, 3);
         for (int i = 0; i < ARG(int, 2); ++i) len[slots[i]] = was[i];
@@ -116,7 +126,7 @@ hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
-hipError_t hipGetSymbolAddress(void **p, const void *) { static char scratch[16]; *p = scratch; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) { static char scratch[64 << 20]; *p = scratch; return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t *) { return hipErrorNotSupported; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
@@ -156,14 +166,14 @@ struct Case {
     const char *name;
     pd_dtype dtype;
     int d, hq, hkv, hd, f, experts;
-    bool chunk;
+    enum { PROMPTS, CHUNK, STEP, STEP_NOALLOC } kind;
     std::vector<int32_t> before, rows;      // cache lengths and new rows of the sequences
     int min_mallocs;                        // allocations that the call has to make beyond its workspace
 };
 
 static void failures(const Case &k)
 {
-    const int n = (int)k.rows.size(), max_len = 4096;
+    const int n = (int)k.rows.size(), max_len = n > 100 ? 64 : 4096;
     std::vector<int32_t> cu(1, 0), slots;
     for (int s = 0; s < n; ++s) {
         cu.push_back(cu.back() + k.rows[(size_t)s]);
@@ -173,6 +183,9 @@ static void failures(const Case &k)
     pd_tokens tk;
     memset(&tk, 0, sizeof(tk));
     tk.hidden = x.data(); tk.n_seqs = n; tk.cu_seqlens = cu.data(); tk.slots = slots.data();
+    pd_batch bt;
+    memset(&bt, 0, sizeof(bt));
+    bt.hidden = x.data(); bt.batch = n; bt.slots = slots.data();
     long launches = 0, mallocs = 0;
     for (long step = -1; step < launches + mallocs; ++step) {
         // a layer of its own each time: what an earlier call has allocated is there
@@ -184,14 +197,21 @@ static void failures(const Case &k)
         CHECK(pd_layer_reserve(L, cu.back()) == PD_OK, "%s", pd_last_error());
         auto lens_are = [&](bool after) {
             for (int s = 0; s < n; ++s) {
-                const int want = after ? (k.chunk ? k.before[(size_t)s] : 0) + k.rows[(size_t)s] : k.before[(size_t)s];
+                const int want = after ? (k.kind == Case::PROMPTS ? 0 : k.before[(size_t)s]) + k.rows[(size_t)s] : k.before[(size_t)s];
                 int32_t h = -1;
                 pd_kv_cache_len(c, slots[(size_t)s], &h);
                 CHECK(d_len[slots[(size_t)s]] == want && h == want, "%s, step %ld of %ld launches + %ld allocations: sequence %d has %d on the device, %d on the host, not %d",
                       k.name, step, launches, mallocs, s, d_len[slots[(size_t)s]], h, want);
             }
         };
-        auto call = [&] { return k.chunk ? pd_prefill_chunk(L, &tk, c, out.data(), nullptr) : pd_prefill(L, &tk, c, out.data(), nullptr); };
+        auto call = [&] {
+            switch (k.kind) {
+            case Case::PROMPTS: return pd_prefill(L, &tk, c, out.data(), nullptr);
+            case Case::CHUNK: return pd_prefill_chunk(L, &tk, c, out.data(), nullptr);
+            case Case::STEP: return pd_decode_step(L, &bt, c, out.data(), nullptr);
+            default: return pd_decode_step_noalloc(L, &bt, c, out.data(), nullptr);
+            }
+        };
         g_launches = g_mallocs = 0;
         g_fail_launch = step < launches ? step : -1;
         g_fail_malloc = step >= launches ? step - launches : -1;
@@ -226,14 +246,22 @@ int main()
         long_before.push_back(700 + 13 * i);
         short_rows.push_back(8 - i % 3);
     }
-    failures({"fp32 prompts", PD_F32, 64, 4, 2, 32, 128, 0, false, four, rows, 0});
-    failures({"fp32 chunk", PD_F32, 64, 4, 2, 32, 128, 0, true, four, rows, 0});
-    failures({"bf16 prompts", PD_BF16, 256, 4, 2, 128, 512, 0, false, four, rows, 1});
-    failures({"bf16 chunk", PD_BF16, 256, 4, 2, 128, 512, 0, true, four, rows, 1});
-    failures({"bf16 short chunk", PD_BF16, 256, 4, 2, 128, 512, 0, true, four, {8, 1, 3, 2}, 0});
-    failures({"bf16 short chunk that outgrows the workspace", PD_BF16, 256, 8, 8, 128, 512, 0, true, long_before, short_rows, 1});
-    failures({"bf16 plain cache", PD_BF16, 128, 4, 2, 64, 256, 0, true, four, rows, 0});
-    failures({"experts", PD_BF16, 256, 4, 2, 128, 512, 4, true, four, rows, 1});
-    failures({"more sequences than a launch's arguments hold", PD_BF16, 256, 4, 2, 128, 512, 0, true, many_before, many_rows, 0});
+    failures({"fp32 prompts", PD_F32, 64, 4, 2, 32, 128, 0, Case::PROMPTS, four, rows, 0});
+    failures({"fp32 chunk", PD_F32, 64, 4, 2, 32, 128, 0, Case::CHUNK, four, rows, 0});
+    failures({"bf16 prompts", PD_BF16, 256, 4, 2, 128, 512, 0, Case::PROMPTS, four, rows, 1});
+    failures({"bf16 chunk", PD_BF16, 256, 4, 2, 128, 512, 0, Case::CHUNK, four, rows, 1});
+    failures({"bf16 short chunk", PD_BF16, 256, 4, 2, 128, 512, 0, Case::CHUNK, four, {8, 1, 3, 2}, 0});
+    failures({"bf16 short chunk that outgrows the workspace", PD_BF16, 256, 8, 8, 128, 512, 0, Case::CHUNK, long_before, short_rows, 1});
+    failures({"bf16 plain cache", PD_BF16, 128, 4, 2, 64, 256, 0, Case::CHUNK, four, rows, 0});
+    failures({"experts", PD_BF16, 256, 4, 2, 128, 512, 4, Case::CHUNK, four, rows, 1});
+    failures({"more sequences than a launch's arguments hold", PD_BF16, 256, 4, 2, 128, 512, 0, Case::CHUNK, many_before, many_rows, 0});
+    const std::vector<int32_t> ones(4, 1), many(300, 1), most(1000, 1);
+    failures({"fp32 step", PD_F32, 64, 4, 2, 32, 128, 0, Case::STEP, four, ones, 0});
+    failures({"fp32 step of many", PD_F32, 64, 4, 2, 32, 128, 0, Case::STEP, many, many, 0});
+    failures({"bf16 step", PD_BF16, 256, 4, 2, 128, 512, 0, Case::STEP, four, ones, 0});
+    failures({"bf16 step of many", PD_BF16, 256, 4, 2, 128, 512, 0, Case::STEP, many, many, 0});
+    failures({"bf16 step of more than a launch's arguments hold", PD_BF16, 256, 4, 2, 128, 512, 0, Case::STEP, most, most, 0});
+    failures({"bf16 step without allocations", PD_BF16, 256, 4, 2, 128, 512, 0, Case::STEP_NOALLOC, four, ones, 0});
+    failures({"experts, step", PD_BF16, 256, 4, 2, 128, 512, 4, Case::STEP, four, ones, 0});
     return 0;
 }

@@ -19,6 +19,6 @@ def driver(tmp_path_factory):
     return exe
 
 
-def test_a_failed_prefill_leaves_the_cache_lengths_alone(driver):
+def test_a_failed_call_leaves_the_cache_lengths_alone(driver):
     r = subprocess.run([driver], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
