@@ -59,5 +59,6 @@ def test_norm_in_products(rows, d, d_ff):
         x[rows // 2] = 0.0
     cu = np.array([0, rows], np.int32)
     got, ref = gl.prefill(x, cu), O.prefill(ol, x, cu)
+    assert np.isfinite(got).all()
     assert max(relmax(got[i], ref[i]) for i in range(rows) if np.abs(ref[i]).max() > 0) <= 2 * TOL["f32"]
     gl.close()

@@ -37,6 +37,7 @@ def test_bf16(T, V, d, form):
     logits = torch.empty((T, V), dtype=torch.bfloat16, device="cuda")
     pd.pd_lm_head(h, to_dev(x, "bf16"), logits)
     torch.cuda.synchronize()
+    assert bool(torch.isfinite(logits).all())
     rows = np.unique(np.r_[0, T - 1, T // 2, np.arange(15, T, 64)[:8], np.arange(16, T, 256)[:4]])
     ref = O.lm_head(x[rows], hw["g_final"], hw["w_lm"])
     got = to_np(logits)[rows]
@@ -58,6 +59,7 @@ def test_codes(M, N, K, form):
     pd.pd_gemm_e4m3(torch.from_numpy(a).cuda(), torch.from_numpy(sa).cuda(), torch.from_numpy(b).cuda(),
                     torch.from_numpy(sb).cuda(), out)
     got = out.float().cpu().numpy()
+    assert np.isfinite(got).all()
     rows = np.unique(np.r_[0, M - 1, M // 2, np.arange(15, M, 256)])
     ref = O.gemm_e4m3(a[rows], sa[rows], b, sb)
     assert max(relmax(got[r], ref[j]) for j, r in enumerate(rows)) <= 2.0 ** -8
