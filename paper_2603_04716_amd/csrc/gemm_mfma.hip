@@ -732,8 +732,7 @@ static int grouped_splits(const GemmArgs &a, int BN)
     return splits < 1 ? 1 : splits;
 }
 
-// Tile and K split of a product of more than 256 rows (or 160 rows per group), and of a dense one of fewer, for both
-// operand widths (a k-tile is 64 x 2 bytes wide in either, and takes the same time).  256 x 256 tiles are the fastest per flop, but a launch runs in
+// Tile and K split of a dense product, and of a grouped one of more than 160 rows per group, for both operand widths (a k-tile is 64 x 2 bytes wide in either, and takes the same time).  256 x 256 tiles are the fastest per flop, but a launch runs in
 // rounds of one workgroup per CU: a few hundred to a few thousand rows fill the last round badly, and so do 257 rows
 // that take two row tiles.  Each form's time is therefore estimated as
 //   start + k-tiles per split x (full rounds x time of a k-tile + the last round's, from few workgroups to a full one)
@@ -794,7 +793,7 @@ static TilePlan plan_tiles(const GemmArgs &a)
                     {TILE_128_64, 128, 64, 256, 1.88, 0.312, 0.472},
                     {TILE_64_128, 64, 128, 256, 4.44, 0.402, 0.306},
                     {TILE_64, 64, 64, 256, 0.83, 0.232, 0.273}};
-    // codes come in larger calls, but for pd_gemm_e4m3
+    // codes come in calls of more than 256 rows, but for pd_gemm_e4m3, which takes the larger calls' forms for fewer rows too
     const bool few = a.M <= 256 && !a.a_scale, many = nk >= 32 && !a.fuse_y;
     const double add = few ? 4.04 : many ? 5.06 : 1.8, partials = few ? 3.2e6 : many ? 4.96e6 : 6e6;     // us, bytes per us
     const Form *forms = few ? few_rows : many ? many_k : few_k;
@@ -819,11 +818,11 @@ static TilePlan plan_tiles(const GemmArgs &a)
     return best;
 }
 
-// The plan of a product of more than 256 rows, for tests that state which form their sizes take (host only; not part of
-// the C ABI): n_groups 0 for a dense product, scratch_elems floats for partials, fused_norm where a split's sum would
-// carry the norm behind it; codes count K in pairs.  form: in the order of TileForm.
+// The plan of a product, for tests that state which form their sizes take (host only; not part of the C ABI): n_groups 0 for
+// a dense product, scratch_elems floats for partials, fused_norm where a split's sum would carry the norm behind it, codes
+// where both operands are E4M3 (K then counts pairs).  form: in the order of TileForm.
 extern "C" void pd_internal_tile_plan(int M, int N, int K, int epilogue, int n_groups, long long scratch_elems, int fused_norm,
-                                      int *form, int *splits)
+                                      int codes, int *form, int *splits)
 {
     static const int32_t some_offsets = 0;
     static float some_scratch;
@@ -840,6 +839,7 @@ extern "C" void pd_internal_tile_plan(int M, int N, int K, int epilogue, int n_g
         a.splitk_ws_elems = (size_t)scratch_elems;
     }
     if (fused_norm) a.fuse_y = &some_row;
+    if (codes) a.a_scale = &some_scratch;
     const TilePlan p = plan_tiles(a);
     *form = p.form;
     *splits = p.splits;
@@ -863,7 +863,7 @@ static hipError_t launch_planned(const GemmArgs &a, hipStream_t s)
     case TILE_256_128: return launch_cfg<256, 128, 2, 2, 3, F8>(a, s, p.splits);
     default: break;
     }
-    if constexpr (!F8) {                                      // calls of up to 256 rows multiply no codes
+    if constexpr (!F8) {                                      // the forms of few rows, which plan_tiles gives to bf16 only
         switch (p.form) {
         case TILE_128_64: return launch_cfg<128, 64, 4, 1, 4>(a, s, p.splits);
         case TILE_64_128: return launch_cfg<64, 128, 2, 2, 4>(a, s, p.splits);

@@ -81,18 +81,18 @@ class GpuLayer:
         self.caches = []
 
 
-def tile_plan(M, N, K, epilogue=0, n_groups=0, scratch=0, fused_norm=0):
-    """"form" or "form/split" of a product of more than 256 rows: what the library's planner says (host only).  Forms:
-    256, 192 (x 256 columns), pair (128 x 128, two workgroups per CU), deep (128 x 128, eight waves).  Codes: half of K."""
+def tile_plan(M, N, K, epilogue=0, n_groups=0, scratch=0, fused_norm=0, codes=False):
+    """"form" or "form/split" of a product: what the library's planner says (host only).  Forms: 256, 192 (x 256 columns),
+    pair (128 x 128, two workgroups per CU), deep (128 x 128, alone on its CU), and rows x columns.  Codes: half of K."""
     form, splits = C.c_int(), C.c_int()
-    pd.lib.pd_internal_tile_plan(M, N, K, epilogue, n_groups, C.c_longlong(scratch), fused_norm, C.byref(form), C.byref(splits))
-    return ("256", "192", "pair", "deep")[form.value] + ("/split" if splits.value > 1 else "")
+    pd.lib.pd_internal_tile_plan(M, N, K, epilogue, n_groups, C.c_longlong(scratch), fused_norm, int(codes), C.byref(form), C.byref(splits))
+    return ("256", "192", "pair", "deep", "256x128", "128x64", "64x128", "64")[form.value] + ("/split" if splits.value > 1 else "")
 
 
 def layer_plans(cfg, T, a8=False):
-    """The plans of the four products of a dense layer called with T > 256 rows, on the layer's own scratch (256 rows of
+    """The plans of the four products of a dense layer called with T rows, on the layer's own scratch (256 rows of
     640 x 128 columns and twice the widest weight matrix)."""
     d, f, nq, nkv = cfg["d_model"], cfg["d_ff"], cfg["n_q_heads"] * cfg["head_dim"], cfg["n_kv_heads"] * cfg["head_dim"]
     scratch, w = 256 * (640 * 128 + 2 * max(nq + 2 * nkv, 2 * f, d)), 2 if a8 else 1
-    return [tile_plan(T, nq + 2 * nkv, d // w, 0, 0, scratch), tile_plan(T, d, nq // w, 1, 0, scratch, 0 if a8 else 1),
-            tile_plan(T, f, d // w, 2, 0, scratch), tile_plan(T, d, f // w, 1, 0, scratch)]
+    return [tile_plan(T, nq + 2 * nkv, d // w, 0, 0, scratch, codes=a8), tile_plan(T, d, nq // w, 1, 0, scratch, 0 if a8 else 1, a8),
+            tile_plan(T, f, d // w, 2, 0, scratch, codes=a8), tile_plan(T, d, f // w, 1, 0, scratch, codes=a8)]

@@ -1,7 +1,5 @@
 """Products of up to 256 rows by their tile forms, the 256 x 128 form of longer K, and launches whose workgroups take
 several tiles of C one after another (the requests of the next one start behind the last k-tiles of the one before)."""
-import ctypes as C
-
 import numpy as np
 import pytest
 import torch
@@ -9,16 +7,9 @@ import torch
 import paper_2603_04716_amd as pd
 import pd_inputs as I
 from oracle import layer as O
-from gpu_util import GpuLayer, TOL, relmax, to_dev, to_np
+from gpu_util import GpuLayer, TOL, relmax, tile_plan, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
-FORMS = ("256", "192", "pair", "deep", "256x128", "128x64", "64x128", "64")
-
-
-def plan(M, N, K, epilogue=0, scratch=0, fused_norm=0):
-    form, splits = C.c_int(), C.c_int()
-    pd.lib.pd_internal_tile_plan(M, N, K, epilogue, 0, C.c_longlong(scratch), fused_norm, C.byref(form), C.byref(splits))
-    return FORMS[form.value] + ("/split" if splits.value > 1 else "")
 
 
 # rows at the edges of the row tiles, columns ending inside a column tile, K of one k-tile and more; 16400 columns and more
@@ -29,7 +20,7 @@ def plan(M, N, K, epilogue=0, scratch=0, fused_norm=0):
                                         (771, 6160, 2048, "256x128"), (1025, 6160, 2112, "256x128"), (300, 12304, 2048, "256x128"),
                                         (2100, 12304, 2048, "256"), (1500, 12304, 2048, "192"), (2000, 33040, 320, "256")])
 def test_bf16(T, V, d, form):
-    assert plan(T, V, d) == form
+    assert tile_plan(T, V, d) == form
     hw = I.head_weights(d, V, seed=d + V, dtype="bf16", std=0.05)
     dev = {k: to_dev(v, "bf16") for k, v in hw.items()}
     h = pd.pd_head_create(d, V, 1e-6, "bf16", dev["g_final"], dev["w_lm"], None, T)
@@ -50,7 +41,7 @@ def test_bf16(T, V, d, form):
 def test_codes(M, N, K, form):
     """Bound: one rounding to bf16, 2^-9 of an element, and the order of the fp32 sums; 2^-8 of the row's largest output.
     K = 1152 is an odd number of k-tiles, which ends in the other set of weight fragments."""
-    assert plan(M, N, K // 2, scratch=8 * 256 * N + M * N) == form
+    assert tile_plan(M, N, K // 2, scratch=8 * 256 * N + M * N, codes=True) == form
     rng = np.random.default_rng(M + N)
     a, b = (rng.integers(0, 256, s, dtype=np.uint8) & 0xB7 for s in ((M, K), (N, K)))
     sa = (2.0 ** rng.integers(-6, 2, M)).astype(np.float32)
@@ -75,7 +66,8 @@ def test_layer_of_few_rows(d, d_ff, T, forms):
     in one is 2 % of its weight, and the tiled kernels of any form are 2.03e-2 off at 130 rows.)"""
     cfg = I.small_config(dtype="bf16", d_model=d, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=d_ff)
     scratch = 256 * (640 * 128 + 2 * max(1024, 2 * d_ff, d))
-    assert [plan(T, 1024, d, 0, scratch), plan(T, d, 512, 1, scratch, 1), plan(T, d_ff, d, 2, scratch), plan(T, d, d_ff, 1, scratch)] == forms
+    assert [tile_plan(T, 1024, d, 0, 0, scratch), tile_plan(T, d, 512, 1, 0, scratch, 1), tile_plan(T, d_ff, d, 2, 0, scratch),
+            tile_plan(T, d, d_ff, 1, 0, scratch)] == forms
     w = I.layer_weights(cfg, std=0.02)
     ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
     x = I.hidden(T, d, seed=T, dtype="bf16")
