@@ -52,11 +52,14 @@ constexpr int BK = 64;  // k per tile: 8 chunks of 16 bytes per row
 
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
 
-// z / (1 + exp(-z)): the quotient by the hardware reciprocal and one correction from its remainder, which is the
-// division's result without its scaling steps (the divisor lies in 1 .. 2^127; the exponent stops where it would overflow)
-__device__ __forceinline__ float silu_fast(float z)
+__device__ __forceinline__ float silu_fast(float z) { return z / (1.0f + __expf(-z)); }
+
+// The same for |z| < kSiluNear, bit for bit (all such z compared; -0 gives +0): the quotient by the hardware reciprocal and one correction
+// from its remainder, without the division's steps for operands and results near the ends of the exponent's range.
+constexpr float kSiluNear = 87.f;
+__device__ __forceinline__ float silu_near(float z)
 {
-    const float d = 1.0f + __expf(fminf(-z, 87.0f)), r = __builtin_amdgcn_rcpf(d), q = z * r;
+    const float d = 1.0f + __expf(-z), r = __builtin_amdgcn_rcpf(d), q = z * r;
     return fmaf(fmaf(-d, q, z), r, q);
 }
 
@@ -465,10 +468,21 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if constexpr (EPI == EPI_SWIGLU) v[4 * b + r] = silu_fast(acc[i][2 * o + b][r]) * acc[i][2 * o + 2 + b][r];
-                    else v[4 * b + r] = acc[i][o + b][r];
+                for (int r = 0; r < 4; ++r) v[4 * b + r] = acc[i][EPI == EPI_SWIGLU ? 2 * o + b : o + b][r];
+            if constexpr (EPI == EPI_SWIGLU) {
+                float far = 0.f;
+#pragma unroll
+                for (int r = 0; r < 8; ++r) far = fmaxf(far, fabsf(v[r]));
+                if (__builtin_expect(__ballot(!(far < kSiluNear)) == 0, 1)) {
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) v[r] = silu_near(v[r]);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) v[r] = silu_fast(v[r]);
                 }
+#pragma unroll
+                for (int r = 0; r < 8; ++r) v[r] *= acc[i][2 * o + 2 + r / 4][r % 4];
+            }
             // lane group kg: block o + kg % 2, columns 8 * (kg / 2) .. +7
             const int n = (EPI == EPI_SWIGLU ? (t.col0 + wn * WN) / 2 : t.col0 + wn * WN) + (o + (eg & 1)) * 16 + 8 * (eg >> 1);
             const bool in = m < t.row_end && n < a.N;
