@@ -23,15 +23,12 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float silu_precise(float z) { return z / (1.0f + expf(-z)); }
 
-// MB x MB blocks of 16 x 16 per workgroup, W waves along K
-template <int MB, int W, int EPI, bool NORM = false>
+// MB x MB blocks of 16 x 16 per workgroup, W waves along K, U 16-wide k-steps requested at a time
+template <int MB, int W, int U, int EPI, bool NORM = false>
 __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GemmArgs a)
 {
     static_assert(!NORM || MB == 1, "one row per lane");
     constexpr int BT = 16 * MB, NM = EPI == EPI_SWIGLU ? 2 : 1;   // NM: weight matrices (gate and up)
-    // 16-wide k-steps requested at a time; with eight waves (K >= 512) eight, one round trip up to K = 1024 (4 x 256 <- 1024
-    // with four: 6.8 us, 6.3 now)
-    constexpr int U = MB == 1 && W == 8 ? 8 : 4;
     __shared__ f32x4 red[W][NM * MB * MB][64];
     __shared__ float sq[NORM ? W : 1][16];
 
@@ -188,21 +185,21 @@ bool gemm_f32_norm_supported(const GemmArgs &a)
            ((uintptr_t)a.norm_g & 15) == 0;
 }
 
-template <int MB, int W>
+template <int MB, int W, int U = 4>
 static hipError_t launch_f32(const GemmArgs &a, hipStream_t s)
 {
     const dim3 grid((unsigned)((a.N + 16 * MB - 1) / (16 * MB)),
                     (unsigned)((a.M + 16 * MB - 1) / (16 * MB) + (a.group_offsets ? a.n_groups : 0)));
     if constexpr (MB == 1)
         if (a.norm_g) {
-            if (a.epilogue == EPI_SWIGLU) gemm_f32_mfma_kernel<1, W, EPI_SWIGLU, true><<<grid, 64 * W, 0, s>>>(a);
-            else gemm_f32_mfma_kernel<1, W, EPI_NONE, true><<<grid, 64 * W, 0, s>>>(a);
+            if (a.epilogue == EPI_SWIGLU) gemm_f32_mfma_kernel<1, W, U, EPI_SWIGLU, true><<<grid, 64 * W, 0, s>>>(a);
+            else gemm_f32_mfma_kernel<1, W, U, EPI_NONE, true><<<grid, 64 * W, 0, s>>>(a);
             return hipGetLastError();
         }
     switch (a.epilogue) {
-    case EPI_NONE: gemm_f32_mfma_kernel<MB, W, EPI_NONE><<<grid, 64 * W, 0, s>>>(a); break;
-    case EPI_RESIDUAL: gemm_f32_mfma_kernel<MB, W, EPI_RESIDUAL><<<grid, 64 * W, 0, s>>>(a); break;
-    default: gemm_f32_mfma_kernel<MB, W, EPI_SWIGLU><<<grid, 64 * W, 0, s>>>(a); break;
+    case EPI_NONE: gemm_f32_mfma_kernel<MB, W, U, EPI_NONE><<<grid, 64 * W, 0, s>>>(a); break;
+    case EPI_RESIDUAL: gemm_f32_mfma_kernel<MB, W, U, EPI_RESIDUAL><<<grid, 64 * W, 0, s>>>(a); break;
+    default: gemm_f32_mfma_kernel<MB, W, U, EPI_SWIGLU><<<grid, 64 * W, 0, s>>>(a); break;
     }
     return hipGetLastError();
 }
@@ -212,7 +209,13 @@ hipError_t launch_gemm_f32_mfma(const GemmArgs &a, hipStream_t s)
     // two workgroups per CU: below that the small tile's four times as many workgroups are worth its extra reads
     if (!small_tiles(a)) return launch_f32<2, 4>(a, s);
     // small tiles: eight waves once each of them has a full round of k-steps to itself
-    return a.K >= 512 ? launch_f32<1, 8>(a, s) : launch_f32<1, 4>(a, s);
+    if (a.K < 512) return launch_f32<1, 4>(a, s);
+    // Eight k-steps at a time halve a wave's round trips, but requests past its last k-step are made and multiplied all the
+    // same: only where four at a time would make as many.  us, four -> eight: gate/up of 1 row, K = 2048 18.9 -> 14.5, K = 1024
+    // 10.3 -> 9.7, 500 rows K = 896 52 -> 46; where they are more, 40 rows: K = 512 11.8 -> 17.8, 1040 22.0 -> 26.2 (100 rows),
+    // 1536 22.5 -> 28.2, 2304 35.1 -> 40.8.
+    const int per = ((a.K + 15) / 16 + 7) / 8;
+    return (per + 7) / 8 * 2 == (per + 3) / 4 ? launch_f32<1, 8, 8>(a, s) : launch_f32<1, 8>(a, s);
 }
 
 }  // namespace pd

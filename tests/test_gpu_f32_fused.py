@@ -49,9 +49,11 @@ def test_steps_at_chunk_edges(head_dim, n_q, n_kv):
     gl.close()
 
 
-@pytest.mark.parametrize("rows,d,d_ff", [(1, 4, 4), (3, 20, 36), (17, 516, 260), (33, 1028, 68), (500, 256, 1024)])
+@pytest.mark.parametrize("rows,d,d_ff", [(1, 4, 4), (3, 20, 36), (17, 516, 260), (33, 1028, 68), (500, 256, 1024),
+                                         (5, 512, 640), (18, 576, 1040), (3, 1020, 1536), (40, 1040, 2060)])
 def test_norm_in_products(rows, d, d_ff):
-    """Rows of one k-step and less, and K on both sides of the eight-wave form; rows of very different sizes, one of zeros."""
+    """Rows of one k-step and less, K on both sides of the eight-wave form and of its rounds of four and of eight k-steps (512, 1536,
+    2060: four; 576, 640, 1020: eight; 1040: nine k-steps a wave, four); rows of very different sizes, one of zeros."""
     cfg, w = _layer(32, 2, 1, d=d, d_ff=d_ff)
     ol, gl = O.Layer(cfg, w), GpuLayer(cfg, w)
     x = I.hidden(rows, d, seed=rows) * np.logspace(-3, 3, rows, dtype=np.float32)[:, None]
