@@ -408,7 +408,7 @@ hipError_t launch_prefill_meta(int32_t *const dst[4], const int32_t *const host_
     d.start[4] = at;
     const unsigned meta = (unsigned)((T + 255) / 256);
     if (!n[2]) len = nullptr;
-    if (norm.x && norm.d % 8 == 0) {
+    if (norm.x && norm.d % 8 == 0 && (long long)meta + T <= 0xffffffffll / 256) {   // a launch has at most 2^32 - 1 threads
         prefill_meta_norm_kernel<<<meta + (unsigned)T, 256, 0, s>>>(d, c, n_seqs, T, tok_seq, tok_pos, tok_slot, len, len_was, add,
                                                                     (const uint4 *)norm.x, (const uint4 *)norm.g, (uint4 *)norm.y, norm.d / 8, 1.0f / (float)norm.d, norm.eps);
         done->norm = true;

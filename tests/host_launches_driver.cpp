@@ -6,6 +6,8 @@
 // failures  every launch and every allocation of a prefill call or a decode step fails in turn: the call has to return an error, the
 //           cache lengths on the device and on the host have to be what they were, and the same call has to
 //           succeed afterwards with the lengths that it would have left at once.
+//
+// limits    a prefill call of nearly as many rows as a launch of a workgroup of 256 per row can have: no launch may be refused.
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -238,8 +240,28 @@ static void failures(const Case &k)
     printf("ok %s: %ld launches, %ld allocations\n", k.name, launches, mallocs);
 }
 
-int main()
+static void limits()
 {
+    const int rows = 16720000, d = 64;      // 2^32 threads: 16777216 rows
+    pd_layer *L = make_layer(PD_BF16, d, 1, 1, 64, 64, 0);
+    void *x = calloc((size_t)rows * d, 2);
+    const int32_t cu[2] = {0, rows};
+    pd_tokens tk;
+    memset(&tk, 0, sizeof(tk));
+    tk.hidden = x; tk.n_seqs = 1; tk.cu_seqlens = cu;
+    CHECK(x && pd_prefill(L, &tk, nullptr, x, nullptr) == PD_OK, "%s", pd_last_error());
+    CHECK(!g_refused, "%d rows", rows);
+    pd_layer_destroy(L);
+    free(x);
+}
+
+int main(int argc, char **argv)
+{
+    if (argc != 2) return 2;
+    if (!strcmp(argv[1], "limits")) {
+        limits();
+        return 0;
+    }
     const std::vector<int32_t> four = {5, 0, 40, 7}, rows = {12, 1, 30, 9};
     std::vector<int32_t> long_before, short_rows, many_before(100, 3), many_rows(100, 2);
     for (int i = 0; i < 63; ++i) {

@@ -1,5 +1,5 @@
 """The library's host code (csrc/pd_api.hip and the launchers) run on the CPU, over a stand-in for the HIP runtime: what a
-call leaves behind when one of its launches or allocations fails."""
+call leaves behind when one of its launches or allocations fails, and which launches the largest calls make."""
 import os
 import subprocess
 
@@ -19,6 +19,14 @@ def driver(tmp_path_factory):
     return exe
 
 
-def test_a_failed_call_leaves_the_cache_lengths_alone(driver):
-    r = subprocess.run([driver], capture_output=True, text=True, timeout=300)
+def run(driver, case):
+    r = subprocess.run([driver, case], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+
+
+def test_a_failed_call_leaves_the_cache_lengths_alone(driver):
+    run(driver, "failures")
+
+
+def test_rows_near_the_size_limit_of_a_launch(driver):
+    run(driver, "limits")
