@@ -709,8 +709,9 @@ __device__ __forceinline__ float finite_from(float m) { return m == -INFINITY ? 
 //
 // ROPE (one row per sequence): q and the new key arrive unrotated.  The first waves rotate them into LDS (the arithmetic of
 // rope_kv_kernel) and one workgroup per kv head stores the new key and value into the cache; every workgroup takes the new
-// token from LDS, so none reads the position that another one writes.  4 rows, 4 heads of 64,
-// 100 keys: rotation 3.4 + attention 6.7 us -> 7.3.
+// token from LDS, so none reads the position that another one writes (of an empty slot, whose only position that is, the
+// new token's unrotated rows are read in its place and not used).  4 rows, 4 heads of 64, 100 keys: rotation 3.4 +
+// attention 6.7 us -> 7.3.
 template <int LPR, bool ROPE>
 __global__ __launch_bounds__(256) void attn_decode_f32_kernel(AttnArgs a, RopeArgs ra)
 {
@@ -726,6 +727,7 @@ __global__ __launch_bounds__(256) void attn_decode_f32_kernel(AttnArgs a, RopeAr
     const int pos = a.tok_pos[t], n_keys = pos + 1;
     const size_t base = (((size_t)a.tok_slot[t] * a.Hkv + g) * a.max_len) * hd;
     const float *Kb = (const float *)a.k_cache + base, *Vb = (const float *)a.v_cache + base;
+    if (ROPE && pos == 0) Kb = Vb = (const float *)a.qkv + (size_t)t * a.ld;
     const int last = ROPE ? max(pos - 1, 0) : n_keys - 1;         // last position that is read from the cache
     const int vrow = lane / LPR, vch = lane % LPR;
     float4 kv[kAhead ? LPR : 1], va[kAhead ? LPR : 1];
