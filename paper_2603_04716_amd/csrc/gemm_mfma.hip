@@ -893,6 +893,30 @@ hipError_t launch_gemm_mfma_f8(const GemmArgs &a, hipStream_t s)
     return launch_planned<true>(a, s);
 }
 
+// Height of the row tiles of a grouped product of up to 160 rows per group, 128 columns wide (see launch_gemm_mfma)
+static int grouped_row_tile(const GemmArgs &a, int rows, int splits)
+{
+    const int n_cols = a.epilogue == EPI_SWIGLU ? 2 * a.N : a.N;
+    const double mean = (double)a.M / a.n_groups, most = mean + 2.0 * sqrt(mean * (1.0 - 1.0 / a.n_groups));
+    auto one_round = [&](int bm) { return ceil(most / bm) * a.n_groups * ((n_cols + 127) / 128) * splits <= 256.0; };
+    if (rows <= 32 || one_round(64)) return 64;
+    return rows <= 107 || one_round(128) ? 128 : 256;
+}
+
+// The same for tests (host only; not part of the C ABI)
+extern "C" int pd_internal_grouped_row_tile(int M, int N, int K, int epilogue, int n_groups, long long scratch_elems)
+{
+    static float some_scratch;
+    GemmArgs a;
+    memset(&a, 0, sizeof(a));
+    a.M = M; a.N = N; a.K = K; a.ldc = N; a.ldr = N; a.epilogue = epilogue; a.n_groups = n_groups;
+    if (scratch_elems > 0) {
+        a.splitk_ws = &some_scratch;
+        a.splitk_ws_elems = (size_t)scratch_elems;
+    }
+    return grouped_row_tile(a, (M + n_groups - 1) / n_groups, grouped_splits(a, 128));
+}
+
 hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s)
 {
     if (!a.group_offsets) return launch_planned<false>(a, s);
@@ -903,12 +927,18 @@ hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s)
     // routings, 768 / 825 / 813 us with 64-row tiles, 672 / 673 / 675 with these), 256-row tiles where a tenth of the groups or so
     // would outgrow 128 (mean + 2 x its root: 105 rows 686 us, with the taller tile 721; 110 rows 823 / 838 and 725 / 729;
     // 128 rows 921 / 902 and 743 / 740), and the estimate of plan_tiles, which counts those second tiles, from 161 rows on (175 rows
-    // 836 -> 783 us, 225 rows 888 -> 863, 237 rows 903 -> 909, 250 rows 1168 -> 1003, 255 rows 1289 -> 1042).
+    // 836 -> 783 us, 225 rows 888 -> 863, 250 rows 1168 -> 1003, 255 rows 1289 -> 1042; between, at 237 rows, 903 -> 909).
+    // That is for launches of more workgroups than CUs.  Where even the second tiles find a CU of their own (narrow or few
+    // experts), they run beside the first, and the lower tile is the faster one; us, gate/up and down, lower -> taller:
+    // 8 experts of 512 x 256 64 rows 7.7 + 6.0 -> 8.4 + 6.4, 116 rows 7.5 + 6.1 -> 11.1 + 7.9 (64 and 256 rows tall); 16 of
+    // 1024 x 512 107 rows 14.3 + 10.4 -> 15.9 + 10.9, 128 rows 16.1 + 11.4 -> 18.9 + 12.3; where they do not, 4 of 1024 x
+    // 2816, gate/up 64 rows 18.4 -> 14.8, 32 of 2048 x 1408, down 64 rows 63 -> 43, 116 rows 59 -> 49.
     const int rows = (a.M + a.n_groups - 1) / a.n_groups;
     if (rows > 160) return launch_planned<false>(a, s);
-    if (rows > 107) return launch_cfg<256, 128, 2, 2, 3>(a, s, grouped_splits(a, 128));
-    if (rows > 32) return launch_cfg<128, 128, 2, 2, 3>(a, s, grouped_splits(a, 128));
-    return launch_cfg<64, 128, 2, 2, 4>(a, s, grouped_splits(a, 128));
+    const int splits = grouped_splits(a, 128), bm = grouped_row_tile(a, rows, splits);
+    if (bm == 256) return launch_cfg<256, 128, 2, 2, 3>(a, s, splits);
+    if (bm == 128) return launch_cfg<128, 128, 2, 2, 3>(a, s, splits);
+    return launch_cfg<64, 128, 2, 2, 4>(a, s, splits);
 }
 
 }  // namespace pd
