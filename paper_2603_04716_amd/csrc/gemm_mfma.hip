@@ -746,22 +746,30 @@ static int grouped_splits(const GemmArgs &a, int BN)
     return splits < 1 ? 1 : splits;
 }
 
-// Tile and K split of a dense product, and of a grouped one of more than 160 rows per group, for both operand widths (a k-tile is 64 x 2 bytes wide in either, and takes the same time).  256 x 256 tiles are the fastest per flop, but a launch runs in
+// Tile and K split of a dense product, and of a grouped one of more than 160 rows per group, for both operand widths (a k-tile
+// is 64 x 2 bytes wide in either, and takes the same time).  256 x 256 tiles are the fastest per flop, but a launch runs in
 // rounds of one workgroup per CU: a few hundred to a few thousand rows fill the last round badly, and so do 257 rows
-// that take two row tiles.  Each form's time is therefore estimated as
+// that take two row tiles.  Each form and split gets the score
 //   start + k-tiles per split x (full rounds x time of a k-tile + the last round's, from few workgroups to a full one)
-// and a split's as the launch that adds the partials and the partials written and read (a product whose sum would carry
-// the norm behind it saves that launch, 6.5 us).  The constants for 32 k-tiles and more are fitted to 5400 launches of the
-// kernels as they are now: 18 shapes of 1024 ... 28672 columns and K = 1024 ... 14336, 257 ... 6000 rows, bf16 and codes,
-// every form and split.  On them the choice takes 0.8 % longer than the best form and split (at worst 14 %); with the
-// constants for fewer k-tiles, which were fitted to these and to shorter products when all forms took longer per k-tile
-// (there 256 x 128 is never ahead), it took 2.5 % longer.  A product whose sum carries a norm keeps those too: the fit does
-// not know that sum's time, and they are within 3 % there.  us, before -> with this fit: bf16 QKV 771 rows 57 -> 48
-// (256 x 128), down 512 rows 84 -> 64 (256 x 128, four splits).
-// Up to 256 rows the weights are streamed once and the tiles are smaller: fitted to 4500 launches of 17 shapes, 18 ... 256
-// rows, up to 12 splits.  On them the choice takes 0.3 % longer than the best (at worst 12 %); one form for each of up to 64,
-// 128 and 256 rows, 128 or 64 columns wide, with as many splits as one round of workgroups holds, took 19 % longer.
-// us, before -> now: 256 rows QKV 31 -> 27, O 23.6 -> 21.3, gate/up 72 -> 64, down 50 -> 44; 64 rows O 16.0 -> 13.4.
+// and a split in addition the launch that adds the partials and the partials written and read (a product whose sum would
+// carry the norm behind it saves that launch).  The constants are fitted so that the best score falls on the fastest form, not
+// so that it is a time: there is no term for the weights' bytes, which all forms share, and a nearly empty last round may
+// count for more than a full one.  8B shape, gate/up: score 29 at 48 rows, 72 at 512, 969 at 8192; measured 47, 93, 1285 us.
+// So the scores rank the forms of products like the fitted ones and say nothing else.  Four sets:
+// - 32 k-tiles and more: 5400 launches of 18 shapes of 1024 ... 28672 columns and K = 1024 ... 14336, 257 ... 6000 rows, bf16 and
+//   codes, every form and split.  The choice takes 0.8 % longer than the best form and split (at worst 14 %).  us, before -> with
+//   this fit: bf16 QKV 771 rows 57 -> 48 (256 x 128), down 512 rows 84 -> 64 (256 x 128, four splits).
+// - fewer k-tiles: 1157 products of 256 ... 8192 columns, K = 256 ... 4096, 257 ... 4000 rows, bf16 and codes, and grouped ones.
+//   5.6 % longer than the best (7.5 % with the constants of the kernels of eight and sixteen waves that stood here before; the best
+//   is two workgroups of 128 x 128 per CU without a split far more often than the fit says, which holds the forms that the tests
+//   state).  us: bf16 300 rows, 1536 <- 1024 15.4 -> 12.4.
+// - a residual product whose sum carries a norm, any K: 234 products of 256 ... 8192 columns.  4.8 % longer (10 % before), 1.2 % from
+//   K = 3072 on (3.4 % before).  us, with the norm: 1024 <- 1024 2000 rows 21.6 -> 16.9, 512 <- 512 4000 rows 22.4 -> 14.4, 4096 <-
+//   4096 771 rows 45 -> 40.
+// - up to 256 rows of bf16, where the weights are streamed once and the tiles are smaller: 4500 launches of 17 shapes, 18 ... 256
+//   rows, up to 12 splits.  0.3 % longer than the best (at worst 12 %); one form for each of up to 64,
+//   128 and 256 rows, 128 or 64 columns wide, with as many splits as one round of workgroups holds, took 19 % longer.
+//   us, before -> now: 256 rows QKV 31 -> 27, O 23.6 -> 21.3, gate/up 72 -> 64, down 50 -> 44; 64 rows O 16.0 -> 13.4.
 // A grouped product's loads are known only on the average, so another form than 256 x 256 has to be 5 % ahead there
 // (without that, 9200 rows on 8 experts took 4330 instead of 4265 us).
 enum TileForm { TILE_256, TILE_192, TILE_128_PAIR, TILE_128_DEEP, TILE_256_128, TILE_128_64, TILE_64_128, TILE_64 };
@@ -793,10 +801,16 @@ static TilePlan plan_tiles(const GemmArgs &a)
         TileForm form;
         int bm, bn, per_round;
         double start, kt_full, kt_few;
-    } few_k[] = {{TILE_256, 256, 256, 256, 3.7, 1.626, 1.211},
-                 {TILE_192, 192, 256, 256, 2.6, 1.348, 1.107},
-                 {TILE_128_PAIR, 128, 128, 512, 0.85, 1.053, 0.62},          // two workgroups per CU
-                 {TILE_128_DEEP, 128, 128, 256, 0.0, 0.636, 0.486}},         // alone on its CU with a deeper ring
+    } few_k[] = {{TILE_256, 256, 256, 256, 4.791, 1.026, 1.301},
+                 {TILE_192, 192, 256, 256, 4.065, 0.947, 1.137},
+                 {TILE_128_PAIR, 128, 128, 512, 2.073, 0.811, 0.494},        // two workgroups per CU
+                 {TILE_128_DEEP, 128, 128, 256, 1.121, 0.554, 0.448},        // alone on its CU with a deeper ring
+                 {TILE_256_128, 256, 128, 256, 5.956, 0.981, 0.385}},
+      normed[] = {{TILE_256, 256, 256, 256, 11.517, 1.011, 1.162},
+                  {TILE_192, 192, 256, 256, 6.100, 0.993, 0.858},
+                  {TILE_128_PAIR, 128, 128, 512, 2.309, 0.826, 0.964},
+                  {TILE_128_DEEP, 128, 128, 256, 0.353, 0.615, 0.819},
+                  {TILE_256_128, 256, 128, 256, 6.434, 0.716, 0.914}},
       many_k[] = {{TILE_256, 256, 256, 256, 1.235, 1.080, 1.306},
                   {TILE_192, 192, 256, 256, 3.609, 0.891, 0.943},
                   {TILE_128_PAIR, 128, 128, 512, 0.392, 0.832, 0.904},
@@ -808,20 +822,25 @@ static TilePlan plan_tiles(const GemmArgs &a)
                     {TILE_64_128, 64, 128, 256, 4.44, 0.402, 0.306},
                     {TILE_64, 64, 64, 256, 0.83, 0.232, 0.273}};
     // codes come in calls of more than 256 rows, but for pd_gemm_e4m3, which takes the larger calls' forms for fewer rows too
-    const bool few = a.M <= 256 && !a.a_scale, many = nk >= 32 && !a.fuse_y;
-    const double add = few ? 4.04 : many ? 5.06 : 1.8, partials = few ? 3.2e6 : many ? 4.96e6 : 6e6;     // us, bytes per us
-    const Form *forms = few ? few_rows : many ? many_k : few_k;
-    const int n_forms = few || many ? 5 : 4, max_splits = few ? 12 : 8, min_k_tiles = few ? 4 : 2;
-    for (int i = 0; i < n_forms; ++i) {
-        const Form &f = forms[i];
+    const bool few = a.M <= 256 && !a.a_scale;
+    const struct Kind {
+        const Form *forms;                     // five each
+        double add, partials, norm;            // us of a split's sum, bytes per us of its partials, us of the norm that it saves
+        int max_splits, min_k_tiles;
+    } kind = few        ? Kind{few_rows, 4.04, 3.2e6, 6.5, 12, 4}
+             : a.fuse_y ? Kind{normed, 1.570, 3.543e6, 0.672, 8, 2}
+             : nk >= 32 ? Kind{many_k, 5.06, 4.96e6, 0.0, 8, 2}
+                        : Kind{few_k, 1.358, 2.909e6, 0.0, 8, 2};
+    for (int i = 0; i < 5; ++i) {
+        const Form &f = kind.forms[i];
         const long long tiles = (long long)ceil(row_tiles(a, f.bm) * ((n_cols + f.bn - 1) / f.bn));
-        for (int sp = 1; sp <= max_splits; ++sp) {
-            if (sp > 1 && (!can_split || nk / sp < min_k_tiles || (size_t)sp * a.M * n_cols > a.splitk_ws_elems)) break;
+        for (int sp = 1; sp <= kind.max_splits; ++sp) {
+            if (sp > 1 && (!can_split || nk / sp < kind.min_k_tiles || (size_t)sp * a.M * n_cols > a.splitk_ws_elems)) break;
             const long long wg = tiles * sp, full = wg / f.per_round, rem = wg % f.per_round;
             const double last = rem ? f.kt_few + (f.kt_full - f.kt_few) * (double)rem / f.per_round : 0.0;
             double us = f.start + ((nk + sp - 1) / sp) * ((double)full * f.kt_full + last);
-            if (sp > 1) us += add + (double)sp * a.M * n_cols * 8.0 / partials;
-            else if (a.fuse_y) us += 6.5;
+            if (sp > 1) us += kind.add + (double)sp * a.M * n_cols * 8.0 / kind.partials;
+            else if (a.fuse_y) us += kind.norm;
             if (a.group_offsets && f.form != TILE_256) us *= 1.05;
             if (us < best_us) {
                 best_us = us;
