@@ -12,7 +12,7 @@ import torch
 import paper_2603_04716_amd as pd
 import pd_inputs as I
 from oracle import layer as O
-from gpu_util import GpuLayer, TOL, relmax, to_dev
+from gpu_util import GpuLayer, TOL, layer_plans, relmax, tile_plan, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -253,6 +253,48 @@ def test_moe_with_8bit_activations_and_empty_experts():
     got = gl.prefill(x, cu, router_logits=rl)
     assert np.array_equal(gl.experts(T), eref)
     assert relmax(got, ref) <= TOL_A8
+    gl.close()
+
+
+@pytest.mark.parametrize("d_ff,T,form", [(4096, 1100, "192"), (4096, 1500, "256"), (3072, 1100, "pair")])
+@pytest.mark.parametrize("skew", ["even", "two", "ragged"])
+def test_moe_workgroups_that_cross_experts(d_ff, T, form, skew):
+    """Gate/up launches of more tiles than workgroups, K of four k-tiles (even, and past the ring): a workgroup goes on to a tile of
+    another expert, whose gathered rows it requests behind the last k-tiles of the one before."""
+    cfg = small(4, 2, 512, d_ff, n_experts=8, top_k=2)
+    assert tile_plan(2 * T, d_ff, 256, 2, 8, codes=True) == form
+    w = I.layer_weights(cfg, std=0.03)
+    ol, gl = O.Layer(cfg, O.quantise_layer_weights(w)), GpuLayer(cfg, w, a8=True)
+    rl = I.router_logits(T, 8, seed=T)
+    if skew == "two":
+        rl[:, 1] += 9.0
+        rl[:, 6] += 8.0
+    if skew == "ragged":
+        rl += np.linspace(0.0, 3.0, 8, dtype=rl.dtype)
+    cu = np.array([0, T // 3, T], np.int32)
+    x = I.hidden(T, cfg["d_model"], seed=3, dtype="bf16")
+    ref, eref = O.prefill(ol, x, cu, router_logits=rl, return_experts=True, act8=True)
+    got = gl.prefill(x, cu, router_logits=rl)
+    assert np.array_equal(gl.experts(T), eref)
+    assert relmax(got, ref) <= TOL_A8
+    gl.close()
+
+
+@pytest.mark.parametrize("d,d_ff,T,which,form", [(4096, 6144, 257, 2, "256x128"), (3072, 12288, 400, 3, "256x128/split"), (3072, 4096, 1300, 3, "256x128")])
+def test_256_x_128_tiles_with_every_epilogue(d, d_ff, T, which, form):
+    """Gate/up (SwiGLU) and down (residual, with K split and without) on 256 x 128 tiles of codes; sampled rows.  Weights of the
+    benchmark's spread: with larger ones and these widths the attention scores amplify the roundings."""
+    cfg = small(4, 2, d, d_ff)
+    assert layer_plans(cfg, T, a8=True)[which] == form
+    w = I.layer_weights(cfg, std=0.02)
+    ol, gl = O.Layer(cfg, O.quantise_layer_weights(w)), GpuLayer(cfg, w, a8=True)
+    x = I.hidden(T, d, seed=T, dtype="bf16")
+    cu = np.array([0, T // 3, T], np.int32)
+    got = gl.prefill(x, cu)
+    assert np.isfinite(got).all()
+    rows = np.unique(np.r_[0, 15, 16, 127, 128, 255, 256, T // 2, T - 1]).astype(np.int32)
+    ref = O.prefill(ol, x, cu, rows=rows, act8=True)
+    assert relmax(got[rows], ref) <= TOL_A8
     gl.close()
 
 
