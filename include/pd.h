@@ -291,7 +291,9 @@ pd_status pd_last_expert_choice(const pd_layer *layer, int32_t rows, void *exper
  * While enabled, pd_prefill / pd_decode_step bracket every step they enqueue with events on the
  * caller's stream.  pd_profile_read waits for the last call's events and returns up to
  * max_entries (name, milliseconds) pairs in launch order; names are static strings owned by the
- * library ("qkv_proj", "gate_up_swiglu", "decode_attention", ...).
+ * library ("qkv_proj", "gate_up_swiglu", "decode_attention", ...).  Steps that share a launch share an
+ * entry: "rmsnorm_attn" holds the call's bookkeeping (sequence arrays, cache lengths) where that rides
+ * along, and a norm, rotation or cache append that another step's kernel does has none of its own.
  */
 pd_status pd_profile_enable(pd_layer *layer, int32_t on);
 pd_status pd_profile_read(pd_layer *layer, int32_t max_entries, const char **names, float *ms,

@@ -401,119 +401,119 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs &a, int tiles_m, i
     };
     for (;;) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    pin_acc();
-    if constexpr (kAgpr) asm volatile("s_nop 7");
-    if constexpr (F8) {
-        for (int kt = kt0; kt < kt1; kt += 2) {       // two register sets of B's fragments
-            k_tile(kt, c0);
-            if (kt + 1 < kt1) k_tile(kt + 1, c1);
+            for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        pin_acc();
+        if constexpr (kAgpr) asm volatile("s_nop 7");
+        if constexpr (F8) {
+            for (int kt = kt0; kt < kt1; kt += 2) {       // two register sets of B's fragments
+                k_tile(kt, c0);
+                if (kt + 1 < kt1) k_tile(kt + 1, c1);
+            }
+        } else {
+            for (int kt = kt0; kt < kt1; ++kt) k_tile(kt, c0);
         }
-    } else {
-        for (int kt = kt0; kt < kt1; ++kt) k_tile(kt, c0);
-    }
-    if (!more) PD_VMCNT(0);                           // the repeated requests: none may outlive the workgroup's LDS
-    if constexpr (kAgpr) asm volatile("s_nop 15\n\ts_nop 15");
-    pin_acc();
+        if (!more) PD_VMCNT(0);                           // the repeated requests: none may outlive the workgroup's LDS
+        if constexpr (kAgpr) asm volatile("s_nop 15\n\ts_nop 15");
+        pin_acc();
 #undef PD_VMCNT
 #undef PD_VMCNT_LGKM0
 
-    // ---- epilogue: lane holds row (lane % 16) of each block, columns 4*(lane/16) .. +3 -------------------------
-    const int el = opaque_lane(), er = el & 15, eg = el >> 4;
-    if constexpr (F8) {
-        f32x4 sbv[NB];
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            // columns past the last block (a multiple of 16 of them exist) are not stored
-            const int n = min(t.col0 + wn * WN + j * 16, n_cols - 16) + 4 * eg;
-            sbv[j] = *(const f32x4 *)(a.b_scale + (size_t)t.group * n_cols + n);
-        }
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-            int mr = min(t.row0 + wm * WM + i * 16 + er, t.row_end - 1);
-            if (a.a_gather) mr = a.a_gather[mr];        // the scale belongs to the row the codes came from
-            const float sav = a.a_scale[mr];
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[i][j][r] *= sav * sbv[j][r];
-        }
-    }
-    if constexpr (EPI == EPI_PARTIAL) {
-        float *P = a.splitk_ws + (size_t)blockIdx.y * a.M * n_cols;
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-            const int m = t.row0 + wm * WM + i * 16 + er;
+        // ---- epilogue: lane holds row (lane % 16) of each block, columns 4*(lane/16) .. +3 -------------------------
+        const int el = opaque_lane(), er = el & 15, eg = el >> 4;
+        if constexpr (F8) {
+            f32x4 sbv[NB];
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                const int n = t.col0 + wn * WN + j * 16 + 4 * eg;
-                if (m < t.row_end && n < n_cols) *(f32x4 *)(P + (size_t)m * n_cols + n) = acc[i][j];
+                // columns past the last block (a multiple of 16 of them exist) are not stored
+                const int n = min(t.col0 + wn * WN + j * 16, n_cols - 16) + 4 * eg;
+                sbv[j] = *(const f32x4 *)(a.b_scale + (size_t)t.group * n_cols + n);
+            }
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                int mr = min(t.row0 + wm * WM + i * 16 + er, t.row_end - 1);
+                if (a.a_gather) mr = a.a_gather[mr];        // the scale belongs to the row the codes came from
+                const float sav = a.a_scale[mr];
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[i][j][r] *= sav * sbv[j][r];
             }
         }
-    } else {
-    uint16_t *C = (uint16_t *)a.C;
-    const uint16_t *R = (const uint16_t *)a.R;
-    // Two neighbouring blocks of 16 columns: the lane groups 4*(lane/16) exchange a block's half in pairs, after which
-    // a lane holds 8 consecutive columns of one block and stores (and loads the residual) 16 bytes; the residual is
-    // added in fp32 ahead of the one rounding to bf16.
-    constexpr int OB = EPI == EPI_SWIGLU ? NB / 2 : NB;   // output blocks of the wave
+        if constexpr (EPI == EPI_PARTIAL) {
+            float *P = a.splitk_ws + (size_t)blockIdx.y * a.M * n_cols;
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
-        const int m = t.row0 + wm * WM + i * 16 + er;
+            for (int i = 0; i < MB; ++i) {
+                const int m = t.row0 + wm * WM + i * 16 + er;
 #pragma unroll
-        for (int o = 0; o < OB; o += 2) {
-            float v[8];                                   // the lane's four columns of block o, then of block o + 1
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[4 * b + r] = acc[i][EPI == EPI_SWIGLU ? 2 * o + b : o + b][r];
-            if constexpr (EPI == EPI_SWIGLU) {
-                float far = 0.f;
-#pragma unroll
-                for (int r = 0; r < 8; ++r) far = fmaxf(far, fabsf(v[r]));
-                if (__builtin_expect(__ballot(!(far < kSiluNear)) == 0, 1)) {
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) v[r] = silu_near(v[r]);
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) v[r] = silu_fast(v[r]);
+                for (int j = 0; j < NB; ++j) {
+                    const int n = t.col0 + wn * WN + j * 16 + 4 * eg;
+                    if (m < t.row_end && n < n_cols) *(f32x4 *)(P + (size_t)m * n_cols + n) = acc[i][j];
                 }
-#pragma unroll
-                for (int r = 0; r < 8; ++r) v[r] *= acc[i][2 * o + 2 + r / 4][r % 4];
             }
-            // lane group kg: block o + kg % 2, columns 8 * (kg / 2) .. +7
-            const int n = (EPI == EPI_SWIGLU ? (t.col0 + wn * WN) / 2 : t.col0 + wn * WN) + (o + (eg & 1)) * 16 + 8 * (eg >> 1);
-            const bool in = m < t.row_end && n < a.N;
-            uint4 out;
-            if constexpr (EPI == EPI_RESIDUAL) {
+        } else {
+            uint16_t *C = (uint16_t *)a.C;
+            const uint16_t *R = (const uint16_t *)a.R;
+            // Two neighbouring blocks of 16 columns: the lane groups 4*(lane/16) exchange a block's half in pairs, after which
+            // a lane holds 8 consecutive columns of one block and stores (and loads the residual) 16 bytes; the residual is
+            // added in fp32 ahead of the one rounding to bf16.
+            constexpr int OB = EPI == EPI_SWIGLU ? NB / 2 : NB;   // output blocks of the wave
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[r]), __float_as_uint(v[4 + r]), false, false);
-                    v[r] = __uint_as_float(p[0]);
-                    v[4 + r] = __uint_as_float(p[1]);
+            for (int i = 0; i < MB; ++i) {
+                const int m = t.row0 + wm * WM + i * 16 + er;
+#pragma unroll
+                for (int o = 0; o < OB; o += 2) {
+                    float v[8];                                   // the lane's four columns of block o, then of block o + 1
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[4 * b + r] = acc[i][EPI == EPI_SWIGLU ? 2 * o + b : o + b][r];
+                    if constexpr (EPI == EPI_SWIGLU) {
+                        float far = 0.f;
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) far = fmaxf(far, fabsf(v[r]));
+                        if (__builtin_expect(__ballot(!(far < kSiluNear)) == 0, 1)) {
+#pragma unroll
+                            for (int r = 0; r < 8; ++r) v[r] = silu_near(v[r]);
+                        } else {
+#pragma unroll
+                            for (int r = 0; r < 8; ++r) v[r] = silu_fast(v[r]);
+                        }
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) v[r] *= acc[i][2 * o + 2 + r / 4][r % 4];
+                    }
+                    // lane group kg: block o + kg % 2, columns 8 * (kg / 2) .. +7
+                    const int n = (EPI == EPI_SWIGLU ? (t.col0 + wn * WN) / 2 : t.col0 + wn * WN) + (o + (eg & 1)) * 16 + 8 * (eg >> 1);
+                    const bool in = m < t.row_end && n < a.N;
+                    uint4 out;
+                    if constexpr (EPI == EPI_RESIDUAL) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[r]), __float_as_uint(v[4 + r]), false, false);
+                            v[r] = __uint_as_float(p[0]);
+                            v[4 + r] = __uint_as_float(p[1]);
+                        }
+                        uint4 rr = make_uint4(0, 0, 0, 0);
+                        if (in) rr = *(const uint4 *)(R + (size_t)m * a.ldr + n);
+                        out.x = pack2bf(v[0] + bfbits2f(rr.x & 0xffffu), v[1] + bfbits2f(rr.x >> 16));
+                        out.y = pack2bf(v[2] + bfbits2f(rr.y & 0xffffu), v[3] + bfbits2f(rr.y >> 16));
+                        out.z = pack2bf(v[4] + bfbits2f(rr.z & 0xffffu), v[5] + bfbits2f(rr.z >> 16));
+                        out.w = pack2bf(v[6] + bfbits2f(rr.w & 0xffffu), v[7] + bfbits2f(rr.w >> 16));
+                    } else {
+                        auto p = __builtin_amdgcn_permlane16_swap(pack2bf(v[0], v[1]), pack2bf(v[4], v[5]), false, false);
+                        auto q = __builtin_amdgcn_permlane16_swap(pack2bf(v[2], v[3]), pack2bf(v[6], v[7]), false, false);
+                        out = make_uint4(p[0], q[0], p[1], q[1]);
+                    }
+                    if (in) *(uint4 *)(C + (size_t)m * a.ldc + n) = out;
                 }
-                uint4 rr = make_uint4(0, 0, 0, 0);
-                if (in) rr = *(const uint4 *)(R + (size_t)m * a.ldr + n);
-                out.x = pack2bf(v[0] + bfbits2f(rr.x & 0xffffu), v[1] + bfbits2f(rr.x >> 16));
-                out.y = pack2bf(v[2] + bfbits2f(rr.y & 0xffffu), v[3] + bfbits2f(rr.y >> 16));
-                out.z = pack2bf(v[4] + bfbits2f(rr.z & 0xffffu), v[5] + bfbits2f(rr.z >> 16));
-                out.w = pack2bf(v[6] + bfbits2f(rr.w & 0xffffu), v[7] + bfbits2f(rr.w >> 16));
-            } else {
-                auto p = __builtin_amdgcn_permlane16_swap(pack2bf(v[0], v[1]), pack2bf(v[4], v[5]), false, false);
-                auto q = __builtin_amdgcn_permlane16_swap(pack2bf(v[2], v[3]), pack2bf(v[6], v[7]), false, false);
-                out = make_uint4(p[0], q[0], p[1], q[1]);
             }
-            if (in) *(uint4 *)(C + (size_t)m * a.ldc + n) = out;
         }
-    }
-    }
-    if (!more) break;
-    t = next;
-    pid += gridDim.x;
-    more = pid < n_tiles;
-    if (more) next = tile_at(pid);
+        if (!more) break;
+        t = next;
+        pid += gridDim.x;
+        more = pid < n_tiles;
+        if (more) next = tile_at(pid);
     }
 }
 

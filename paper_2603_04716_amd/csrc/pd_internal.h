@@ -313,11 +313,11 @@ hipError_t launch_prefill_meta(int32_t *const dst[4], const int32_t *const host_
 hipError_t launch_scatter_ints(int32_t *dst, const int32_t *host_idx, const int32_t *host_val, int n,
                                hipStream_t s);
 // decode meta: for b in [0,B): pos[b] = len[slot[b]]; len[slot[b]] += 1
+hipError_t launch_decode_meta(const int32_t *d_slots, int B, int32_t *d_len, int32_t *d_pos,
+                              hipStream_t s);
 // the same with up to 256 slots taken from the host array (and stored to d_slots): one launch
 hipError_t launch_decode_meta_upload(const int32_t *host_slots, int32_t *d_slots, int B, int32_t *d_len, int32_t *d_pos,
                                      hipStream_t s);
-hipError_t launch_decode_meta(const int32_t *d_slots, int B, int32_t *d_len, int32_t *d_pos,
-                              hipStream_t s);
 // len[slot[i]] = was[i]
 hipError_t launch_restore_len(const int32_t *d_slots, const int32_t *d_was, int n_seqs, int32_t *d_len, hipStream_t s);
 // prefill: len[slot[s]] = cu[s+1]-cu[s]  (add != 0: += instead of =)
