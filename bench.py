@@ -32,7 +32,7 @@ DECODE_REPS = 3                    # decode steps per batch size per step; media
 # the FETCH_SIZE / WRITE_SIZE counters scaled by a plain copy (paper_2603_04716_amd/traffic_probe.py).
 # Valid only for the kernel source the counters were taken on.
 TRAFFIC = {"source": os.path.join("paper_2603_04716_amd", "csrc", "gemm_mfma.hip"),
-           "sha256": "d53a4a94b0a0f4f003b242bd4e1a4386d9b8d7948d0645631e3d0bf057a20ea0",
+           "sha256": "726d498ac414b9fa6dbabb6cda07580cbe6a29869a903cdc2e12b0b30c6748f3",
            "bytes_per_launch": 3054.3e6}
 
 

@@ -220,7 +220,8 @@ typedef struct {
  * Writes out_hidden (device [T, d]).  With a cache and slots, stores each sequence's rotated keys
  * and values into its slot and sets the slot's length to the sequence length.
  * Errors: PD_ERR_INVALID_ARG, PD_ERR_SHAPE (bad cu_seqlens), PD_ERR_KV_CAPACITY (a sequence longer
- * than max_len), PD_ERR_OOM / PD_ERR_DEVICE (workspace growth, launch failure).
+ * than max_len), PD_ERR_OOM / PD_ERR_DEVICE (workspace growth, launch failure).  After an error the
+ * slots' lengths are what they were, and the call can be made again.
  */
 pd_status pd_prefill(pd_layer *layer, const pd_tokens *tokens, pd_kv_cache *cache /* nullable */,
                      void *out_hidden, void *stream);
