@@ -32,8 +32,8 @@ DECODE_REPS = 3                    # decode steps per batch size per step; media
 # the FETCH_SIZE / WRITE_SIZE counters scaled by a plain copy (paper_2603_04716_amd/traffic_probe.py).
 # Valid only for the kernel source the counters were taken on.
 TRAFFIC = {"source": os.path.join("paper_2603_04716_amd", "csrc", "gemm_mfma.hip"),
-           "sha256": "726d498ac414b9fa6dbabb6cda07580cbe6a29869a903cdc2e12b0b30c6748f3",
-           "bytes_per_launch": 3054.3e6}
+           "sha256": "618e8951ab503889ce24ff58443d8e60e628d42833471b4585213efe973dd0b1",
+           "bytes_per_launch": 3054.2e6}
 
 
 def counted_traffic():

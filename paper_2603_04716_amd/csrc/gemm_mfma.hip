@@ -54,8 +54,11 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >>
 
 __device__ __forceinline__ float silu_fast(float z) { return z / (1.0f + __expf(-z)); }
 
-// The same for |z| < kSiluNear, bit for bit (all such z compared; -0 gives +0): the quotient by the hardware reciprocal and one correction
-// from its remainder, without the division's steps for operands and results near the ends of the exponent's range.
+// The same for |z| < kSiluNear, bit for bit (all such z compared; -0 gives +0): the quotient by the hardware reciprocal and
+// one correction from its remainder, without the division's steps for operands and results near the ends of the exponent's
+// range.  The tiles take it where all gates of a wave's eight columns are that small, else the division (an infinite gate's
+// correction would be inf - inf).  Gate/up of the 8B shape, division everywhere -> this: 8192 rows 1320 -> 1284 us, codes 672 ->
+// 657, 2048 rows of 5632 <- 1024 27.7 -> 26.5; the look at the gates costs nothing that shows.
 constexpr float kSiluNear = 87.f;
 __device__ __forceinline__ float silu_near(float z)
 {
